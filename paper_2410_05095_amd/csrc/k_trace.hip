@@ -322,23 +322,27 @@ __device__ inline uint32_t wave_key(bool hit, float t0, uint32_t slot)
     return m != 0 ? (k0 | slot) : (RC_KEY_MISS | slot);
 }
 
-// Slab test of the wave kernels for a segment 0 <= t <= 1: the entry distance, clamped to [0, 1] in one
-// median, against the exit distance.  Against max(entry, 0) <= min(exit, 1) it also accepts boxes that the
-// line meets only beyond t = 1 (beyond the light): extra visits, no change in any result, and one vector
-// operation less per child.  Finished and idle lanes carry far-plane addends of -inf (wave_mute), so their
-// exit distance is -inf (or NaN) and no box accepts them.
+// Slab test of the wave kernels for a segment 0 < t < 1: entry and exit distance each clamped to [0, 1] (the
+// clamp modifiers of v_max3 and v_min3, no instruction) and compared strictly, so that a box left before t = 0
+// (exit 0) or entered after t = 1 (entry 1) fails: 6 FMAs, v_max3, v_min3 and a compare.  A box that the segment
+// enters passes: its entry is computed below 1 (rc_ray_inv<true>), its exit is above 0 and, by the outward far
+// constants, above its entry.  (Clamping the entry alone, entry <= exit, had accepted every box whose exit lies
+// beyond t = 1, met or missed: towards a light amid the geometry, one walk could visit the whole tree.  4 point
+// lights, 1080p, 2x2 samples, 1.1M triangles: shadow pass 154.7 ms then, 1.42 ms now.)  Finished and idle lanes carry far-plane
+// addends of -inf (wave_mute), so their exit is 0 (NaN clamps to 0 as well) and no box accepts them.
 __device__ inline bool rc_slab_seg(const TravRay& r, float nx, float ny, float nz, float fx, float fy, float fz,
                                    float& t0)
 {
     const float u = fmaxf(fmaxf(fmaf(nx, r.inv[0], r.cn[0]), fmaf(ny, r.inv[1], r.cn[1])), fmaf(nz, r.inv[2], r.cn[2]));
     t0 = __builtin_amdgcn_fmed3f(u, 0.0f, 1.0f);
     const float v = fminf(fminf(fmaf(fx, r.invf[0], r.cf[0]), fmaf(fy, r.invf[1], r.cf[1])), fmaf(fz, r.invf[2], r.cf[2]));
-    return t0 <= v;
+    const float t1 = __builtin_amdgcn_fmed3f(v, 0.0f, 1.0f);
+    return t0 < t1;
 }
 
 // A lane whose ray is finished (live == 0) takes part in no slab test: its far-plane addends become -inf.  An
 // idle lane's traversal constants were never set (set == false): they become 0 first, so that every far
-// distance is -inf (or NaN for an infinite plane) and the entry distance finite (or NaN).
+// distance is -inf (or NaN for an infinite plane) and the exit clamps to 0.
 __device__ inline void wave_mute(TravRay& r, uint32_t live, bool set)
 {
 #pragma unroll
@@ -659,7 +663,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TWO || WT
                 busy = rc_shadow_ray(P.L.point[0], P.L.rect, P.nL, true, px, k, P.L.area_stream, P.cam.seed,
                                      P.cam.frame, os, nf, ray);
                 if (busy) {
-                    rc_ray_inv(ray);
+                    rc_ray_inv<!TWO && !WT>(ray);   // the flat Moller-Trumbore walk takes the clamped slab test
                     ++rays_cast;
                 }
             }
@@ -728,7 +732,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TWO || WT
                 busy = rc_shadow_ray(P.L.point[l], P.L.rect, P.nL, false, px, (uint32_t)l, P.L.area_stream,
                                      P.cam.seed, P.cam.frame, os, nf, ray);
                 if (busy) {
-                    rc_ray_inv(ray);
+                    rc_ray_inv<!TWO && !WT>(ray);   // the flat Moller-Trumbore walk takes the clamped slab test
                     ++rays_cast;
                 }
             }

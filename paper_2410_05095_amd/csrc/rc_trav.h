@@ -10,6 +10,8 @@
 
 // growth of the far-plane reciprocals (1 + 2^-20): the far slab distances round outward
 #define RC_FAR_GROW 1.000001f
+// shrink of the near-plane reciprocals of segment rays (1 - 2^-20), see rc_ray_inv
+#define RC_NEAR_SHRINK 0x1.ffffep-1f
 
 struct TravRay {
     float o[3], d[3], inv[3];
@@ -56,13 +58,18 @@ struct TravWorld {
 // cyclically (swapped when d[kz] < 0), Sx = d[kx] / d[kz], Sy = d[ky] / d[kz], Sz = 1 / d[kz] (correctly
 // rounded).  Kernels that test triangles with Moller-Trumbore never read the shear constants, so their
 // computation is dropped.
+// SEG (rays traced as segments 0 < t < 1 by the clamped slab test of the wave kernels, rc_slab_seg): the near
+// reciprocal is inv = (1 / dd) * (1 - 2^-20) and cn follows from it, so that the computed entry distance of a
+// box that the segment enters before t = 1 stays below 1 after all roundings.
+template <bool SEG = false>
 __device__ inline void rc_ray_inv(TravRay& r)
 {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         float dd = fabsf(r.d[a]) < 1e-20f ? copysignf(1e-20f, r.d[a]) : r.d[a];
-        r.inv[a] = 1.0f / dd;
-        r.invf[a] = r.inv[a] * RC_FAR_GROW;
+        const float i = 1.0f / dd;
+        r.inv[a] = SEG ? i * RC_NEAR_SHRINK : i;
+        r.invf[a] = i * RC_FAR_GROW;
         const float c = -(r.o[a] * r.inv[a]);
         r.cn[a] = c - (fabsf(c) * 0x1p-21f + 0x1p-120f);
         const float e = -(r.o[a] * r.invf[a]);
