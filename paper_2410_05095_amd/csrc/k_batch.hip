@@ -10,7 +10,7 @@
 // registers, and no kernel keeps a lane's FP64 shading state across a traversal.  The traversal, shading
 // and resolve use the same device code as the single-view kernels, so every view is bit-identical to its
 // single-view render whatever the form and tuning.
-#include "rc_trav.h"
+#include "rc_wave.h"
 
 namespace {
 
@@ -351,6 +351,85 @@ __global__ __launch_bounds__(256) void k_batch_setup(BatchParams P)
         }
         P.setup[2 * ((size_t)V.setup_first + s)] = a;
         P.setup[2 * ((size_t)V.setup_first + s) + 1] = b;
+        if (P.wave) V.shadow[s] = 0u;   // the wave-uniform pass adds one light's bit at a time
+    }
+}
+
+// Point-light shadow rays of the three-kernel form by wave-uniform walks (wave_occluded): a unit of work is 64
+// consecutive samples of one view (an 8x8-pixel tile, or 4x4 pixels x 4 samples, whatever the tuning's tile) and
+// one of its lights.  Node and triangle records come through the scalar cache once per wave, where the per-lane
+// kernel's divergent 16-byte loads keep the texture units 91% busy and its vector pipe 70%.
+template <bool BIG, bool COUNT>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void k_batch_wave(BatchParams P)
+{
+    typedef const __attribute__((address_space(4))) DevView c_view;
+    typedef const __attribute__((address_space(4))) DevScene c_scene;
+    typedef const __attribute__((address_space(4))) float c_float;
+    const uint32_t lane = __lane_id();
+    uint32_t rays_cast = 0, node_visits = 0, tri_tests = 0;
+    const XcdQueue<64> queue(P.w.counters, 4u, P.n_units);
+    DevScene none;   // flat walks read the scene through the two array bases alone
+    uint32_t pos = 0, pos_end = 0;
+    for (;;) {
+        if (pos == pos_end) {
+            pos = queue.claim(P.claim);
+            pos_end = pos + P.claim;
+        }
+        const uint32_t q = pos++;
+        if (queue.exhausted(q)) break;
+        const uint64_t u64 = queue.at(q);
+        if (u64 >= P.n_units) continue;
+        const uint32_t unit = (uint32_t)u64;
+        // the unit's view: the lanes compare 64 views' first units at a time
+        uint32_t v = 0;
+        for (uint32_t base = 0; base < P.n_views; base += 64u) {
+            const uint32_t i = min(base + lane, P.n_views - 1u);
+            const uint32_t below = (uint32_t)__popcll(__ballot(base + lane < P.n_views && P.unit_first[i] <= unit));
+            if (below == 0u) break;
+            v = base + below - 1u;
+            if (below < 64u) break;
+        }
+        v = __builtin_amdgcn_readfirstlane(v);
+        c_view* V = (c_view*)(const void*)(P.views + v);
+        const uint32_t n_l = V->n_lights;
+        const uint32_t local = unit - __builtin_amdgcn_readfirstlane(P.unit_first[v]);
+        const uint32_t packet = local / n_l, l = local - packet * n_l;
+        DevCamera cam;   // the fields that rc_item_to_sample reads
+        cam.width = V->cam.width;
+        cam.height = V->cam.height;
+        cam.ssaa = V->cam.ssaa;
+        uint32_t px = 0, pk = 0;
+        const bool in_image = rc_item_to_sample(cam, packet * 64u + lane, px, pk);
+        const uint32_t s = px * (uint32_t)(cam.ssaa * cam.ssaa) + pk;
+        c_float* Lp = (c_float*)(const void*)(P.lights + 6 * (size_t)(V->light_first + l));
+        const float light[3] = {Lp[0], Lp[1], Lp[2]};
+        TravRay ray;
+        bool busy = false;
+        if (in_image) {
+            const float4* e = P.setup + 2 * ((size_t)V->setup_first + s);
+            const float4 a = e[0], b = e[1];
+            if (a.w != 0.0f) {
+                const float os[3] = {a.x, a.y, a.z}, nf[3] = {b.x, b.y, b.z};
+                busy = rc_shadow_ray(light, nullptr, nullptr, false, px, l, 0u, 0u, 0u, os, nf, ray);
+                if (busy) {
+                    rc_ray_inv<true>(ray);
+                    ++rays_cast;
+                }
+            }
+        }
+        c_scene* S = (c_scene*)(const void*)(P.scenes + V->scene);
+        const uint32_t occ = wave_occluded<false, false, BIG, COUNT>(none, (const char*)S->nodes, (const char*)S->tris, ray,
+                                                                    busy, node_visits, tri_tests, P.w.error_flag);
+        if (busy && occ == 0u) atomicOr(V->shadow + s, 1u << l);
+    }
+    if (P.w.ray_count) {
+        unsigned long long cnt[3] = {rays_cast, node_visits, tri_tests};
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            unsigned long long c = cnt[k];
+            for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+            if (lane == 0) atomicAdd(P.w.ray_count + 2 * k + 1, c);
+        }
     }
 }
 
@@ -360,6 +439,7 @@ static const void* batch_kernel(int pass)
     case 1: return reinterpret_cast<const void*>(&k_batch<1>);
     case 2: return reinterpret_cast<const void*>(&k_batch<2>);
     case 3: return reinterpret_cast<const void*>(&k_batch<3>);
+    case 4: return reinterpret_cast<const void*>(&k_batch_wave<true, false>);
     default: return reinterpret_cast<const void*>(&k_batch<0>);
     }
 }
@@ -369,7 +449,7 @@ int rc_batch_max_blocks_per_cu(int device, int pass)
     int blocks = 0;
     (void)device;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, batch_kernel(pass), BLOCK,
-                                                     TravStack<SL, BLOCK, true>::lds_bytes()) != hipSuccess)
+                                                     pass == 4 ? 0 : TravStack<SL, BLOCK, true>::lds_bytes()) != hipSuccess)
         blocks = 1;
     return blocks < 1 ? 1 : blocks;
 }
@@ -382,7 +462,11 @@ void rc_launch_batch(const BatchParams& P, int pass, int grid, hipStream_t st)
     case 1: hipLaunchKernelGGL(k_batch<1>, dim3(grid), dim3(BLOCK), lds, st, P); break;
     case 2:
         hipLaunchKernelGGL(k_batch_setup, dim3((P.n_items + 255) / 256), dim3(256), 0, st, P);
-        hipLaunchKernelGGL(k_batch<2>, dim3(grid), dim3(BLOCK), lds, st, P);
+        if (P.wave == 0) hipLaunchKernelGGL(k_batch<2>, dim3(grid), dim3(BLOCK), lds, st, P);
+        else if (P.wave == 1 && !P.w.ray_count) hipLaunchKernelGGL((k_batch_wave<false, false>), dim3(grid), dim3(BLOCK), 0, st, P);
+        else if (P.wave == 1) hipLaunchKernelGGL((k_batch_wave<false, true>), dim3(grid), dim3(BLOCK), 0, st, P);
+        else if (!P.w.ray_count) hipLaunchKernelGGL((k_batch_wave<true, false>), dim3(grid), dim3(BLOCK), 0, st, P);
+        else hipLaunchKernelGGL((k_batch_wave<true, true>), dim3(grid), dim3(BLOCK), 0, st, P);
         break;
     case 3: hipLaunchKernelGGL(k_batch<3>, dim3(grid), dim3(BLOCK), lds, st, P); break;
     default: hipLaunchKernelGGL(k_batch<0>, dim3(grid), dim3(BLOCK), lds, st, P); break;

@@ -982,7 +982,12 @@ struct BatchPlan {
     uint32_t n_items = 0;
     uint32_t max_stack = 0;
     uint64_t n_samples = 0;    // samples of all views: entries of the three-kernel form's shadow-ray setup
-    size_t bytes = 0, off_views = 0, off_lights = 0;
+    size_t bytes = 0, off_views = 0, off_lights = 0, off_units = 0;
+    // wave-uniform shadow pass: units of 64 samples and one light, first unit per view, rc_wave_work of
+    // all views, and whether every scene's tree is within the walk's limits
+    std::vector<uint32_t> unit_first;
+    uint64_t n_units = 0, wave_work = 0;
+    bool wave_ok = true;
 };
 
 int plan_batch(rc_scene* const* scenes, uint32_t n_scenes, const rc_view* views, uint32_t n_views,
@@ -996,6 +1001,7 @@ int plan_batch(rc_scene* const* scenes, uint32_t n_scenes, const rc_view* views,
         if (scenes[i]->two_level || scenes[i]->watertight) return RC_ERR_UNSUPPORTED;
         bp.scenes.push_back(dev_scene(scenes[i]));
         bp.max_stack = std::max(bp.max_stack, scenes[i]->hb.max_stack);
+        bp.wave_ok = bp.wave_ok && rc_wave_ok(bp.scenes.back());
     }
     uint64_t items = 0;
     for (uint32_t v = 0; v < n_views; ++v) {
@@ -1023,6 +1029,9 @@ int plan_batch(rc_scene* const* scenes, uint32_t n_scenes, const rc_view* views,
         d.setup_first = (uint32_t)bp.n_samples;
         bp.n_samples += (uint64_t)cam->width * cam->height * cam->ssaa * cam->ssaa;
         if (bp.n_samples >= (1ull << 32)) return RC_ERR_UNSUPPORTED;
+        bp.unit_first.push_back((uint32_t)std::min<uint64_t>(bp.n_units, 0xFFFFFFFFu));
+        bp.n_units += (uint64_t)(rc_n_items(cam->width, cam->height, cam->ssaa) / 64u) * V.n_lights;
+        bp.wave_work += rc_wave_work((uint64_t)cam->width * cam->height * cam->ssaa * cam->ssaa, V.n_lights);
         d.rgba = V.d_rgba;
         d.hit = reinterpret_cast<uint4*>(V.d_hit);
         d.shadow = V.n_lights > 0 ? V.d_shadow : nullptr;
@@ -1034,7 +1043,8 @@ int plan_batch(rc_scene* const* scenes, uint32_t n_scenes, const rc_view* views,
     bp.n_items = (uint32_t)items;
     bp.off_views = align16(sizeof(DevScene) * n_scenes);
     bp.off_lights = bp.off_views + align16(sizeof(DevView) * n_views);
-    bp.bytes = bp.off_lights + align16(sizeof(float) * 6 * std::max<uint32_t>(n_lights_total, 1));
+    bp.off_units = bp.off_lights + align16(sizeof(float) * 6 * std::max<uint32_t>(n_lights_total, 1));
+    bp.bytes = bp.off_units + align16(sizeof(uint32_t) * n_views);
     return RC_OK;
 }
 
@@ -1056,9 +1066,19 @@ int batch_launch(rc_ctx* c, rc_scene* const* scenes, uint32_t n_scenes, const rc
     // persistent grid of each launch: the requested waves per SIMD, capped at that kernel's own occupancy
     const int blocks_req = std::max(1, (int)(t.waves_per_simd * 4) / (RC_TRACE_BLOCK / 64));
     int grids[4] = {0, 0, 0, 0};
+    // The shadow pass of the three-kernel form by wave-uniform walks where a single view of as many segments would
+    // take them (rc_launch_shadow; shadow pass per lane / wave-uniform: 2 views with 4.9M segments 0.53 / 0.32 ms, 12
+    // views with 17.1M 3.33 / 1.46 ms, 64 views with 97.2M 14.96 / 9.98 ms).  An untuned or largest waves_per_simd
+    // gives that kernel its own largest grid.
+    const bool wave = t.passes == 3 && bp.wave_ok && bp.n_units > 0 && bp.n_units < (1ull << 32) &&
+                      (bp.wave_work >= RC_WAVE_WORK || (flags & RC_FLAG_WAVE));
     for (int p = 0; p < 4; ++p)
         if ((p == 0) == (t.passes == 1))
             grids[p] = n_cu * std::min(blocks_req, rc_batch_max_blocks_per_cu(c->device, p));
+    if (wave) {
+        const int most = rc_batch_max_blocks_per_cu(c->device, 4);
+        grids[2] = n_cu * ((int)t.waves_per_simd >= batch_form_wps(c->device, 3) ? most : std::min(blocks_req, most));
+    }
     const int grid = std::max(std::max(grids[0], grids[1]), std::max(grids[2], grids[3]));
 
     // overflow stack area for this grid
@@ -1094,6 +1114,7 @@ int batch_launch(rc_ctx* c, rc_scene* const* scenes, uint32_t n_scenes, const rc
         float* L = reinterpret_cast<float*>(c->h_table + bp.off_lights) + 6 * l;
         for (int k = 0; k < 3; ++k) { L[k] = lights[l].position[k]; L[3 + k] = lights[l].intensity[k]; }
     }
+    memcpy(c->h_table + bp.off_units, bp.unit_first.data(), sizeof(uint32_t) * n_views);
     RC_HIP(hipMemcpyAsync(c->d_table, c->h_table, bp.bytes, hipMemcpyHostToDevice, c->stream));
     RC_HIP(hipEventRecord(c->ev_staging, c->stream));
     c->staging_pending = true;
@@ -1124,6 +1145,11 @@ int batch_launch(rc_ctx* c, rc_scene* const* scenes, uint32_t n_scenes, const rc
     P.w.n_lanes = (uint32_t)grid * RC_TRACE_BLOCK;
     P.w.error_flag = c->d_counters + 8;
     P.w.ray_count = (flags & RC_FLAG_COUNT) ? c->d_rays : nullptr;   // counts on request only
+
+    P.wave = !wave ? 0u : bp.max_stack <= 64 ? 1u : 2u;
+    P.n_units = bp.n_units;
+    P.unit_first = reinterpret_cast<const uint32_t*>(c->d_table + bp.off_units);
+    P.claim = (uint32_t)std::min<uint64_t>(4, std::max<uint64_t>(1, bp.n_units / ((uint64_t)std::max(grids[2], 1) * (RC_TRACE_BLOCK / 64) * 64)));
 
     bool timing = (flags & RC_FLAG_TIMING) != 0;
     if (timing) RC_HIP(hipEventRecord(c->ev[0], c->stream));

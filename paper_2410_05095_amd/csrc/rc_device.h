@@ -166,11 +166,3 @@ __device__ inline bool rc_item_to_sample(const DevCamera& c, uint32_t item, uint
     pixel = j * (uint32_t)c.width + i;
     return true;
 }
-
-__host__ __device__ inline uint32_t rc_n_items(int width, int height, int ssaa)
-{
-    uint32_t spp = (uint32_t)(ssaa * ssaa);
-    uint32_t tw = spp == 1 ? 8u : 4u;
-    uint32_t tx = ((uint32_t)width + tw - 1) / tw, ty = ((uint32_t)height + tw - 1) / tw;
-    return tx * ty * 64u;
-}

@@ -56,12 +56,34 @@ struct DevScene {
     const float* nrm;         // n_vertices x 3 vertex normals (current pose), or NULL
 };
 
+// whether the wave-uniform shadow kernels can walk the scene's tree: 32-bit byte offsets of nodes and triangles, at
+// most 128 stack entries
+inline bool rc_wave_ok(const DevScene& sc)
+{
+    return sc.max_stack <= 128 && sc.n_nodes < (1u << 25) && (uint64_t)sc.n_tris * 48u < (1ull << 32);
+}
+
+// Size of a point-light pass for the choice between the wave-uniform and the per-lane shadow kernels: samples x
+// (lights + 1) rather than the samples x lights segments, since with more units of fewer samples the longest walk
+// weighs more.  Wave-uniform from RC_WAVE_WORK on (figures at rc_launch_shadow).
+constexpr uint64_t RC_WAVE_WORK = 3500000;
+inline uint64_t rc_wave_work(uint64_t samples, uint64_t n_lights) { return n_lights ? samples * (n_lights + 1) : 0; }
+
 struct DevCamera {
     float eye[3], f[3], r[3], u[3];
     float tan_half, x_scale;
     int32_t width, height, ssaa;
     uint32_t seed, frame;
 };
+
+// work items of an image in tiles of 64 samples (8x8 pixels, or 4x4 pixels x 4 samples)
+__host__ __device__ inline uint32_t rc_n_items(int width, int height, int ssaa)
+{
+    uint32_t spp = (uint32_t)(ssaa * ssaa);
+    uint32_t tw = spp == 1 ? 8u : 4u;
+    uint32_t tx = ((uint32_t)width + tw - 1) / tw, ty = ((uint32_t)height + tw - 1) / tw;
+    return tx * ty * 64u;
+}
 
 struct DevLights {
     int n_point;
@@ -179,10 +201,15 @@ struct BatchParams {
     uint32_t n_items;
     BatchTune tune;
     TraceWork w;
+    // shadow pass by wave-uniform walks (wave != 0; 2: some tree needs the two-register stack): units of 64 samples
+    // of one view and one light, view v's from unit_first[v] on; claim: units a wave takes per atomic
+    uint32_t wave, claim;
+    uint64_t n_units;
+    const uint32_t* unit_first;
 };
 
 // pass 0: the one-kernel form; 1, 2, 3: camera rays, shadow rays, shading + resolve (work-queue slots 3, 4, 5);
-// the shadow pass first fills P.setup from the camera hits
+// the shadow pass first fills P.setup from the camera hits; with P.wave it runs as kernel 4 (rc_batch_max_blocks_per_cu)
 void rc_launch_batch(const BatchParams& P, int pass, int grid, hipStream_t st);
 int rc_batch_max_blocks_per_cu(int device, int pass);
 
