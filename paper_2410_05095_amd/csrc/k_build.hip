@@ -778,13 +778,13 @@ hipError_t rc_build_bvh_device(const float* d_pos, const uint32_t* d_idx, uint32
 // the exact FP32 union boxes, the first minimum over (axis, k) in order; a range of n <= max_leaf triangles
 // stays a leaf when no split exists or n <= node_cost + best / area(node); a range whose centroids coincide is
 // halved.  Ranges above SAH_SMALL triangles are split level by level, every workgroup binning a chunk of one
-// range; each smaller range is then built to the leaves by one wave.  Partitions are stable, so the build is
+// range; each smaller range is then built to the leaves by one workgroup.  Partitions are stable, so the build is
 // deterministic.  The binary tree is collapsed to 4-wide like the radix trees (explicit leaves).
 namespace {
 
 constexpr int SAH_NB_MAX = 64;
-constexpr uint32_t SAH_SMALL = 1024;
-constexpr uint32_t SAH_CHUNK = 8192;
+constexpr uint32_t SAH_SMALL = 512;
+constexpr uint32_t SAH_CHUNK = 2048;   // 1M triangles: binning passes 1.38 ms at 8192 (122 workgroups), 0.80 at 2048, 0.72 at 1024
 constexpr int SAH_BIN_WORDS = 8;   // ordered lo[3], hi[3], count, pad
 
 __device__ inline uint32_t f2o(float f)
@@ -818,7 +818,6 @@ struct SahTree {
     int2* child;     // (left, right), or (-1, -1) for a leaf
     int2* range;     // (first slot, count)
     Box6* box;
-    uint32_t* node_ctr;
 };
 
 // The split decision of one range, by one wave: from the bins of the three axes (box as ordered words, count)
@@ -1028,7 +1027,7 @@ __global__ __launch_bounds__(64) void k_sah_split(const SahTask* tasks, const ui
     sah_decide(bins + (size_t)t * 3 * NB * SAH_BIN_WORDS, NB, clo, chi, axis, split, nl, cost);
     if (axis < 0) nl = task.count / 2;
     if (__lane_id() == 0) {
-        const uint32_t l = atomicAdd(T.node_ctr, 2u), r = l + 1;
+        const uint32_t l = 2u * (task.first + nl), r = l + 1;   // every slot is split at once: numbers are unique
         write_sah_node(T, task.node, blo, bhi, (int)l, (int)r, task.first, task.count);
         const SahTask kids[2] = {{l, task.first, nl, 0u}, {r, task.first + nl, task.count - nl, 0u}};
         for (int s = 0; s < 2; ++s) {
@@ -1130,130 +1129,209 @@ __global__ __launch_bounds__(256) void k_sah_copy(const uint32_t* src, const uin
     for (uint32_t i = chunk_begin[c] + threadIdx.x; i < chunk_end[c]; i += 256) dst[i] = src[i];
 }
 
-// ---- small ranges: one wave builds the whole subtree (depth first, its pending ranges in stack[first ..]) ----
-__global__ __launch_bounds__(256) void k_sah_small(const SahTask* small, uint32_t n_small, uint32_t* ids,
-                                                   uint32_t* tmp, const Box6* tri_box, const float4* cen, int NB,
-                                                   uint32_t max_leaf, double node_cost, SahTree T, uint4* stack)
+// ---- small ranges: one workgroup builds the whole subtree of a range of at most SAH_SMALL triangles ----
+// Boxes, centroids and the order of the range's triangles stay in LDS; the subtree grows level by level, its waves
+// taking the level's ranges in turn.  Ranges of up to SAH_TINY triangles (nineteen in twenty) are split without
+// bins: lane (axis, i) sums up the two sides of the split after triangle i's bin directly, 3 n candidates against the n
+// triangles.  A split between bins that holds the same triangles on each side is met first right after the last
+// occupied bin of its left side, so the candidates are those the bin sweep would choose from, with the same
+// costs.  Larger ranges are binned in LDS and swept.  What bounds it is the chain of dependent steps of each range, so
+// it wants many ranges in flight: with one wave per range of up to 1024 triangles, its data in global memory and
+// node numbers from one global counter, 1M triangles took 6.5 ms here; BUILD_SMALL_MS now.
+constexpr int SAH_SMALL_WAVES = 8;
+constexpr uint32_t SAH_TINY = 21;   // 3 n lanes
+
+struct SahSmallLds {
+    float box[6][SAH_SMALL];
+    float cen[3][SAH_SMALL];
+    uint32_t gid[SAH_SMALL];
+    uint16_t ord[SAH_SMALL], tmp[SAH_SMALL];
+    uint32_t list[2][SAH_SMALL];    // ranges of this level and the next: first | (count << 11) | (right child << 22)
+    uint32_t n_list[2];
+};
+
+__device__ inline void sah_wave_sync()
 {
-    __shared__ uint32_t lbins[4][3 * SAH_NB_MAX * SAH_BIN_WORDS];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__global__ __launch_bounds__(64 * SAH_SMALL_WAVES) void k_sah_small(const SahTask* small, uint32_t* ids,
+                                                                    const Box6* tri_box, const float4* cen, int NB,
+                                                                    uint32_t max_leaf, double node_cost, SahTree T)
+{
+    extern __shared__ uint32_t sah_lds[];
+    SahSmallLds& L = *reinterpret_cast<SahSmallLds*>(sah_lds);
     const uint32_t lane = __lane_id(), wave = threadIdx.x >> 6;
-    const uint32_t ti = blockIdx.x * 4 + wave;
-    if (ti >= n_small) return;   // whole waves only: no workgroup barrier below
-    uint32_t* lb = lbins[wave];
-    const SahTask root = small[ti];
-    uint4* stk = stack + root.first;
-    uint32_t sp = 0;
-    uint32_t node = root.node, f = root.first, n = root.count;
     const int words = 3 * NB * SAH_BIN_WORDS;
-    for (;;) {
-        // bounds of the range
-        float v[12];
-        for (int k = 0; k < 12; ++k) v[k] = (k % 6) < 3 ? INFINITY : -INFINITY;
-        for (uint32_t i = f + lane; i < f + n; i += 64) {
-            const uint32_t t = ids[i];
-            const Box6 b = tri_box[t];
-            const float4 q = cen[t];
-            const float cc[3] = {q.x, q.y, q.z};
-            for (int k = 0; k < 3; ++k) {
-                v[k] = fminf(v[k], b.lo[k]); v[3 + k] = fmaxf(v[3 + k], b.hi[k]);
-                v[6 + k] = fminf(v[6 + k], cc[k]); v[9 + k] = fmaxf(v[9 + k], cc[k]);
-            }
-        }
-        for (int off = 32; off > 0; off >>= 1)
-            for (int k = 0; k < 12; ++k) {
-                const float o = __shfl_xor(v[k], off);
-                v[k] = (k % 6) < 3 ? fminf(v[k], o) : fmaxf(v[k], o);
-            }
-        const float blo[3] = {v[0], v[1], v[2]}, bhi[3] = {v[3], v[4], v[5]};
-        const float clo[3] = {v[6], v[7], v[8]}, chi[3] = {v[9], v[10], v[11]};
-        bool leaf = n == 1;
-        int axis = -1, split = 0;
-        uint32_t nl = 0;
-        if (!leaf) {
-            for (int i = lane; i < words; i += 64) {
-                const int w = i % SAH_BIN_WORDS;
-                lb[i] = w < 3 ? O_POS_INF : (w < 6 ? O_NEG_INF : 0u);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            for (uint32_t i = f + lane; i < f + n; i += 64) {
-                const uint32_t t = ids[i];
-                const Box6 b = tri_box[t];
-                const float4 q = cen[t];
-                const float cc[3] = {q.x, q.y, q.z};
-                for (int ax = 0; ax < 3; ++ax) {
-                    const float ext = chi[ax] - clo[ax];
-                    if (!(ext > 0.0f)) continue;
-                    const int k = sah_bin(cc[ax], clo[ax], (double)NB / (double)ext, NB);
-                    uint32_t* w = lb + ((size_t)ax * NB + k) * SAH_BIN_WORDS;
-                    for (int j = 0; j < 3; ++j) { atomicMin(w + j, f2o(b.lo[j])); atomicMax(w + 3 + j, f2o(b.hi[j])); }
-                    atomicAdd(w + 6, 1u);
-                }
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            double best;
-            sah_decide(lb, NB, clo, chi, axis, split, nl, best);
-            const double parea = sah_area(blo, bhi);
-            const double split_cost = parea > 0.0 ? node_cost + best / parea : (double)n;
-            leaf = n <= max_leaf && (axis < 0 || (double)n <= split_cost);
-            __builtin_amdgcn_wave_barrier();
-        }
-        if (leaf) {
-            if (lane == 0) write_sah_node(T, node, blo, bhi, -1, -1, f, n);
-            if (sp == 0) break;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            const uint4 e = stk[--sp];
-            node = e.x; f = e.y; n = e.z;
-            continue;
-        }
-        if (axis < 0) {
-            nl = n / 2;   // coinciding centroids: halve the range, order kept
-        } else {
-            // stable partition into tmp, then back
-            const float lo = clo[axis];
-            const double scale = (double)NB / (double)(chi[axis] - clo[axis]);
-            uint32_t lpos = f, rpos = f + nl;
-            for (uint32_t i0 = f; i0 < f + n; i0 += 64) {
-                const uint32_t i = i0 + lane;
-                const bool valid = i < f + n;
-                const uint32_t t = valid ? ids[i] : 0u;
-                float c = 0.0f;
-                if (valid) {
-                    const float4 q = cen[t];
-                    c = axis == 0 ? q.x : (axis == 1 ? q.y : q.z);
-                }
-                const bool left = valid && sah_bin(c, lo, scale, NB) < split;
-                const uint64_t m = __ballot(left), mv = __ballot(valid);
-                const uint64_t below = (1ull << lane) - 1ull;
-                const uint32_t rl = (uint32_t)__popcll(m & below), rr = (uint32_t)__popcll(mv & ~m & below);
-                const uint32_t dst = left ? lpos + rl : rpos + rr;
-                if (valid && dst < f + n) tmp[dst] = t;   // always in range: the bins counted the same decisions
-                lpos += (uint32_t)__popcll(m);
-                rpos += (uint32_t)__popcll(mv & ~m);
-            }
-            // the lanes exchange ids through global memory: order the stores before the other lanes' loads
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            for (uint32_t i = f + lane; i < f + n; i += 64) ids[i] = tmp[i];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        }
-        uint32_t l = 0;
-        if (lane == 0) l = atomicAdd(T.node_ctr, 2u);
-        l = (uint32_t)__builtin_amdgcn_readfirstlane((int)l);
-        if (lane == 0) write_sah_node(T, node, blo, bhi, (int)l, (int)(l + 1), f, n);
-        stk[sp] = make_uint4(l + 1, f + nl, n - nl, 0u);   // every lane writes (and later reads) the same entry
-        ++sp;
-        node = l;
-        n = nl;
+    uint32_t* lb = sah_lds + sizeof(SahSmallLds) / 4 + wave * words;
+    const SahTask root = small[blockIdx.x];
+    const uint32_t base = root.first;
+    for (uint32_t i = threadIdx.x; i < root.count; i += 64 * SAH_SMALL_WAVES) {
+        const uint32_t t = ids[base + i];
+        const Box6 b = tri_box[t];
+        const float4 q = cen[t];
+        for (int k = 0; k < 3; ++k) { L.box[k][i] = b.lo[k]; L.box[3 + k][i] = b.hi[k]; }
+        L.cen[0][i] = q.x; L.cen[1][i] = q.y; L.cen[2][i] = q.z;
+        L.gid[i] = t;
+        L.ord[i] = (uint16_t)i;
     }
+    if (threadIdx.x == 0) {
+        L.list[0][0] = root.count << 11;
+        L.n_list[0] = 1u;
+        L.n_list[1] = 0u;
+    }
+    __syncthreads();
+    for (uint32_t lev = 0;; ++lev) {
+        const uint32_t cur = lev & 1u, n_cur = L.n_list[cur];
+        if (n_cur == 0u) break;
+        for (uint32_t it = wave; it < n_cur; it += SAH_SMALL_WAVES) {
+            const uint32_t e = __builtin_amdgcn_readfirstlane(L.list[cur][it]);
+            const uint32_t f = e & 0x7FFu, n = (e >> 11) & 0x7FFu;
+            // children of the split at slot s are nodes 2 s and 2 s + 1, so a range knows its node
+            const uint32_t node = lev == 0 ? root.node : ((e >> 22) ? 2u * (base + f) + 1u : 2u * (base + f + n));
+            float v[12];   // box lo, hi, centroid lo, hi of the range
+            for (int k = 0; k < 12; ++k) v[k] = (k % 6) < 3 ? INFINITY : -INFINITY;
+            auto take = [&](uint32_t t) {
+                for (int k = 0; k < 3; ++k) {
+                    v[k] = fminf(v[k], L.box[k][t]); v[3 + k] = fmaxf(v[3 + k], L.box[3 + k][t]);
+                    v[6 + k] = fminf(v[6 + k], L.cen[k][t]); v[9 + k] = fmaxf(v[9 + k], L.cen[k][t]);
+                }
+            };
+            const bool tiny = n <= SAH_TINY;
+            if (tiny) {
+                for (uint32_t j = 0; j < n; ++j) take(L.ord[f + j]);
+            } else {
+                for (uint32_t i = f + lane; i < f + n; i += 64) take(L.ord[i]);
+                for (int off = 32; off > 0; off >>= 1)
+                    for (int k = 0; k < 12; ++k) {
+                        const float o = __shfl_xor(v[k], off);
+                        v[k] = (k % 6) < 3 ? fminf(v[k], o) : fmaxf(v[k], o);
+                    }
+            }
+            const float blo[3] = {v[0], v[1], v[2]}, bhi[3] = {v[3], v[4], v[5]};
+            const float clo[3] = {v[6], v[7], v[8]}, chi[3] = {v[9], v[10], v[11]};
+            bool leaf = n == 1;
+            int axis = -1, split = 0, my_bin = 0;
+            uint32_t nl = 0;
+            double best = INFINITY;
+            if (!leaf && tiny) {
+                const uint32_t ax = lane / n, i = lane - ax * n;
+                uint32_t bnl = 0;
+                int bidx = 0x7FFFFFFF;
+                const float lo_a = ax == 0u ? clo[0] : (ax == 1u ? clo[1] : clo[2]);
+                const float ext = (ax == 0u ? chi[0] : (ax == 1u ? chi[1] : chi[2])) - lo_a;
+                const bool cand = ax < 3u && ext > 0.0f;
+                if (cand) my_bin = sah_bin(L.cen[ax][L.ord[f + i]], lo_a, (double)NB / (double)ext, NB);
+                float pl[3], ph[3], sl[3], sh[3];
+                for (int k = 0; k < 3; ++k) { pl[k] = sl[k] = INFINITY; ph[k] = sh[k] = -INFINITY; }
+                for (uint32_t j = 0; j < n; ++j) {
+                    const uint32_t t = L.ord[f + j];
+                    const bool left = __shfl(my_bin, (int)min(ax * n + j, 63u)) <= my_bin;
+                    bnl += left ? 1u : 0u;
+                    for (int k = 0; k < 3; ++k) {
+                        const float lo = L.box[k][t], hi = L.box[3 + k][t];
+                        pl[k] = fminf(pl[k], left ? lo : INFINITY); ph[k] = fmaxf(ph[k], left ? hi : -INFINITY);
+                        sl[k] = fminf(sl[k], left ? INFINITY : lo); sh[k] = fmaxf(sh[k], left ? -INFINITY : hi);
+                    }
+                }
+                if (cand && bnl < n) {
+                    best = sah_area(pl, ph) * (double)bnl + sah_area(sl, sh) * (double)(n - bnl);
+                    bidx = best < INFINITY ? (int)ax * NB + my_bin + 1 : bidx;
+                }
+                // first minimum over (axis, split) in order
+                for (int off = 32; off > 0; off >>= 1) {
+                    const double oc = __shfl_xor(best, off);
+                    const int oi = __shfl_xor(bidx, off);
+                    const uint32_t on = __shfl_xor(bnl, off);
+                    if (oc < best || (oc == best && oi < bidx)) { best = oc; bidx = oi; bnl = on; }
+                }
+                if (bidx != 0x7FFFFFFF) {
+                    axis = bidx / NB;
+                    split = bidx - axis * NB;
+                    nl = bnl;
+                }
+            } else if (!leaf) {
+                for (int i = lane; i < words; i += 64) {
+                    const int w = i % SAH_BIN_WORDS;
+                    lb[i] = w < 3 ? O_POS_INF : (w < 6 ? O_NEG_INF : 0u);
+                }
+                sah_wave_sync();
+                double scale[3];
+                for (int ax = 0; ax < 3; ++ax) scale[ax] = (double)NB / (double)(chi[ax] - clo[ax]);
+                for (uint32_t i = f + lane; i < f + n; i += 64) {
+                    const uint32_t t = L.ord[i];
+                    uint32_t o[6];
+                    for (int k = 0; k < 6; ++k) o[k] = f2o(L.box[k][t]);
+                    for (int ax = 0; ax < 3; ++ax) {
+                        if (!(chi[ax] - clo[ax] > 0.0f)) continue;
+                        const int k = sah_bin(L.cen[ax][t], clo[ax], scale[ax], NB);
+                        uint32_t* w = lb + (ax * NB + k) * SAH_BIN_WORDS;
+                        for (int j = 0; j < 3; ++j) { atomicMin(w + j, o[j]); atomicMax(w + 3 + j, o[3 + j]); }
+                        atomicAdd(w + 6, 1u);
+                    }
+                }
+                sah_wave_sync();
+                sah_decide(lb, NB, clo, chi, axis, split, nl, best);
+                sah_wave_sync();
+            }
+            if (!leaf) {
+                const double parea = sah_area(blo, bhi);
+                const double split_cost = parea > 0.0 ? node_cost + best / parea : (double)n;
+                leaf = n <= max_leaf && (axis < 0 || (double)n <= split_cost);
+            }
+            if (leaf) {
+                if (lane == 0) write_sah_node(T, node, blo, bhi, -1, -1, base + f, n);
+                continue;
+            }
+            if (axis < 0) {
+                nl = n / 2;   // coinciding centroids: halve the range, order kept
+            } else if (n <= 64u) {
+                // stable partition in place: every lane holds its slot's triangle before any is written
+                const bool valid = lane < n;
+                const uint16_t t = valid ? L.ord[f + lane] : (uint16_t)0;
+                int k;
+                if (tiny) k = __shfl(my_bin, (int)min((uint32_t)axis * n + lane, 63u));
+                else k = sah_bin(L.cen[axis][t], clo[axis], (double)NB / (double)(chi[axis] - clo[axis]), NB);
+                const bool left = valid && k < split;
+                const uint64_t m = __ballot(left), mv = __ballot(valid), below = (1ull << lane) - 1ull;
+                const uint32_t dst = left ? (uint32_t)__popcll(m & below) : nl + (uint32_t)__popcll(mv & ~m & below);
+                sah_wave_sync();
+                if (valid && dst < n) L.ord[f + dst] = t;   // always in range: the candidates counted the same decisions
+                sah_wave_sync();
+            } else {
+                const float lo = clo[axis];
+                const double scale = (double)NB / (double)(chi[axis] - clo[axis]);
+                uint32_t lpos = f, rpos = f + nl;
+                for (uint32_t i0 = f; i0 < f + n; i0 += 64) {
+                    const uint32_t i = i0 + lane;
+                    const bool valid = i < f + n;
+                    const uint16_t t = valid ? L.ord[i] : (uint16_t)0;
+                    const bool left = valid && sah_bin(L.cen[axis][t], lo, scale, NB) < split;
+                    const uint64_t m = __ballot(left), mv = __ballot(valid), below = (1ull << lane) - 1ull;
+                    const uint32_t dst = left ? lpos + (uint32_t)__popcll(m & below) : rpos + (uint32_t)__popcll(mv & ~m & below);
+                    if (valid && dst < f + n) L.tmp[dst] = t;   // always in range: the bins counted the same decisions
+                    lpos += (uint32_t)__popcll(m);
+                    rpos += (uint32_t)__popcll(mv & ~m);
+                }
+                sah_wave_sync();
+                for (uint32_t i = f + lane; i < f + n; i += 64) L.ord[i] = L.tmp[i];
+                sah_wave_sync();
+            }
+            if (lane == 0) {
+                const uint32_t s = base + f + nl;
+                write_sah_node(T, node, blo, bhi, (int)(2u * s), (int)(2u * s + 1u), base + f, n);
+                const uint32_t at = atomicAdd(&L.n_list[cur ^ 1u], 2u);
+                L.list[cur ^ 1u][at] = f | (nl << 11);
+                L.list[cur ^ 1u][at + 1] = (f + nl) | ((n - nl) << 11) | (1u << 22);
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) L.n_list[cur] = 0u;
+        __syncthreads();
+    }
+    for (uint32_t i = threadIdx.x; i < root.count; i += 64 * SAH_SMALL_WAVES) ids[base + i] = L.gid[L.ord[i]];
 }
 
 }  // namespace
@@ -1280,7 +1358,6 @@ hipError_t rc_build_bvh_device_sah(const float* d_pos, const uint32_t* d_idx, ui
         task_nchunks, par_a, par_b, overflow;
     DevBuf<SahTask> big_a, big_b, small;
     DevBuf<int4> decision;
-    DevBuf<uint4> stack;
     DevBuf<int> lvl_a, lvl_b, nint, offs;
     DevBuf<Node4> nodes;
     DevBuf<uint8_t> temp;
@@ -1304,7 +1381,6 @@ hipError_t rc_build_bvh_device_sah(const float* d_pos, const uint32_t* d_idx, ui
     BH(big_b.alloc(max_big));
     BH(small.alloc(n));
     BH(decision.alloc(max_big));
-    BH(stack.alloc(n));
     BH(nodes.alloc(cap));
     BH(lvl_a.alloc(cap));
     BH(lvl_b.alloc(cap));
@@ -1319,10 +1395,11 @@ hipError_t rc_build_bvh_device_sah(const float* d_pos, const uint32_t* d_idx, ui
 
     hipLaunchKernelGGL(k_tri_boxes, dim3(nb(n, 256)), dim3(256), 0, st, d_pos, d_idx, n, tri_box.p, cen.p);
     hipLaunchKernelGGL(k_iota, dim3(nb(n, 256)), dim3(256), 0, st, d_order, n);
-    // counters: [0] binary nodes allocated (the root is node 0), [1] large ranges of the next level, [2] small ranges
-    const uint32_t ctr0[4] = {1u, 0u, 0u, 0u};
+    // counters: [1] large ranges of the next level, [2] small ranges (binary nodes: the root is 0, the halves of the
+    // split at slot s are 2 s and 2 s + 1)
+    const uint32_t ctr0[4] = {0u, 0u, 0u, 0u};
     BH(hipMemcpyAsync(ctr.p, ctr0, sizeof(ctr0), hipMemcpyHostToDevice, st));
-    const SahTree T{child.p, range.p, box.p, ctr.p};
+    const SahTree T{child.p, range.p, box.p};
     std::vector<SahTask> big_h;
     if (n > SAH_SMALL) {
         big_h.push_back({0u, 0u, n, 0u});
@@ -1386,8 +1463,9 @@ hipError_t rc_build_bvh_device_sah(const float* d_pos, const uint32_t* d_idx, ui
     BH(hipStreamSynchronize(st));
     if (n_small > n) return hipErrorUnknown;
     if (n_small)
-        hipLaunchKernelGGL(k_sah_small, dim3(nb(n_small, 4)), dim3(256), 0, st, small.p, n_small, d_order, tmp.p,
-                           tri_box.p, cen.p, NB, max_leaf, (double)node_cost, T, stack.p);
+        hipLaunchKernelGGL(k_sah_small, dim3(n_small), dim3(64 * SAH_SMALL_WAVES),
+                           sizeof(SahSmallLds) + (size_t)SAH_SMALL_WAVES * 3 * NB * SAH_BIN_WORDS * 4, st, small.p, d_order,
+                           tri_box.p, cen.p, NB, max_leaf, (double)node_cost, T);
     BH(hipGetLastError());
 
     // 4-wide collapse from the root (binary node 0), level by level
