@@ -279,6 +279,7 @@ bool rc_build_bvh_host(const float* pos, const uint32_t* idx, uint32_t n_tris, u
     out.depth = depth;
     out.max_stack = 3 * depth + 1;
     out.n_leaves = leaves;
+    out.n_nodes = (uint32_t)out.nodes.size();
     out.sah_cost = rc_bvh_sah(out.nodes);
     return true;
 }

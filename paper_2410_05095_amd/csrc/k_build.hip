@@ -447,10 +447,12 @@ __global__ __launch_bounds__(256) void k_collapse_count(TreeView T, const int* l
 __global__ __launch_bounds__(256) void k_collapse_write(TreeView T, const int* level, const uint32_t* level_parent,
                                                         int m, const int* offs, uint32_t level_base, uint32_t next_base,
                                                         uint32_t depth, uint32_t cap, Node4* nodes,
-                                                        int* next_level, uint32_t* next_parent, uint32_t* overflow)
+                                                        int* next_level, uint32_t* next_parent, uint32_t* overflow,
+                                                        const int* n_internal, uint32_t* next_m)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= m) return;
+    if (k == m - 1) *next_m = (uint32_t)(offs[k] + n_internal[k]);   // nodes of the next level, in pinned memory
     int kids[4];
     const int b = level[k];
     const int cnt = gather_kids(T, b, kids);
@@ -608,11 +610,42 @@ __global__ void k_fill_i32(int* p, int v, uint32_t n)
 
 inline unsigned nb(size_t n, unsigned b) { return (unsigned)((n + b - 1) / b); }
 
+// Device buffers of one build, carved from one allocation (some forty separate ones and their frees took 6 of the
+// 14 ms of a build of 1M triangles), and a pinned word array that kernels write the next level's size to.
 template <class T>
 struct DevBuf {
     T* p = nullptr;
-    ~DevBuf() { if (p) (void)hipFree(p); }
-    hipError_t alloc(size_t n) { return hipMalloc(reinterpret_cast<void**>(&p), (n ? n : 1) * sizeof(T)); }
+};
+
+struct BuildArena {
+    static constexpr int STAT_BLOCKS = 256, HOST_WORDS = 4 * STAT_BLOCKS;
+    std::vector<std::pair<void**, size_t>> parts;   // where the pointer goes, offset
+    size_t bytes = 0;
+    uint8_t* base = nullptr;
+    uint32_t* host = nullptr;
+    BuildArena() = default;
+    BuildArena(const BuildArena&) = delete;
+    BuildArena& operator=(const BuildArena&) = delete;
+    ~BuildArena()
+    {
+        if (base) (void)hipFree(base);
+        if (host) (void)hipHostFree(host);
+    }
+    template <class T>
+    void add(DevBuf<T>& b, size_t n)
+    {
+        parts.emplace_back(reinterpret_cast<void**>(&b.p), bytes);
+        bytes += ((n ? n : 1) * sizeof(T) + 255) & ~size_t(255);
+    }
+    hipError_t commit()
+    {
+        hipError_t e = hipMalloc(reinterpret_cast<void**>(&base), bytes);
+        if (e != hipSuccess) { base = nullptr; return e; }
+        for (auto& q : parts) *q.first = base + q.second;
+        e = hipHostMalloc(reinterpret_cast<void**>(&host), HOST_WORDS * 4, hipHostMallocDefault);
+        if (e != hipSuccess) host = nullptr;
+        return e;
+    }
 };
 
 #define BH(call)                                  \
@@ -620,6 +653,85 @@ struct DevBuf {
         hipError_t e_ = (call);                   \
         if (e_ != hipSuccess) return e_;          \
     } while (0)
+
+// Leaf count and SAH terms of the finished nodes: each workgroup's share in a fixed order, into pinned memory (reading
+// the nodes back for the host to sum up took 3 ms of a build of 1M triangles).
+struct NodeStat {
+    double sah;
+    uint32_t leaves, pad;
+};
+
+__global__ __launch_bounds__(256) void k_node_stats(const Node4* nodes, uint32_t n, NodeStat* out)
+{
+    __shared__ double s_sah[256];
+    __shared__ uint32_t s_leaves[256];
+    auto area = [](float lx, float hx, float ly, float hy, float lz, float hz) {
+        const double dx = (double)hx - lx, dy = (double)hy - ly, dz = (double)hz - lz;
+        if (!(dx >= 0.0) || !(dy >= 0.0) || !(dz >= 0.0)) return 0.0;
+        return 2.0 * (dx * dy + dy * dz + dz * dx);
+    };
+    const Node4& r = nodes[0];
+    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (int c = 0; c < 4; ++c) {   // empty slots hold inverted infinite boxes
+        lo[0] = fminf(lo[0], r.lo_x[c]); hi[0] = fmaxf(hi[0], r.hi_x[c]);
+        lo[1] = fminf(lo[1], r.lo_y[c]); hi[1] = fmaxf(hi[1], r.hi_y[c]);
+        lo[2] = fminf(lo[2], r.lo_z[c]); hi[2] = fmaxf(hi[2], r.hi_z[c]);
+    }
+    const double ra = area(lo[0], hi[0], lo[1], hi[1], lo[2], hi[2]);
+    double sum = 0.0;
+    uint32_t leaves = 0;
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+        const Node4& nd = nodes[i];
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t w = nd.child[c];
+            if (w == RC_EMPTY_CHILD) continue;
+            const double a = ra > 0.0 ? area(nd.lo_x[c], nd.hi_x[c], nd.lo_y[c], nd.hi_y[c], nd.lo_z[c], nd.hi_z[c]) / ra : 0.0;
+            sum += rc_is_leaf(w) ? a * rc_leaf_count(w) : a;
+            leaves += rc_is_leaf(w) ? 1u : 0u;
+        }
+    }
+    s_sah[threadIdx.x] = sum;
+    s_leaves[threadIdx.x] = leaves;
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+        if ((int)threadIdx.x < h) {
+            s_sah[threadIdx.x] += s_sah[threadIdx.x + h];
+            s_leaves[threadIdx.x] += s_leaves[threadIdx.x + h];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[blockIdx.x] = NodeStat{s_sah[0], s_leaves[0], ra > 0.0 ? 1u : 0u};
+}
+
+// The finished nodes as an array of their own, with their statistics; synchronises the stream.
+hipError_t finish_nodes(BuildArena& A, const Node4* nodes, uint32_t total, Node4** d_nodes_out, uint32_t* n_nodes_out,
+                        BuildStats& stats, hipStream_t st)
+{
+    static_assert(sizeof(NodeStat) == 16 && BuildArena::HOST_WORDS * 4 >= BuildArena::STAT_BLOCKS * 16, "statistics words");
+    Node4* out = nullptr;
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(&out), (size_t)total * sizeof(Node4));
+    if (e != hipSuccess) return e;
+    e = hipMemcpyAsync(out, nodes, (size_t)total * sizeof(Node4), hipMemcpyDeviceToDevice, st);
+    NodeStat* h = reinterpret_cast<NodeStat*>(A.host);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_node_stats, dim3(BuildArena::STAT_BLOCKS), dim3(256), 0, st, nodes, total, h);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) {
+        (void)hipFree(out);
+        return e;
+    }
+    stats = BuildStats();
+    stats.sah_cost = h[0].pad ? 1.0 : 0.0;   // the root itself
+    for (int b = 0; b < BuildArena::STAT_BLOCKS; ++b) {
+        stats.sah_cost += h[b].sah;
+        stats.n_leaves += h[b].leaves;
+    }
+    *d_nodes_out = out;
+    *n_nodes_out = total;
+    return hipSuccess;
+}
 
 }  // namespace
 
@@ -633,7 +745,7 @@ struct DevBuf {
 hipError_t rc_build_bvh_device(const float* d_pos, const uint32_t* d_idx, uint32_t n, uint32_t max_leaf,
                                const uint32_t* d_seg, const std::vector<uint32_t>& seg_first,
                                const std::vector<uint32_t>& seg_count, Node4** d_nodes_out, uint32_t* n_nodes_out,
-                               uint32_t* d_order, std::vector<uint32_t>& level_start, hipStream_t st)
+                               uint32_t* d_order, std::vector<uint32_t>& level_start, BuildStats& stats, hipStream_t st)
 {
     *d_nodes_out = nullptr;
     *n_nodes_out = 0;
@@ -648,6 +760,7 @@ hipError_t rc_build_bvh_device(const float* d_pos, const uint32_t* d_idx, uint32
     // there are at most (n - 1 + n / 2) / 2 < 3n / 4 of them, plus one root per segment.
     const size_t cap = 3 * (size_t)n / 4 + n_seg + 2;
     const int red_blocks = 1024;
+    BuildArena A;
     DevBuf<Box6> tri_box, box;
     DevBuf<float4> cen;
     DevBuf<float> partial, bounds;
@@ -658,42 +771,43 @@ hipError_t rc_build_bvh_device(const float* d_pos, const uint32_t* d_idx, uint32
     DevBuf<int> parent, lvl_a, lvl_b, nint, offs;
     DevBuf<Node4> nodes;
     DevBuf<uint8_t> temp;
-    BH(tri_box.alloc(n));
-    BH(cen.alloc(n));
-    BH(partial.alloc((size_t)red_blocks * 6));
-    BH(bounds.alloc(6));
-    BH(keys.alloc(n));
-    BH(keys_s.alloc(n));
-    BH(vals.alloc(n));
-    BH(box.alloc(2 * (size_t)n));
-    BH(child.alloc(n));
-    BH(range.alloc(n));
-    BH(parent.alloc(2 * (size_t)n));
-    BH(flags.alloc(n));
-    BH(nodes.alloc(cap));
-    BH(lvl_a.alloc(cap));
-    BH(lvl_b.alloc(cap));
-    BH(par_a.alloc(cap));
-    BH(par_b.alloc(cap));
-    BH(nint.alloc(cap));
-    BH(offs.alloc(cap));
-    BH(overflow.alloc(1));
+    A.add(tri_box, n);
+    A.add(cen, n);
+    A.add(partial, (size_t)red_blocks * 6);
+    A.add(bounds, 6);
+    A.add(keys, n);
+    A.add(keys_s, n);
+    A.add(vals, n);
+    A.add(box, 2 * (size_t)n);
+    A.add(child, n);
+    A.add(range, n);
+    A.add(parent, 2 * (size_t)n);
+    A.add(flags, n);
+    A.add(nodes, cap);
+    A.add(lvl_a, cap);
+    A.add(lvl_b, cap);
+    A.add(par_a, cap);
+    A.add(par_b, cap);
+    A.add(nint, cap);
+    A.add(offs, cap);
+    A.add(overflow, 1);
     if (segmented) {
-        BH(keys_m.alloc(n));
-        BH(order_m.alloc(n));
-        BH(seg_g.alloc(n));
-        BH(seg_s.alloc(n));
-        BH(pos.alloc(n));
-        BH(perm.alloc(n));
-        BH(seg_first_d.alloc(n_seg));
-        BH(seg_count_d.alloc(n_seg));
+        A.add(keys_m, n);
+        A.add(order_m, n);
+        A.add(seg_g, n);
+        A.add(seg_s, n);
+        A.add(pos, n);
+        A.add(perm, n);
+        A.add(seg_first_d, n_seg);
+        A.add(seg_count_d, n_seg);
     }
     size_t sort_bytes = 0, seg_sort_bytes = 0, scan_bytes = 0;
     BH(rocprim::radix_sort_pairs(nullptr, sort_bytes, keys.p, keys_s.p, vals.p, d_order, n, 0, 63, st));
     if (segmented)
         BH(rocprim::radix_sort_pairs(nullptr, seg_sort_bytes, seg_g.p, seg_s.p, pos.p, perm.p, n, 0, 32, st));
     BH(rocprim::exclusive_scan(nullptr, scan_bytes, nint.p, offs.p, 0, cap, rocprim::plus<int>(), st));
-    BH(temp.alloc(std::max(std::max(sort_bytes, seg_sort_bytes), scan_bytes)));
+    A.add(temp, std::max(std::max(sort_bytes, seg_sort_bytes), scan_bytes));
+    BH(A.commit());
 
     hipLaunchKernelGGL(k_tri_boxes, dim3(nb(n, 256)), dim3(256), 0, st, d_pos, d_idx, n, tri_box.p, cen.p);
     hipLaunchKernelGGL(k_cen_bounds, dim3(red_blocks), dim3(256), 0, st, cen.p, n, partial.p);
@@ -739,35 +853,23 @@ hipError_t rc_build_bvh_device(const float* d_pos, const uint32_t* d_idx, uint32
         size_t sb = scan_bytes;
         BH(rocprim::exclusive_scan(temp.p, sb, nint.p, offs.p, 0, (size_t)m, rocprim::plus<int>(), st));
         hipLaunchKernelGGL(k_collapse_write, dim3(nb(m, 256)), dim3(256), 0, st, T, lvl_a.p, par_a.p, (int)m, offs.p,
-                           base, base + m, depth, (uint32_t)cap, nodes.p, lvl_b.p, par_b.p, overflow.p);
+                           base, base + m, depth, (uint32_t)cap, nodes.p, lvl_b.p, par_b.p, overflow.p, nint.p,
+                           A.host);
         BH(hipGetLastError());
-        int tail[2] = {0, 0};
-        uint32_t ovf = 0;
-        BH(hipMemcpyAsync(&tail[0], offs.p + (m - 1), sizeof(int), hipMemcpyDeviceToHost, st));
-        BH(hipMemcpyAsync(&tail[1], nint.p + (m - 1), sizeof(int), hipMemcpyDeviceToHost, st));
-        BH(hipMemcpyAsync(&ovf, overflow.p, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
         BH(hipStreamSynchronize(st));
-        if (ovf) return hipErrorUnknown;
         level_start.push_back(base);
         base += m;
         ++depth;
-        m = (uint32_t)(tail[0] + tail[1]);
+        m = A.host[0];
         std::swap(lvl_a.p, lvl_b.p);
         std::swap(par_a.p, par_b.p);
     }
     level_start.push_back(base);
+    BH(hipMemcpyAsync(A.host, overflow.p, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    BH(hipStreamSynchronize(st));
+    if (A.host[0]) return hipErrorUnknown;
     const uint32_t total = level_start.back();
-    Node4* out = nullptr;
-    BH(hipMalloc(reinterpret_cast<void**>(&out), (size_t)total * sizeof(Node4)));
-    hipError_t e = hipMemcpyAsync(out, nodes.p, (size_t)total * sizeof(Node4), hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) {
-        (void)hipFree(out);
-        return e;
-    }
-    *d_nodes_out = out;
-    *n_nodes_out = total;
-    return hipSuccess;
+    return finish_nodes(A, nodes.p, total, d_nodes_out, n_nodes_out, stats, st);
 }
 
 // ---------------------------------------------------------------- binned SAH on the GPU --------
@@ -811,7 +913,7 @@ __device__ inline int sah_bin(float c, float lo, double scale, int NB)
 }
 
 struct SahTask {
-    uint32_t node, first, count, pad;
+    uint32_t node, first, count, buf;   // buf: which of the two id arrays holds the range
 };
 
 struct SahTree {
@@ -902,23 +1004,75 @@ __device__ inline void write_sah_node(const SahTree& T, uint32_t node, const flo
     T.range[node] = make_int2((int)first, (int)count);
 }
 
+// the first level: all triangles as one large range, or as one small one
+__global__ void k_sah_start(uint32_t n, SahTask* big, SahTask* small, uint32_t* ctr)
+{
+    if (threadIdx.x != 0) return;
+    const SahTask root = {0u, 0u, n, 0u};
+    (n > SAH_SMALL ? big : small)[0] = root;
+    ctr[0] = ctr[1] = 0u;
+    ctr[2] = n > SAH_SMALL ? 0u : 1u;
+}
+
 // ---- large ranges, level by level (chunk c of the level: elements chunk_begin[c] .. chunk_end[c] - 1 of task
 // chunk_task[c]) ----
-__global__ __launch_bounds__(256) void k_sah_reset(uint32_t* acc, uint32_t* bins, uint32_t n_tasks, int NB)
+// Level set-up without the host: k_sah_plan (one workgroup) sums up the chunk counts of the level's ranges,
+// k_sah_chunks lists every chunk's range and extent and clears the ranges' bins.  ctl[0]: chunks of the level; the
+// chunk kernels are launched for the largest possible number and leave early.
+constexpr int SAH_PLAN_THREADS = 1024;
+__global__ __launch_bounds__(SAH_PLAN_THREADS) void k_sah_plan(const SahTask* tasks, uint32_t nt, uint32_t* task_chunk0,
+                                                               uint32_t* ctl, uint32_t* next_n)
 {
-    const size_t per_task = 12 + (size_t)3 * NB * SAH_BIN_WORDS;
-    const size_t total = per_task * n_tasks;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-        const size_t t = i / per_task, w = i % per_task;
-        uint32_t v;
-        if (w < 12) {
-            v = (w % 6) < 3 ? O_POS_INF : O_NEG_INF;   // box lo, box hi, centroid lo, centroid hi
-            acc[t * 12 + w] = v;
-        } else {
-            const size_t q = w - 12, word = q % SAH_BIN_WORDS;
-            v = word < 3 ? O_POS_INF : (word < 6 ? O_NEG_INF : 0u);
-            bins[t * (per_task - 12) + q] = v;
+    __shared__ uint32_t wave_sum[SAH_PLAN_THREADS / 64];
+    const uint32_t lane = __lane_id(), wave = threadIdx.x >> 6;
+    uint32_t carry = 0;
+    for (uint32_t t0 = 0; t0 < nt; t0 += SAH_PLAN_THREADS) {
+        const uint32_t t = t0 + threadIdx.x;
+        const uint32_t mine = t < nt ? (tasks[t].count + SAH_CHUNK - 1) / SAH_CHUNK : 0u;
+        uint32_t x = mine;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = __shfl_up(x, off);
+            if ((int)lane >= off) x += o;
         }
+        if (lane == 63) wave_sum[wave] = x;
+        __syncthreads();
+        uint32_t before = 0, total = 0;
+        for (uint32_t w = 0; w < SAH_PLAN_THREADS / 64; ++w) {
+            if (w < wave) before += wave_sum[w];
+            total += wave_sum[w];
+        }
+        if (t < nt) task_chunk0[t] = carry + before + x - mine;
+        carry += total;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        task_chunk0[nt] = carry;
+        ctl[0] = carry;
+        *next_n = 0u;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_sah_chunks(const SahTask* tasks, uint32_t nt, const uint32_t* task_chunk0,
+                                                    uint32_t* chunk_task, uint32_t* chunk_begin, uint32_t* chunk_end,
+                                                    uint32_t* bins, int NB)
+{
+    const uint32_t nc = task_chunk0[nt];
+    for (uint32_t c = blockIdx.x * 256 + threadIdx.x; c < nc; c += gridDim.x * 256) {
+        uint32_t lo = 0, hi = nt;   // the last range whose first chunk is not beyond c
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (task_chunk0[mid] <= c) lo = mid; else hi = mid;
+        }
+        const SahTask t = tasks[lo];
+        const uint32_t begin = t.first + (c - task_chunk0[lo]) * SAH_CHUNK;
+        chunk_task[c] = lo;
+        chunk_begin[c] = begin;
+        chunk_end[c] = min(begin + SAH_CHUNK, t.first + t.count);
+    }
+    const size_t words = (size_t)3 * NB * SAH_BIN_WORDS * nt;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (size_t)gridDim.x * 256) {
+        const uint32_t w = (uint32_t)(i % SAH_BIN_WORDS);
+        bins[i] = w < 3 ? O_POS_INF : (w < 6 ? O_NEG_INF : 0u);
     }
 }
 
@@ -939,11 +1093,12 @@ __device__ inline void block_reduce_minmax(float v[12], float* sm /* [12][4] */)
 }
 
 __global__ __launch_bounds__(256) void k_sah_bounds(const uint32_t* ids, const Box6* tri_box, const float4* cen,
-                                                    const uint32_t* chunk_task, const uint32_t* chunk_begin,
-                                                    const uint32_t* chunk_end, uint32_t* acc)
+                                                    const uint32_t* chunk_begin, const uint32_t* chunk_end,
+                                                    const uint32_t* ctl, float* partial)
 {
     __shared__ float sm[48];
     const uint32_t c = blockIdx.x;
+    if (c >= ctl[0]) return;
     float v[12];
     for (int k = 0; k < 12; ++k) v[k] = (k % 6) < 3 ? INFINITY : -INFINITY;
     for (uint32_t i = chunk_begin[c] + threadIdx.x; i < chunk_end[c]; i += 256) {
@@ -957,22 +1112,39 @@ __global__ __launch_bounds__(256) void k_sah_bounds(const uint32_t* ids, const B
         }
     }
     block_reduce_minmax(v, sm);
-    if (threadIdx.x == 0) {
-        uint32_t* a = acc + 12 * (size_t)chunk_task[c];
+    if (threadIdx.x == 0)
+        for (int k = 0; k < 12; ++k) partial[12 * (size_t)c + k] = v[k];
+}
+
+// the bounds of each range from its chunks', one wave per range (as ordered words)
+__global__ __launch_bounds__(64) void k_sah_bounds_final(const uint32_t* task_chunk0, const float* partial, uint32_t* acc)
+{
+    const uint32_t t = blockIdx.x;
+    float v[12];
+    for (int k = 0; k < 12; ++k) v[k] = (k % 6) < 3 ? INFINITY : -INFINITY;
+    for (uint32_t c = task_chunk0[t] + __lane_id(); c < task_chunk0[t + 1]; c += 64)
         for (int k = 0; k < 12; ++k) {
-            if ((k % 6) < 3) atomicMin(a + k, f2o(v[k]));
-            else atomicMax(a + k, f2o(v[k]));
+            const float o = partial[12 * (size_t)c + k];
+            v[k] = (k % 6) < 3 ? fminf(v[k], o) : fmaxf(v[k], o);
         }
-    }
+    for (int off = 32; off > 0; off >>= 1)
+        for (int k = 0; k < 12; ++k) {
+            const float o = __shfl_xor(v[k], off);
+            v[k] = (k % 6) < 3 ? fminf(v[k], o) : fmaxf(v[k], o);
+        }
+    if (__lane_id() == 0)
+        for (int k = 0; k < 12; ++k) acc[12 * (size_t)t + k] = f2o(v[k]);
 }
 
 __global__ __launch_bounds__(256) void k_sah_bins(const uint32_t* ids, const Box6* tri_box, const float4* cen,
                                                   const uint32_t* chunk_task, const uint32_t* chunk_begin,
-                                                  const uint32_t* chunk_end, const uint32_t* acc, uint32_t* bins,
-                                                  int NB)
+                                                  const uint32_t* chunk_end, const uint32_t* ctl, const uint32_t* acc,
+                                                  uint32_t* bins, int NB)
 {
     __shared__ uint32_t lb[3 * SAH_NB_MAX * SAH_BIN_WORDS];
-    const uint32_t c = blockIdx.x, task = chunk_task[c];
+    const uint32_t c = blockIdx.x;
+    if (c >= ctl[0]) return;
+    const uint32_t task = chunk_task[c];
     const int words = 3 * NB * SAH_BIN_WORDS;
     for (int i = threadIdx.x; i < words; i += 256) {
         const int w = i % SAH_BIN_WORDS;
@@ -982,7 +1154,12 @@ __global__ __launch_bounds__(256) void k_sah_bins(const uint32_t* ids, const Box
     float clo[3], chi[3];
     for (int k = 0; k < 3; ++k) { clo[k] = o2f(a[6 + k]); chi[k] = o2f(a[9 + k]); }
     __syncthreads();
-    for (uint32_t i = chunk_begin[c] + threadIdx.x; i < chunk_end[c]; i += 256) {
+    // a thread takes consecutive triangles, so that the lanes of a wave are a few triangles apart: neighbours of a
+    // mesh fall into one bin, and atomics of one instruction on one word run one after the other
+    constexpr uint32_t PER = SAH_CHUNK / 256;
+    for (uint32_t j = 0; j < PER; ++j) {
+        const uint32_t i = chunk_begin[c] + threadIdx.x * PER + j;
+        if (i >= chunk_end[c]) break;
         const uint32_t t = ids[i];
         const Box6 b = tri_box[t];
         const float4 q = cen[t];
@@ -1012,7 +1189,7 @@ __global__ __launch_bounds__(256) void k_sah_bins(const uint32_t* ids, const Box
 // left count).
 __global__ __launch_bounds__(64) void k_sah_split(const SahTask* tasks, const uint32_t* acc, const uint32_t* bins,
                                                   int NB, SahTree T, SahTask* big_next, uint32_t* big_next_n,
-                                                  SahTask* small, uint32_t* small_n, int4* decision)
+                                                  SahTask* small, uint32_t* small_n, int4* decision, uint32_t dst_buf)
 {
     const uint32_t t = blockIdx.x;
     const SahTask task = tasks[t];
@@ -1029,7 +1206,7 @@ __global__ __launch_bounds__(64) void k_sah_split(const SahTask* tasks, const ui
     if (__lane_id() == 0) {
         const uint32_t l = 2u * (task.first + nl), r = l + 1;   // every slot is split at once: numbers are unique
         write_sah_node(T, task.node, blo, bhi, (int)l, (int)r, task.first, task.count);
-        const SahTask kids[2] = {{l, task.first, nl, 0u}, {r, task.first + nl, task.count - nl, 0u}};
+        const SahTask kids[2] = {{l, task.first, nl, dst_buf}, {r, task.first + nl, task.count - nl, dst_buf}};
         for (int s = 0; s < 2; ++s) {
             if (kids[s].count > SAH_SMALL) big_next[atomicAdd(big_next_n, 1u)] = kids[s];
             else small[atomicAdd(small_n, 1u)] = kids[s];
@@ -1050,11 +1227,13 @@ __device__ inline bool sah_goes_left(const float4* cen, uint32_t tri, int axis, 
 __global__ __launch_bounds__(256) void k_sah_count(const uint32_t* ids, const float4* cen, const SahTask* tasks,
                                                    const uint32_t* chunk_task,
                                                    const uint32_t* chunk_begin, const uint32_t* chunk_end,
-                                                   const uint32_t* acc, const int4* decision, int NB,
+                                                   const uint32_t* ctl, const uint32_t* acc, const int4* decision, int NB,
                                                    uint32_t* chunk_left)
 {
     __shared__ uint32_t s;
-    const uint32_t c = blockIdx.x, task = chunk_task[c];
+    const uint32_t c = blockIdx.x;
+    if (c >= ctl[0]) return;
+    const uint32_t task = chunk_task[c];
     const int4 d = decision[task];
     if (threadIdx.x == 0) s = 0;
     __syncthreads();
@@ -1069,27 +1248,37 @@ __global__ __launch_bounds__(256) void k_sah_count(const uint32_t* ids, const fl
     if (threadIdx.x == 0) chunk_left[c] = s;
 }
 
-// one thread per large range: exclusive offsets of its chunks' left counts (its chunks are consecutive)
-__global__ __launch_bounds__(256) void k_sah_offsets(const uint32_t* task_chunk0, const uint32_t* task_nchunks,
-                                                     uint32_t n_tasks, const uint32_t* chunk_left, uint32_t* chunk_off)
+// one wave per large range: exclusive offsets of its chunks' left counts (its chunks are consecutive)
+__global__ __launch_bounds__(64) void k_sah_offsets(const uint32_t* task_chunk0, const uint32_t* chunk_left,
+                                                    uint32_t* chunk_off)
 {
-    const uint32_t t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= n_tasks) return;
-    uint32_t acc = 0;
-    for (uint32_t c = task_chunk0[t]; c < task_chunk0[t] + task_nchunks[t]; ++c) {
-        chunk_off[c] = acc;
-        acc += chunk_left[c];
+    const uint32_t t = blockIdx.x, lane = __lane_id(), end = task_chunk0[t + 1];
+    uint32_t carry = 0;
+    for (uint32_t c0 = task_chunk0[t]; c0 < end; c0 += 64) {
+        const uint32_t c = c0 + lane;
+        const uint32_t mine = c < end ? chunk_left[c] : 0u;
+        uint32_t x = mine;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = __shfl_up(x, off);
+            if ((int)lane >= off) x += o;
+        }
+        if (c < end) chunk_off[c] = carry + x - mine;
+        carry += __shfl(x, 63);
     }
 }
 
 __global__ __launch_bounds__(256) void k_sah_scatter(const uint32_t* ids, const float4* cen, const SahTask* tasks,
                                                      const uint32_t* chunk_task, const uint32_t* chunk_begin,
-                                                     const uint32_t* chunk_end, const uint32_t* acc,
-                                                     const int4* decision, int NB, const uint32_t* chunk_off,
-                                                     uint32_t* ids_out)
+                                                     const uint32_t* chunk_end, const uint32_t* ctl,
+                                                     const uint32_t* acc, const int4* decision, int NB,
+                                                     const uint32_t* chunk_off, uint32_t* ids_out,
+                                                     const uint32_t* next_n, uint32_t* next_host)
 {
     __shared__ uint32_t s_wave[4];
-    const uint32_t c = blockIdx.x, task = chunk_task[c];
+    const uint32_t c = blockIdx.x;
+    if (c == 0 && threadIdx.x == 0) *next_host = *next_n;   // large ranges of the next level, in pinned memory
+    if (c >= ctl[0]) return;
+    const uint32_t task = chunk_task[c];
     const int4 d = decision[task];
     const SahTask tk = tasks[task];
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1122,13 +1311,6 @@ __global__ __launch_bounds__(256) void k_sah_scatter(const uint32_t* ids, const 
     }
 }
 
-__global__ __launch_bounds__(256) void k_sah_copy(const uint32_t* src, const uint32_t* chunk_begin,
-                                                  const uint32_t* chunk_end, uint32_t* dst)
-{
-    const uint32_t c = blockIdx.x;
-    for (uint32_t i = chunk_begin[c] + threadIdx.x; i < chunk_end[c]; i += 256) dst[i] = src[i];
-}
-
 // ---- small ranges: one workgroup builds the whole subtree of a range of at most SAH_SMALL triangles ----
 // Boxes, centroids and the order of the range's triangles stay in LDS; the subtree grows level by level, its waves
 // taking the level's ranges in turn.  Ranges of up to SAH_TINY triangles (nineteen in twenty) are split without
@@ -1157,7 +1339,8 @@ __device__ inline void sah_wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__global__ __launch_bounds__(64 * SAH_SMALL_WAVES) void k_sah_small(const SahTask* small, uint32_t* ids,
+__global__ __launch_bounds__(64 * SAH_SMALL_WAVES) void k_sah_small(const SahTask* small, const uint32_t* ids0,
+                                                                    const uint32_t* ids1, uint32_t* order,
                                                                     const Box6* tri_box, const float4* cen, int NB,
                                                                     uint32_t max_leaf, double node_cost, SahTree T)
 {
@@ -1168,6 +1351,7 @@ __global__ __launch_bounds__(64 * SAH_SMALL_WAVES) void k_sah_small(const SahTas
     uint32_t* lb = sah_lds + sizeof(SahSmallLds) / 4 + wave * words;
     const SahTask root = small[blockIdx.x];
     const uint32_t base = root.first;
+    const uint32_t* ids = root.buf ? ids1 : ids0;
     for (uint32_t i = threadIdx.x; i < root.count; i += 64 * SAH_SMALL_WAVES) {
         const uint32_t t = ids[base + i];
         const Box6 b = tri_box[t];
@@ -1331,7 +1515,7 @@ __global__ __launch_bounds__(64 * SAH_SMALL_WAVES) void k_sah_small(const SahTas
         if (threadIdx.x == 0) L.n_list[cur] = 0u;
         __syncthreads();
     }
-    for (uint32_t i = threadIdx.x; i < root.count; i += 64 * SAH_SMALL_WAVES) ids[base + i] = L.gid[L.ord[i]];
+    for (uint32_t i = threadIdx.x; i < root.count; i += 64 * SAH_SMALL_WAVES) order[base + i] = L.gid[L.ord[i]];
 }
 
 }  // namespace
@@ -1339,7 +1523,7 @@ __global__ __launch_bounds__(64 * SAH_SMALL_WAVES) void k_sah_small(const SahTas
 // Binned-SAH build of n triangles on the device (see above); outputs as rc_build_bvh_device.
 hipError_t rc_build_bvh_device_sah(const float* d_pos, const uint32_t* d_idx, uint32_t n, uint32_t bins,
                                    uint32_t max_leaf, float node_cost, Node4** d_nodes_out, uint32_t* n_nodes_out,
-                                   uint32_t* d_order, std::vector<uint32_t>& level_start, hipStream_t st)
+                                   uint32_t* d_order, std::vector<uint32_t>& level_start, BuildStats& stats, hipStream_t st)
 {
     *d_nodes_out = nullptr;
     *n_nodes_out = 0;
@@ -1351,121 +1535,93 @@ hipError_t rc_build_bvh_device_sah(const float* d_pos, const uint32_t* d_idx, ui
     const uint32_t max_big = n / SAH_SMALL + 2;      // large ranges of one level are disjoint
     const uint32_t max_chunks = n / SAH_CHUNK + max_big + 2;
     const size_t cap = (size_t)n + 2;                 // 4-wide nodes: at most one per internal binary node, plus root
+    BuildArena A;
     DevBuf<Box6> tri_box, box;
     DevBuf<float4> cen;
     DevBuf<int2> child, range;
     DevBuf<uint32_t> tmp, ctr, acc, binbuf, chunk_task, chunk_begin, chunk_end, chunk_left, chunk_off, task_chunk0,
-        task_nchunks, par_a, par_b, overflow;
+        par_a, par_b, overflow;
+    DevBuf<float> partial;
     DevBuf<SahTask> big_a, big_b, small;
     DevBuf<int4> decision;
     DevBuf<int> lvl_a, lvl_b, nint, offs;
     DevBuf<Node4> nodes;
     DevBuf<uint8_t> temp;
-    BH(tri_box.alloc(n));
-    BH(cen.alloc(n));
-    BH(box.alloc(n2));
-    BH(child.alloc(n2));
-    BH(range.alloc(n2));
-    BH(tmp.alloc(n));
-    BH(ctr.alloc(4));
-    BH(acc.alloc((size_t)max_big * 12));
-    BH(binbuf.alloc((size_t)max_big * 3 * NB * SAH_BIN_WORDS));
-    BH(chunk_task.alloc(max_chunks));
-    BH(chunk_begin.alloc(max_chunks));
-    BH(chunk_end.alloc(max_chunks));
-    BH(chunk_left.alloc(max_chunks));
-    BH(chunk_off.alloc(max_chunks));
-    BH(task_chunk0.alloc(max_big));
-    BH(task_nchunks.alloc(max_big));
-    BH(big_a.alloc(max_big));
-    BH(big_b.alloc(max_big));
-    BH(small.alloc(n));
-    BH(decision.alloc(max_big));
-    BH(nodes.alloc(cap));
-    BH(lvl_a.alloc(cap));
-    BH(lvl_b.alloc(cap));
-    BH(par_a.alloc(cap));
-    BH(par_b.alloc(cap));
-    BH(nint.alloc(cap));
-    BH(offs.alloc(cap));
-    BH(overflow.alloc(1));
+    A.add(tri_box, n);
+    A.add(cen, n);
+    A.add(box, n2);
+    A.add(child, n2);
+    A.add(range, n2);
+    A.add(tmp, n);
+    A.add(ctr, 4);
+    A.add(acc, (size_t)max_big * 12);
+    A.add(binbuf, (size_t)max_big * 3 * NB * SAH_BIN_WORDS);
+    A.add(chunk_task, max_chunks);
+    A.add(chunk_begin, max_chunks);
+    A.add(chunk_end, max_chunks);
+    A.add(chunk_left, max_chunks);
+    A.add(chunk_off, max_chunks);
+    A.add(task_chunk0, max_big + 1);
+    A.add(partial, 12 * (size_t)max_chunks);
+    A.add(big_a, max_big);
+    A.add(big_b, max_big);
+    A.add(small, n);
+    A.add(decision, max_big);
+    A.add(nodes, cap);
+    A.add(lvl_a, cap);
+    A.add(lvl_b, cap);
+    A.add(par_a, cap);
+    A.add(par_b, cap);
+    A.add(nint, cap);
+    A.add(offs, cap);
+    A.add(overflow, 1);
     size_t scan_bytes = 0;
     BH(rocprim::exclusive_scan(nullptr, scan_bytes, nint.p, offs.p, 0, cap, rocprim::plus<int>(), st));
-    BH(temp.alloc(scan_bytes));
+    A.add(temp, scan_bytes);
+    BH(A.commit());
 
     hipLaunchKernelGGL(k_tri_boxes, dim3(nb(n, 256)), dim3(256), 0, st, d_pos, d_idx, n, tri_box.p, cen.p);
     hipLaunchKernelGGL(k_iota, dim3(nb(n, 256)), dim3(256), 0, st, d_order, n);
-    // counters: [1] large ranges of the next level, [2] small ranges (binary nodes: the root is 0, the halves of the
-    // split at slot s are 2 s and 2 s + 1)
-    const uint32_t ctr0[4] = {0u, 0u, 0u, 0u};
-    BH(hipMemcpyAsync(ctr.p, ctr0, sizeof(ctr0), hipMemcpyHostToDevice, st));
+    // counters: [0] chunks of the level, [1] large ranges of the next level, [2] small ranges (binary nodes: the root is
+    // 0, the halves of the split at slot s are 2 s and 2 s + 1)
     const SahTree T{child.p, range.p, box.p};
-    std::vector<SahTask> big_h;
-    if (n > SAH_SMALL) {
-        big_h.push_back({0u, 0u, n, 0u});
-    } else {
-        const SahTask root{0u, 0u, n, 0u};
-        BH(hipMemcpyAsync(small.p, &root, sizeof(root), hipMemcpyHostToDevice, st));
-        const uint32_t one = 1u;
-        BH(hipMemcpyAsync(ctr.p + 2, &one, sizeof(one), hipMemcpyHostToDevice, st));
-    }
-    if (!big_h.empty()) BH(hipMemcpyAsync(big_a.p, big_h.data(), sizeof(SahTask), hipMemcpyHostToDevice, st));
-    std::vector<uint32_t> ct, cb, ce, t0, tn;
-    while (!big_h.empty()) {
-        const uint32_t nt = (uint32_t)big_h.size();
-        ct.clear(); cb.clear(); ce.clear(); t0.clear(); tn.clear();
-        for (uint32_t t = 0; t < nt; ++t) {
-            t0.push_back((uint32_t)ct.size());
-            for (uint32_t b = big_h[t].first; b < big_h[t].first + big_h[t].count; b += SAH_CHUNK) {
-                ct.push_back(t);
-                cb.push_back(b);
-                ce.push_back(std::min(b + SAH_CHUNK, big_h[t].first + big_h[t].count));
-            }
-            tn.push_back((uint32_t)ct.size() - t0.back());
-        }
-        const uint32_t nc = (uint32_t)ct.size();
+    hipLaunchKernelGGL(k_sah_start, dim3(1), dim3(64), 0, st, n, big_a.p, small.p, ctr.p);
+    uint32_t* ids[2] = {d_order, tmp.p};   // a level's partition goes from one to the other
+    uint32_t nt = n > SAH_SMALL ? 1u : 0u, src = 0;
+    while (nt > 0) {
+        const uint32_t nc = n / SAH_CHUNK + nt;   // at least the level's chunks: its ranges are disjoint
         if (nc > max_chunks || nt > max_big) return hipErrorUnknown;
-        BH(hipMemcpyAsync(chunk_task.p, ct.data(), nc * 4, hipMemcpyHostToDevice, st));
-        BH(hipMemcpyAsync(chunk_begin.p, cb.data(), nc * 4, hipMemcpyHostToDevice, st));
-        BH(hipMemcpyAsync(chunk_end.p, ce.data(), nc * 4, hipMemcpyHostToDevice, st));
-        BH(hipMemcpyAsync(task_chunk0.p, t0.data(), nt * 4, hipMemcpyHostToDevice, st));
-        BH(hipMemcpyAsync(task_nchunks.p, tn.data(), nt * 4, hipMemcpyHostToDevice, st));
-        const uint32_t zero = 0u;
-        BH(hipMemcpyAsync(ctr.p + 1, &zero, sizeof(zero), hipMemcpyHostToDevice, st));
-        hipLaunchKernelGGL(k_sah_reset, dim3(std::min<unsigned>(1024, nb((size_t)nt * (12 + 3 * NB * SAH_BIN_WORDS), 256))),
-                           dim3(256), 0, st, acc.p, binbuf.p, nt, NB);
-        hipLaunchKernelGGL(k_sah_bounds, dim3(nc), dim3(256), 0, st, d_order, tri_box.p, cen.p, chunk_task.p,
-                           chunk_begin.p, chunk_end.p, acc.p);
-        hipLaunchKernelGGL(k_sah_bins, dim3(nc), dim3(256), 0, st, d_order, tri_box.p, cen.p, chunk_task.p,
-                           chunk_begin.p, chunk_end.p, acc.p, binbuf.p, NB);
+        hipLaunchKernelGGL(k_sah_plan, dim3(1), dim3(SAH_PLAN_THREADS), 0, st, big_a.p, nt, task_chunk0.p, ctr.p, ctr.p + 1);
+        hipLaunchKernelGGL(k_sah_chunks, dim3(std::min<unsigned>(1024, nb((size_t)nt * 3 * NB * SAH_BIN_WORDS + nc, 256))),
+                           dim3(256), 0, st, big_a.p, nt, task_chunk0.p, chunk_task.p, chunk_begin.p, chunk_end.p,
+                           binbuf.p, NB);
+        hipLaunchKernelGGL(k_sah_bounds, dim3(nc), dim3(256), 0, st, ids[src], tri_box.p, cen.p, chunk_begin.p,
+                           chunk_end.p, ctr.p, partial.p);
+        hipLaunchKernelGGL(k_sah_bounds_final, dim3(nt), dim3(64), 0, st, task_chunk0.p, partial.p, acc.p);
+        hipLaunchKernelGGL(k_sah_bins, dim3(nc), dim3(256), 0, st, ids[src], tri_box.p, cen.p, chunk_task.p,
+                           chunk_begin.p, chunk_end.p, ctr.p, acc.p, binbuf.p, NB);
         hipLaunchKernelGGL(k_sah_split, dim3(nt), dim3(64), 0, st, big_a.p, acc.p, binbuf.p, NB, T, big_b.p, ctr.p + 1,
-                           small.p, ctr.p + 2, decision.p);
-        hipLaunchKernelGGL(k_sah_count, dim3(nc), dim3(256), 0, st, d_order, cen.p, big_a.p, chunk_task.p,
-                           chunk_begin.p, chunk_end.p, acc.p, decision.p, NB, chunk_left.p);
-        hipLaunchKernelGGL(k_sah_offsets, dim3(nb(nt, 256)), dim3(256), 0, st, task_chunk0.p, task_nchunks.p, nt,
-                           chunk_left.p, chunk_off.p);
-        hipLaunchKernelGGL(k_sah_scatter, dim3(nc), dim3(256), 0, st, d_order, cen.p, big_a.p, chunk_task.p,
-                           chunk_begin.p, chunk_end.p, acc.p, decision.p, NB, chunk_off.p, tmp.p);
-        hipLaunchKernelGGL(k_sah_copy, dim3(nc), dim3(256), 0, st, tmp.p, chunk_begin.p, chunk_end.p, d_order);
+                           small.p, ctr.p + 2, decision.p, src ^ 1u);
+        hipLaunchKernelGGL(k_sah_count, dim3(nc), dim3(256), 0, st, ids[src], cen.p, big_a.p, chunk_task.p,
+                           chunk_begin.p, chunk_end.p, ctr.p, acc.p, decision.p, NB, chunk_left.p);
+        hipLaunchKernelGGL(k_sah_offsets, dim3(nt), dim3(64), 0, st, task_chunk0.p, chunk_left.p, chunk_off.p);
+        hipLaunchKernelGGL(k_sah_scatter, dim3(nc), dim3(256), 0, st, ids[src], cen.p, big_a.p, chunk_task.p,
+                           chunk_begin.p, chunk_end.p, ctr.p, acc.p, decision.p, NB, chunk_off.p, ids[src ^ 1u],
+                           ctr.p + 1, A.host);
         BH(hipGetLastError());
-        uint32_t next = 0;
-        BH(hipMemcpyAsync(&next, ctr.p + 1, sizeof(next), hipMemcpyDeviceToHost, st));
         BH(hipStreamSynchronize(st));
-        if (next > max_big) return hipErrorUnknown;
-        big_h.resize(next);
-        if (next) BH(hipMemcpyAsync(big_h.data(), big_b.p, next * sizeof(SahTask), hipMemcpyDeviceToHost, st));
-        BH(hipStreamSynchronize(st));
+        nt = A.host[0];
+        if (nt > max_big) return hipErrorUnknown;
+        src ^= 1u;
         std::swap(big_a.p, big_b.p);
-        if (next) BH(hipMemcpyAsync(big_a.p, big_h.data(), next * sizeof(SahTask), hipMemcpyHostToDevice, st));
     }
-    uint32_t n_small = 0;
-    BH(hipMemcpyAsync(&n_small, ctr.p + 2, sizeof(n_small), hipMemcpyDeviceToHost, st));
+    BH(hipMemcpyAsync(A.host, ctr.p + 2, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     BH(hipStreamSynchronize(st));
-    if (n_small > n) return hipErrorUnknown;
-    if (n_small)
-        hipLaunchKernelGGL(k_sah_small, dim3(n_small), dim3(64 * SAH_SMALL_WAVES),
-                           sizeof(SahSmallLds) + (size_t)SAH_SMALL_WAVES * 3 * NB * SAH_BIN_WORDS * 4, st, small.p, d_order,
-                           tri_box.p, cen.p, NB, max_leaf, (double)node_cost, T);
+    const uint32_t n_small = A.host[0];
+    if (n_small == 0 || n_small > n) return hipErrorUnknown;
+    hipLaunchKernelGGL(k_sah_small, dim3(n_small), dim3(64 * SAH_SMALL_WAVES),
+                       sizeof(SahSmallLds) + (size_t)SAH_SMALL_WAVES * 3 * NB * SAH_BIN_WORDS * 4, st, small.p, ids[0],
+                       ids[1], d_order, tri_box.p, cen.p, NB, max_leaf, (double)node_cost, T);
     BH(hipGetLastError());
 
     // 4-wide collapse from the root (binary node 0), level by level
@@ -1481,35 +1637,23 @@ hipError_t rc_build_bvh_device_sah(const float* d_pos, const uint32_t* d_idx, ui
         size_t sb = scan_bytes;
         BH(rocprim::exclusive_scan(temp.p, sb, nint.p, offs.p, 0, (size_t)m, rocprim::plus<int>(), st));
         hipLaunchKernelGGL(k_collapse_write, dim3(nb(m, 256)), dim3(256), 0, st, TV, lvl_a.p, par_a.p, (int)m, offs.p,
-                           base, base + m, depth, (uint32_t)cap, nodes.p, lvl_b.p, par_b.p, overflow.p);
+                           base, base + m, depth, (uint32_t)cap, nodes.p, lvl_b.p, par_b.p, overflow.p, nint.p,
+                           A.host);
         BH(hipGetLastError());
-        int tail[2] = {0, 0};
-        uint32_t ovf = 0;
-        BH(hipMemcpyAsync(&tail[0], offs.p + (m - 1), sizeof(int), hipMemcpyDeviceToHost, st));
-        BH(hipMemcpyAsync(&tail[1], nint.p + (m - 1), sizeof(int), hipMemcpyDeviceToHost, st));
-        BH(hipMemcpyAsync(&ovf, overflow.p, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
         BH(hipStreamSynchronize(st));
-        if (ovf) return hipErrorUnknown;
         level_start.push_back(base);
         base += m;
         ++depth;
-        m = (uint32_t)(tail[0] + tail[1]);
+        m = A.host[0];
         std::swap(lvl_a.p, lvl_b.p);
         std::swap(par_a.p, par_b.p);
     }
     level_start.push_back(base);
+    BH(hipMemcpyAsync(A.host, overflow.p, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    BH(hipStreamSynchronize(st));
+    if (A.host[0]) return hipErrorUnknown;
     const uint32_t total = level_start.back();
-    Node4* out = nullptr;
-    BH(hipMalloc(reinterpret_cast<void**>(&out), (size_t)total * sizeof(Node4)));
-    hipError_t e = hipMemcpyAsync(out, nodes.p, (size_t)total * sizeof(Node4), hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) {
-        (void)hipFree(out);
-        return e;
-    }
-    *d_nodes_out = out;
-    *n_nodes_out = total;
-    return hipSuccess;
+    return finish_nodes(A, nodes.p, total, d_nodes_out, n_nodes_out, stats, st);
 }
 
 // ---------------------------------------------------------------- top level --------

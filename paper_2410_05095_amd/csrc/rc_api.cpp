@@ -42,13 +42,16 @@ void dev_free(T*& p)
     p = nullptr;
 }
 
-void free_bvh(rc_scene* s)
+// keep_tris: the per-triangle arrays stay, for a build that follows (their sizes are the scene's)
+void free_bvh(rc_scene* s, bool keep_tris = false)
 {
     dev_free(s->d_nodes);
-    dev_free(s->d_order);
-    dev_free(s->d_tris);
+    if (!keep_tris) {
+        dev_free(s->d_order);
+        dev_free(s->d_tris);
+        dev_free(s->d_tri_node);
+    }
     dev_free(s->d_inst);
-    dev_free(s->d_tri_node);
     dev_free(s->d_dirty);
     rc_tlas_free(s->tlas);
     s->two_level = false;
@@ -108,7 +111,7 @@ DevScene dev_scene(const rc_scene* s)
     d.tris = s->d_tris;
     d.n_tris = s->nt;
     // allocated node count (a two-level scene's array has room for its largest top level)
-    d.n_nodes = s->two_level ? s->blas_nodes + s->tlas.cap : (uint32_t)s->hb.nodes.size();
+    d.n_nodes = s->two_level ? s->blas_nodes + s->tlas.cap : s->hb.n_nodes;
     d.max_stack = s->hb.max_stack;
     d.scale = s->scale;
     d.inst = s->two_level ? s->d_inst : nullptr;
@@ -279,7 +282,7 @@ static int upload_body_tris(rc_ctx* c, rc_scene* s)
 static int prepare_dirty_refit(rc_ctx* c, rc_scene* s, uint32_t n_nodes)
 {
     if (!s->d_body_tri_off) return RC_OK;
-    int st = dev_alloc(&s->d_tri_node, s->nt);
+    int st = s->d_tri_node ? RC_OK : dev_alloc(&s->d_tri_node, s->nt);
     const size_t words = n_nodes;   // one mark per node
     if (st == RC_OK) st = dev_alloc(&s->d_dirty, words);
     if (st != RC_OK) return st;
@@ -393,24 +396,25 @@ int rc_scene_destroy(rc_ctx* c, rc_scene* s)
     return RC_OK;
 }
 
-// Device build (k_build.hip): the tree and leaf order stay on the GPU; the nodes are read back once for the
-// host-side statistics (leaf count, SAH cost), after the build time is taken.
+// Device build (k_build.hip): the tree, its leaf order and its statistics (leaf count, SAH cost) come from the GPU;
+// a rebuild of the scene reuses its per-triangle arrays.
 static int build_device(rc_ctx* c, rc_scene* s, uint32_t max_leaf, bool sah = false, uint32_t bins = 32,
                         float node_cost = 4.0f)
 {
-    free_bvh(s);
+    free_bvh(s, true);
     RC_HIP(hipStreamSynchronize(c->stream));
     auto t0 = std::chrono::steady_clock::now();
     HostBvh hb;
-    int st = dev_alloc(&s->d_order, s->nt);
-    if (st == RC_OK) st = dev_alloc(&s->d_tris, 3 * (size_t)s->nt);
+    BuildStats bs;
+    int st = s->d_order ? RC_OK : dev_alloc(&s->d_order, s->nt);
+    if (st == RC_OK && !s->d_tris) st = dev_alloc(&s->d_tris, 3 * (size_t)s->nt);
     if (st != RC_OK) { free_bvh(s); return st; }
     Node4* d_nodes = nullptr;
     uint32_t n_nodes = 0;
     hipError_t e = sah ? rc_build_bvh_device_sah(s->d_pos, s->d_idx, s->nt, bins, max_leaf, node_cost, &d_nodes,
-                                                 &n_nodes, s->d_order, hb.level_start, c->stream)
+                                                 &n_nodes, s->d_order, hb.level_start, bs, c->stream)
                        : rc_build_bvh_device(s->d_pos, s->d_idx, s->nt, max_leaf, nullptr, {}, {}, &d_nodes, &n_nodes,
-                                             s->d_order, hb.level_start, c->stream);
+                                             s->d_order, hb.level_start, bs, c->stream);
     if (e != hipSuccess) { free_bvh(s); return hip_status(e); }
     s->d_nodes = d_nodes;
     rc_launch_pack(s->d_pos, s->d_idx, s->d_order, s->nt, s->d_tris, s->watertight, c->stream);
@@ -418,16 +422,11 @@ static int build_device(rc_ctx* c, rc_scene* s, uint32_t max_leaf, bool sah = fa
     s->build_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     st = prepare_dirty_refit(c, s, n_nodes);
     if (st != RC_OK) { free_bvh(s); return st; }
-    hb.nodes.resize(n_nodes);
-    if (hipMemcpy(hb.nodes.data(), d_nodes, (size_t)n_nodes * sizeof(Node4), hipMemcpyDeviceToHost) != hipSuccess) {
-        free_bvh(s);
-        return RC_ERR_HIP;
-    }
+    hb.n_nodes = n_nodes;
     hb.depth = (uint32_t)hb.level_start.size() - 1;
     hb.max_stack = 3 * hb.depth + 1;
-    for (const Node4& nd : hb.nodes)
-        for (int k = 0; k < 4; ++k) hb.n_leaves += rc_is_leaf(nd.child[k]) ? 1u : 0u;
-    hb.sah_cost = rc_bvh_sah(hb.nodes);
+    hb.n_leaves = bs.n_leaves;
+    hb.sah_cost = bs.sah_cost;
     s->hb = std::move(hb);
     s->built = true;
     s->sah_stale = false;
@@ -471,11 +470,12 @@ static int build_two_level(rc_ctx* c, rc_scene* s, uint32_t max_leaf)
     if (st == RC_OK && hipMemcpyAsync(d_seg, seg.data(), seg.size() * 4, hipMemcpyHostToDevice, c->stream) != hipSuccess)
         st = RC_ERR_HIP;
     HostBvh hb;
+    BuildStats bs;
     Node4* d_blas = nullptr;
     uint32_t n_blas = 0;
     if (st == RC_OK) {
         hipError_t e = rc_build_bvh_device(s->d_rest, s->d_idx, s->nt, max_leaf, d_seg, first, count, &d_blas, &n_blas,
-                                           s->d_order, hb.level_start, c->stream);
+                                           s->d_order, hb.level_start, bs, c->stream);
         if (e != hipSuccess) st = hip_status(e);
     }
     dev_free(d_seg);
@@ -501,13 +501,8 @@ static int build_two_level(rc_ctx* c, rc_scene* s, uint32_t max_leaf)
     uint32_t info[3] = {0, 0, 0};
     if (hipMemcpy(info, s->tlas.info, sizeof(info), hipMemcpyDeviceToHost) != hipSuccess) { free_bvh(s); return RC_ERR_HIP; }
     if (info[2]) { free_bvh(s); return RC_ERR_QUEUE_OVERFLOW; }
-    hb.nodes.resize((size_t)n_blas + info[0]);
-    if (hipMemcpy(hb.nodes.data(), s->d_nodes, hb.nodes.size() * sizeof(Node4), hipMemcpyDeviceToHost) != hipSuccess) {
-        free_bvh(s);
-        return RC_ERR_HIP;
-    }
-    for (const Node4& nd : hb.nodes)
-        for (int k = 0; k < 4; ++k) hb.n_leaves += rc_is_leaf(nd.child[k]) ? 1u : 0u;
+    hb.n_nodes = n_blas + info[0];
+    hb.n_leaves = bs.n_leaves + s->nb;   // the top level holds one leaf per body
     hb.depth = s->blas_depth + info[1];
     // a path crosses at most the top level's bound of levels and one bottom-level tree, plus the end marker
     hb.max_stack = 3 * (s->blas_depth + RC_TLAS_MAX_LEVELS) + 2;
@@ -650,13 +645,14 @@ int rc_bvh_get_stats(rc_ctx* c, const rc_scene* s_, rc_bvh_stats* o)
     }
     if (s->sah_stale) {
         RC_HIP(hipSetDevice(c->device));
+        s->hb.nodes.resize(s->hb.n_nodes);
         RC_HIP(hipMemcpyAsync(s->hb.nodes.data(), s->d_nodes, s->hb.nodes.size() * sizeof(Node4),
                               hipMemcpyDeviceToHost, c->stream));
         RC_HIP(hipStreamSynchronize(c->stream));
         s->hb.sah_cost = rc_bvh_sah(s->hb.nodes);
         s->sah_stale = false;
     }
-    o->n_nodes = s->hb.nodes.size();
+    o->n_nodes = s->hb.n_nodes;
     o->n_leaves = s->hb.n_leaves;
     o->n_tris = s->nt;
     o->depth = s->hb.depth;
@@ -682,7 +678,7 @@ int rc_bvh_export(rc_ctx* c, const rc_scene* s, uint32_t* nodes_out, uint32_t* o
     if (!c || !s) return RC_ERR_INVALID_ARG;
     if (!s->built) return RC_ERR_NOT_BUILT;
     RC_HIP(hipSetDevice(c->device));
-    size_t n_nodes = s->hb.nodes.size();
+    size_t n_nodes = s->hb.n_nodes;
     if (s->two_level) {
         uint32_t info[3] = {0, 0, 0};
         RC_HIP(hipStreamSynchronize(c->stream));
@@ -1202,7 +1198,7 @@ std::string tune_key(rc_ctx* c, rc_scene* const* scenes, uint32_t n_scenes, cons
     uint64_t h = 1469598103934665603ull;
     h = fnv1a(h, &n_scenes, sizeof(n_scenes));
     for (uint32_t i = 0; i < n_scenes; ++i) {
-        uint64_t sz[2] = {scenes[i]->nt, scenes[i]->hb.nodes.size()};
+        uint64_t sz[2] = {scenes[i]->nt, scenes[i]->hb.n_nodes};
         h = fnv1a(h, sz, sizeof(sz));
     }
     h = fnv1a(h, &n_views, sizeof(n_views));

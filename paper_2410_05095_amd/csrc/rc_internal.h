@@ -96,7 +96,8 @@ struct DevLights {
 
 // Host-built BVH (binned SAH, collapsed to 4-wide, nodes in breadth-first order).
 struct HostBvh {
-    std::vector<Node4> nodes;
+    std::vector<Node4> nodes;            // host builds, and trees whose refit boxes were read back; else empty
+    uint32_t n_nodes = 0;
     std::vector<uint32_t> tri_order;     // slot -> original triangle id
     std::vector<uint32_t> level_start;   // node index where each level starts (size depth+1)
     uint32_t depth = 0;
@@ -108,16 +109,21 @@ struct HostBvh {
 bool rc_build_bvh_host(const float* pos, const uint32_t* idx, uint32_t n_tris,
                        uint32_t bins, uint32_t max_leaf, float node_cost, HostBvh& out);
 double rc_bvh_sah(const std::vector<Node4>& nodes);
+// Leaf count and SAH cost (rc_bvh_sah) of a tree that a device build has just finished.
+struct BuildStats {
+    uint64_t n_leaves = 0;
+    double sah_cost = 0.0;
+};
 // Device LBVH builds (k_build.hip); see rc_bvh_build.
 hipError_t rc_build_bvh_device(const float* d_pos, const uint32_t* d_idx, uint32_t n, uint32_t max_leaf,
                                const uint32_t* d_seg, const std::vector<uint32_t>& seg_first,
                                const std::vector<uint32_t>& seg_count, Node4** d_nodes_out, uint32_t* n_nodes_out,
-                               uint32_t* d_order, std::vector<uint32_t>& level_start, hipStream_t st);
+                               uint32_t* d_order, std::vector<uint32_t>& level_start, BuildStats& stats, hipStream_t st);
 // Device binned-SAH build (k_build.hip): the host builder's algorithm on the GPU (bins <= 64); outputs as
 // rc_build_bvh_device.
 hipError_t rc_build_bvh_device_sah(const float* d_pos, const uint32_t* d_idx, uint32_t n, uint32_t bins,
                                    uint32_t max_leaf, float node_cost, Node4** d_nodes_out, uint32_t* n_nodes_out,
-                                   uint32_t* d_order, std::vector<uint32_t>& level_start, hipStream_t st);
+                                   uint32_t* d_order, std::vector<uint32_t>& level_start, BuildStats& stats, hipStream_t st);
 // Top-level workspace (all device memory, sized for n instances at allocation).
 struct TlasWork {
     uint32_t n = 0, cap = 0;
