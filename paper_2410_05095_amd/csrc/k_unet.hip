@@ -584,84 +584,147 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void
 }
 
 // ---------------------------------------------------------------- FP32 copy of the network
-// 3x3 convolution in FP32 on v_mfma_f32_16x16x4_f32: FP32 activations and weights (the master copy,
-// transposed to [tap][ci][co]), FP32 accumulation.  Same tiling as k_conv_lds with one 16-pixel M-tile
-// per wave; the halo of a CC-channel chunk is staged in LDS; the first layer reads the BF16 features, and
-// the decoder's upsample + concat is fused into the halo load as in the BF16 kernel.
-template <int NT, int CC>
-__global__ __launch_bounds__(256) void k_conv_f32(ConvArgsF32 a)
+// 3x3 convolution in FP32 on v_mfma_f32_16x16x4_f32: FP32 activations and weights, FP32 accumulation.  Bound by the
+// matrix cores (32 cycles per instruction), so the operands come in wide LDS reads that serve many instructions.
+// Workgroup of 4 waves, tile of 4 rows x 16 MT columns x 16 NT output channels (blockIdx.y: the block of output
+// channels), wave w computes row w as MT x NT tiles of 16 x 16.  Per chunk of CC input channels the halo and the
+// chunk's weights are staged in LDS; of the chunk, lane group kq = lane / 16 holds the S = CC / 4 channels S kq ..
+// S kq + S - 1, its K index 4 s + kq of instruction s standing for channel S kq + s on both sides, so that one
+// 16-byte read per tile and tap feeds S instructions of each of its row or column of tiles.  The first layer reads the
+// BF16 features; the decoder's upsample + concat is fused into the halo load as in the BF16 kernel.
+// 540x960 inference: 2.43 ms when each instruction took one 4-byte LDS read and one 4-byte load from the weights in
+// memory (48 TFLOP/s), 1.30 ms now (90; 1080x1920 4.4 ms, 106 TFLOP/s).  The next chunk's halo, or halo and weights, held
+// in registers under this chunk's instructions measured 6% and 60% slower.
+constexpr int F32_NB = 64;   // output channels of a block: 16 NT = min(Cout, F32_NB)
+
+template <int S>
+struct FVec;
+template <>
+struct FVec<4> { typedef float4 t; };
+template <>
+struct FVec<2> { typedef float2 t; };
+__device__ inline float fvec_at(const float4& v, int s) { return s == 0 ? v.x : s == 1 ? v.y : s == 2 ? v.z : v.w; }
+__device__ inline float fvec_at(const float2& v, int s) { return s == 0 ? v.x : v.y; }
+
+template <int MT, int NT, int CC>
+struct ConvF32 {
+    static constexpr int TW = 16 * MT, HW = TW + 2, HR = 6, S = CC / 4;
+    static constexpr int HALO_BYTES = 4 * HR * HW * S * 4, W_BYTES = 9 * 4 * 16 * NT * S * 4;
+    static_assert(HALO_BYTES % 16 == 0 && W_BYTES % 1024 == 0, "LDS parts in 16-byte and wave-load units");
+    static constexpr size_t bytes() { return (size_t)HALO_BYTES + W_BYTES; }
+};
+
+// W_BYTES of weights from src straight into LDS at dst, 1 KB per wave and instruction
+template <int W_BYTES>
+__device__ __attribute__((always_inline)) inline void f32_weights_to_lds(const char* src, char* dst, int wave, int lane)
 {
-    extern __shared__ float cf_lds[];
-    constexpr int TW = 16, HW = TW + 2, HR = 6, PST = CC + 1;
+    for (int f = wave; f < W_BYTES / 1024; f += 4)
+        __builtin_amdgcn_global_load_lds(src + f * 1024 + lane * 16, dst + f * 1024, 16, 0, 0);
+}
+
+template <int MT, int NT, int CC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_f32(ConvArgsF32 a)
+{
+    extern __shared__ uint4 conv_lds[];
+    using L = ConvF32<MT, NT, CC>;
+    constexpr int HW = L::HW, HR = L::HR, S = L::S, HP = HR * HW;
+    typedef typename FVec<S>::t vec;
+    vec* halo = reinterpret_cast<vec*>(conv_lds);                                               // [4][HP]
+    char* wl = reinterpret_cast<char*>(conv_lds) + L::HALO_BYTES;
+    const vec* wt = reinterpret_cast<const vec*>(wl);                                           // [9][4][16 NT]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int tiles_x = (a.W + TW - 1) / TW, tiles_y = (a.H + 3) / 4;
-    int tt = blockIdx.x;
+    const int tiles_x = (a.W + L::TW - 1) / L::TW, tiles_y = (a.H + 3) / 4;
+    int tt = xcd_tile(blockIdx.x, gridDim.x);
     const int tx = tt % tiles_x;
     tt /= tiles_x;
     const int ty = tt % tiles_y, n = tt / tiles_y;
-    const int x0 = tx * TW, y0 = ty * 4;
+    const int x0 = tx * L::TW, y0 = ty * 4;
     const int r = lane & 15, kq = lane >> 4;
-    const int Cs = a.Cin - a.Ca;
-    f32x4 acc[NT];
+    const int Cs = a.Cin - a.Ca, n_blocks = gridDim.y;
+    f32x4 acc[MT][NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int c0 = 0; c0 < a.Cin; c0 += CC) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < HR * HW * (CC / 4); i += 256) {
-            const int g4 = i % (CC / 4), pix = i / (CC / 4);
-            const int hx = pix % HW, hy = pix / HW;
-            const int y = y0 - 1 + hy, x = x0 - 1 + hx, ci = c0 + 4 * g4;
-            float v[4] = {0.f, 0.f, 0.f, 0.f};
-            if (y >= 0 && y < a.H && x >= 0 && x < a.W) {
-                if (a.in_bf16) {
-                    const uint2 q = *reinterpret_cast<const uint2*>(
-                        static_cast<const uint16_t*>(a.in) + ((size_t)(n * a.H + y) * a.W + x) * a.Cin + ci);
-                    v[0] = __uint_as_float(q.x << 16); v[1] = __uint_as_float(q.x & 0xFFFF0000u);
-                    v[2] = __uint_as_float(q.y << 16); v[3] = __uint_as_float(q.y & 0xFFFF0000u);
-                } else {
-                    const float* src;
-                    if (a.in2 == nullptr)
-                        src = static_cast<const float*>(a.in) + ((size_t)(n * a.H + y) * a.W + x) * a.Cin + ci;
-                    else if (ci < a.Ca)
-                        src = static_cast<const float*>(a.in) +
-                              ((size_t)(n * (a.H / 2) + y / 2) * (a.W / 2) + x / 2) * a.Ca + ci;
-                    else
-                        src = a.in2 + ((size_t)(n * a.H + y) * a.W + x) * Cs + (ci - a.Ca);
-                    const float4 q = *reinterpret_cast<const float4*>(src);
-                    v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-                }
-            }
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) cf_lds[pix * PST + 4 * g4 + e] = v[e];
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // halo item i: the S channels of lane group i % 4 of halo pixel i / 4, zero outside the image (clamped address)
+    constexpr int ITEMS = 4 * HP, PF = (ITEMS + 255) / 256;
+    auto item = [&](int c0, int i) -> vec {
+        const int pix = i >> 2, ci = c0 + S * (i & 3);
+        const int y = y0 - 1 + pix / HW, x = x0 - 1 + pix % HW;
+        const bool inb = (unsigned)y < (unsigned)a.H && (unsigned)x < (unsigned)a.W;
+        const int yc = min(max(y, 0), a.H - 1), xc = min(max(x, 0), a.W - 1);
+        vec v;
+        if constexpr (S == 2) {   // 8-channel BF16 features
+            const uint32_t q = *reinterpret_cast<const uint32_t*>(static_cast<const uint16_t*>(a.in) +
+                                                                  ((size_t)(n * a.H + yc) * a.W + xc) * a.Cin + ci);
+            v.x = inb ? __uint_as_float(q << 16) : 0.0f;
+            v.y = inb ? __uint_as_float(q & 0xFFFF0000u) : 0.0f;
+        } else {
+            const float* src;
+            if (a.in2 == nullptr)
+                src = static_cast<const float*>(a.in) + ((size_t)(n * a.H + yc) * a.W + xc) * a.Cin + ci;
+            else if (ci < a.Ca)
+                src = static_cast<const float*>(a.in) +
+                      ((size_t)(n * (a.H >> 1) + (yc >> 1)) * (a.W >> 1) + (xc >> 1)) * a.Ca + ci;
+            else
+                src = a.in2 + ((size_t)(n * a.H + yc) * a.W + xc) * Cs + (ci - a.Ca);
+            const float4 q = *reinterpret_cast<const float4*>(src);
+            v.x = inb ? q.x : 0.0f; v.y = inb ? q.y : 0.0f; v.z = inb ? q.z : 0.0f; v.w = inb ? q.w : 0.0f;
         }
+        return v;
+    };
+    for (int c0 = 0; c0 < a.Cin; c0 += CC) {
+        vec pf[PF];
+#pragma unroll
+        for (int k = 0; k < PF; ++k) {
+            const int i = (int)threadIdx.x + 256 * k;
+            if (ITEMS % 256 == 0 || i < ITEMS) pf[k] = item(c0, i);
+        }
+        __syncthreads();   // every wave is done with the previous chunk
+        f32_weights_to_lds<L::W_BYTES>(reinterpret_cast<const char*>(a.wt) +
+                                           ((size_t)(c0 / CC) * n_blocks + blockIdx.y) * L::W_BYTES,
+                                       wl, wave, lane);
+#pragma unroll
+        for (int k = 0; k < PF; ++k) {
+            const int i = (int)threadIdx.x + 256 * k;
+            if (ITEMS % 256 == 0 || i < ITEMS) halo[(i & 3) * HP + (i >> 2)] = pf[k];
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the direct-to-LDS loads have landed
         __syncthreads();
+#pragma unroll
         for (int tap = 0; tap < 9; ++tap) {
             const int dy = tap / 3, dx = tap % 3;
-            const float* arow = cf_lds + ((wave + dy) * HW + r + dx) * PST;
-            const float* wrow = a.wt + ((size_t)tap * a.Cin + c0) * a.Cout + r;
-            for (int kc = 0; kc < CC; kc += 4) {
-                const float A = arow[kc + kq];
+            vec A[MT], B[NT];
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const float B = wrow[(size_t)(kc + kq) * a.Cout + 16 * nt];
-                    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(A, B, acc[nt], 0, 0, 0);
-                }
-            }
+            for (int mt = 0; mt < MT; ++mt) A[mt] = halo[kq * HP + (wave + dy) * HW + 16 * mt + r + dx];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) B[nt] = wt[(tap * 4 + kq) * 16 * NT + 16 * nt + r];
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(fvec_at(A[mt], s), fvec_at(B[nt], s),
+                                                                           acc[mt][nt], 0, 0, 0);
         }
     }
     // D layout: lane holds column (channel) 16 nt + (lane & 15), rows (pixels) 4 (lane >> 4) + e
     const int y = y0 + wave;
     if (y >= a.H) return;
+    const int co0 = blockIdx.y * 16 * NT;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-        const int co = 16 * nt + r;
+        const int co = co0 + 16 * nt + r;
         const float b = a.bias[co];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int x = x0 + 4 * kq + e;
-            if (x >= a.W) continue;
-            a.out[((size_t)(n * a.H + y) * a.W + x) * a.Cout + co] = fmaxf(acc[nt][e] + b, 0.0f);
-        }
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int x = x0 + 16 * mt + 4 * kq + e;
+                if (x >= a.W) continue;
+                a.out[((size_t)(n * a.H + y) * a.W + x) * a.Cout + co] = fmaxf(acc[mt][nt][e] + b, 0.0f);
+            }
     }
 }
 
@@ -697,14 +760,19 @@ __global__ __launch_bounds__(256) void k_head_f32(const float* d1, const float* 
     y[p] = 1.0f / (1.0f + expf(-s));
 }
 
-// FP32 master [Cout][9][Cin] -> [9][Cin][Cout]
-__global__ __launch_bounds__(256) void k_weights_f32t(const float* w, int Cout, int Cin, float* wt)
+// FP32 master [Cout][9][Cin] of every layer -> the order k_conv_f32 stages them in: [chunk of CC channels][block of
+// output channels][tap][lane group kq][output channel of the block][S], CC = 16 (8 for the 8-channel first layer),
+// channel CC chunk + S kq + s
+__global__ __launch_bounds__(256) void k_weights_f32(UnetF32Weights u)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int n = Cout * 9 * Cin;
-    if (i >= n) return;
-    int ci = i % Cin, tap = (i / Cin) % 9, co = i / (9 * Cin);
-    wt[((size_t)tap * Cin + ci) * Cout + co] = w[i];
+    const UnetF32Weights::Layer l = u.layer[blockIdx.y];
+    const int cc = l.cin % 16 == 0 ? 16 : 8, S = cc / 4, cb = min(l.cout, F32_NB);
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < l.cout * 9 * l.cin; i += gridDim.x * 256) {
+        const int ci = i % l.cin, tap = (i / l.cin) % 9, co = i / (9 * l.cin);
+        const int chunk = ci / cc, kq = ci % cc / S, s = ci % S, blk = co / cb;
+        const size_t o = ((((size_t)chunk * (l.cout / cb) + blk) * 9 + tap) * 4 + kq) * cb * S + (size_t)(co % cb) * S + s;
+        u.out[l.out + o] = u.w[l.in + i];
+    }
 }
 
 // ---------------------------------------------------------------- weight gradient
@@ -1377,16 +1445,36 @@ void unet_adam(float* w, const float* g, float* m, float* v, int n, float lr, fl
     hipLaunchKernelGGL(k_adam, dim3(nb(n, 256)), dim3(256), 0, st, w, g, m, v, n, lr, b1, b2, eps, c1, c2);
 }
 
+namespace {
+template <int MT, int NT, int CC>
+void launch_conv_f32(const ConvArgsF32& a, hipStream_t st)
+{
+    static_assert(ConvF32<MT, NT, CC>::bytes() <= 65536, "LDS beyond 64 KB");
+    const size_t tiles = (size_t)a.N * ((a.H + 3) / 4) * ((a.W + 16 * MT - 1) / (16 * MT));
+    const size_t lds = ConvF32<MT, NT, CC>::bytes();
+    hipLaunchKernelGGL((k_conv_f32<MT, NT, CC>), dim3((unsigned)tiles, a.Cout / (16 * NT)), dim3(256), lds, st, a);
+}
+}  // namespace
+
 void unet_conv3x3_f32(const ConvArgsF32& a, hipStream_t st)
 {
-    const int nt = a.Cout / 16, cc = a.Cin % 32 == 0 ? 32 : 8;
-    const size_t tiles = (size_t)a.N * ((a.H + 3) / 4) * ((a.W + 15) / 16);
-    const size_t lds = (size_t)6 * 18 * (cc + 1) * 4;
-    switch (nt * 100 + cc) {
-    case 208: hipLaunchKernelGGL((k_conv_f32<2, 8>), dim3((unsigned)tiles), dim3(256), lds, st, a); break;
-    case 232: hipLaunchKernelGGL((k_conv_f32<2, 32>), dim3((unsigned)tiles), dim3(256), lds, st, a); break;
-    case 432: hipLaunchKernelGGL((k_conv_f32<4, 32>), dim3((unsigned)tiles), dim3(256), lds, st, a); break;
-    case 832: hipLaunchKernelGGL((k_conv_f32<8, 32>), dim3((unsigned)tiles), dim3(256), lds, st, a); break;
+    // Narrow tiles hold little LDS and few registers, so more workgroups overlap one's staging with another's
+    // instructions and the last round of workgroups is shorter; wide ones read and stage less per instruction, which
+    // pays once there are many.  All convolutions of an inference, tiles of 16 / 32 / 64 columns: 256^2 224 / 318 /
+    // 486 us, 540x960 1239 / 1318 / 1516 us, 1080x1920 4491 / 4326 / 4429 us (its 64-channel layers 1965 / 1903 / 1774).
+    const int nt = std::min(a.Cout, F32_NB) / 16;
+    auto blocks = [&](int mt) {
+        return (size_t)a.N * ((a.H + 3) / 4) * ((a.W + 16 * mt - 1) / (16 * mt)) * (a.Cout / (16 * nt));
+    };
+    const int mt = nt == 4 && blocks(4) >= 2000 ? 4 : blocks(2) >= 4000 ? 2 : 1;
+    switch ((a.Cin % 16 == 0 ? 100 : 0) + 10 * nt + mt) {
+    case 22: launch_conv_f32<2, 2, 8>(a, st); break;
+    case 21: launch_conv_f32<1, 2, 8>(a, st); break;
+    case 122: launch_conv_f32<2, 2, 16>(a, st); break;
+    case 121: launch_conv_f32<1, 2, 16>(a, st); break;
+    case 144: launch_conv_f32<4, 4, 16>(a, st); break;
+    case 142: launch_conv_f32<2, 4, 16>(a, st); break;
+    case 141: launch_conv_f32<1, 4, 16>(a, st); break;
     default: break;   // channel counts of this network only
     }
 }
@@ -1402,10 +1490,9 @@ void unet_head_f32(const float* d1, const float* wh, const float* bh, int P, flo
     hipLaunchKernelGGL(k_head_f32, dim3(nb(P, 256)), dim3(256), 0, st, d1, wh, bh, P, y);
 }
 
-void unet_weights_f32t(const float* w, int Cout, int Cin, float* wt, hipStream_t st)
+void unet_weights_f32(const UnetF32Weights& u, hipStream_t st)
 {
-    int n = Cout * 9 * Cin;
-    hipLaunchKernelGGL(k_weights_f32t, dim3(nb(n, 256)), dim3(256), 0, st, w, Cout, Cin, wt);
+    hipLaunchKernelGGL(k_weights_f32, dim3(64, u.n_layers), dim3(256), 0, st, u);
 }
 
 void unet_fill_f32(float* p, float v, size_t n, hipStream_t st)

@@ -76,7 +76,7 @@ struct rc_denoiser {
     float* d_wt32 = nullptr;
     float* act32 = nullptr;
     int fn = 0, fh = 0, fw = 0;
-    size_t f_e1a, f_e1b, f_p1, f_e2a, f_e2b, f_p2, f_bna, f_bnb, f_d2a, f_d2b, f_d1a, f_d1b, f_y, f_total;
+    size_t f_e1a, f_e1b, f_p1, f_e2a, f_e2b, f_p2, f_bna, f_bnb, f_d2a, f_d2b, f_d1a, f_d1b, f_total;
 };
 
 namespace {
@@ -138,7 +138,6 @@ int ensure_workspace_f32(rc_denoiser* d, int n, int h, int w)
     d->f_e2a = take(P2 * 64); d->f_e2b = take(P2 * 64); d->f_p2 = take(P4 * 64);
     d->f_bna = take(P4 * 128); d->f_bnb = take(P4 * 128);
     d->f_d2a = take(P2 * 64); d->f_d2b = take(P2 * 64); d->f_d1a = take(P * 32); d->f_d1b = take(P * 32);
-    d->f_y = take(P);
     d->f_total = o;
     DN_HIP(hipMalloc(reinterpret_cast<void**>(&d->act32), d->f_total * 4));
     d->fn = n; d->fh = h; d->fw = w;
@@ -255,11 +254,11 @@ int forward(rc_denoiser* d, const uint16_t* x, int n, int h, int w, hipStream_t 
 }
 
 // layer l in FP32 (input `in` float, or the BF16 features for the first layer)
-void conv_f32(rc_denoiser* d, const void* in, bool in_bf16, int n, int h, int w, int l, float* out, hipStream_t st,
+void conv_f32(rc_denoiser* d, const void* in, int n, int h, int w, int l, float* out, hipStream_t st,
               const float* skip = nullptr, int Ca = 0)
 {
     ConvArgsF32 a = {};
-    a.in = in; a.in_bf16 = in_bf16 ? 1 : 0; a.in2 = skip; a.Ca = Ca;
+    a.in = in; a.in2 = skip; a.Ca = Ca;
     a.N = n; a.H = h; a.W = w; a.Cin = LAYERS[l].cin;
     a.wt = d->d_wt32 + d->off_bf[l];
     a.bias = d->d_w + d->off_b[l];
@@ -268,28 +267,32 @@ void conv_f32(rc_denoiser* d, const void* in, bool in_bf16, int n, int h, int w,
     unet_conv3x3_f32(a, st);
 }
 
-int forward_f32(rc_denoiser* d, const uint16_t* x, int n, int h, int w, hipStream_t st)
+int forward_f32(rc_denoiser* d, const uint16_t* x, int n, int h, int w, float* y_out, hipStream_t st)
 {
     int st_ = ensure_workspace_f32(d, n, h, w);
     if (st_ != RC_OK) return st_;
-    for (int l = 0; l < N_LAYERS; ++l)
-        unet_weights_f32t(d->d_w + d->off_w[l], LAYERS[l].cout, LAYERS[l].cin, d->d_wt32 + d->off_bf[l], st);
+    UnetF32Weights u = {};
+    u.n_layers = N_LAYERS;
+    u.w = d->d_w;
+    u.out = d->d_wt32;
+    for (int l = 0; l < N_LAYERS; ++l) u.layer[l] = {LAYERS[l].cin, LAYERS[l].cout, d->off_w[l], d->off_bf[l]};
+    unet_weights_f32(u, st);
     float* F = d->act32;
     int h2 = h / 2, w2 = w / 2, h4 = h / 4, w4 = w / 4;
-    conv_f32(d, x, true, n, h, w, E1A, F + d->f_e1a, st);
-    conv_f32(d, F + d->f_e1a, false, n, h, w, E1B, F + d->f_e1b, st);
+    conv_f32(d, x, n, h, w, E1A, F + d->f_e1a, st);
+    conv_f32(d, F + d->f_e1a, n, h, w, E1B, F + d->f_e1b, st);
     unet_pool2_f32(F + d->f_e1b, n, h, w, 32, F + d->f_p1, st);
-    conv_f32(d, F + d->f_p1, false, n, h2, w2, E2A, F + d->f_e2a, st);
-    conv_f32(d, F + d->f_e2a, false, n, h2, w2, E2B, F + d->f_e2b, st);
+    conv_f32(d, F + d->f_p1, n, h2, w2, E2A, F + d->f_e2a, st);
+    conv_f32(d, F + d->f_e2a, n, h2, w2, E2B, F + d->f_e2b, st);
     unet_pool2_f32(F + d->f_e2b, n, h2, w2, 64, F + d->f_p2, st);
-    conv_f32(d, F + d->f_p2, false, n, h4, w4, BNA, F + d->f_bna, st);
-    conv_f32(d, F + d->f_bna, false, n, h4, w4, BNB, F + d->f_bnb, st);
-    conv_f32(d, F + d->f_bnb, false, n, h2, w2, D2A, F + d->f_d2a, st, F + d->f_e2b, 128);
-    conv_f32(d, F + d->f_d2a, false, n, h2, w2, D2B, F + d->f_d2b, st);
-    conv_f32(d, F + d->f_d2b, false, n, h, w, D1A, F + d->f_d1a, st, F + d->f_e1b, 64);
-    conv_f32(d, F + d->f_d1a, false, n, h, w, D1B, F + d->f_d1b, st);
-    unet_head_f32(F + d->f_d1b, d->d_w + d->off_w[N_LAYERS], d->d_w + d->off_b[N_LAYERS], n * h * w,
-                  F + d->f_y, st);
+    conv_f32(d, F + d->f_p2, n, h4, w4, BNA, F + d->f_bna, st);
+    conv_f32(d, F + d->f_bna, n, h4, w4, BNB, F + d->f_bnb, st);
+    conv_f32(d, F + d->f_bnb, n, h2, w2, D2A, F + d->f_d2a, st, F + d->f_e2b, 128);
+    conv_f32(d, F + d->f_d2a, n, h2, w2, D2B, F + d->f_d2b, st);
+    conv_f32(d, F + d->f_d2b, n, h, w, D1A, F + d->f_d1a, st, F + d->f_e1b, 64);
+    conv_f32(d, F + d->f_d1a, n, h, w, D1B, F + d->f_d1b, st);
+    unet_head_f32(F + d->f_d1b, d->d_w + d->off_w[N_LAYERS], d->d_w + d->off_b[N_LAYERS], n * h * w, y_out,
+                  st);
     DN_HIP(hipGetLastError());
     return RC_OK;
 }
@@ -489,10 +492,7 @@ int rc_denoiser_infer_fp32(rc_ctx* c, rc_denoiser* d, const uint16_t* d_feat, ui
     if (reinterpret_cast<uintptr_t>(d_feat) & 15u) return RC_ERR_INVALID_ARG;
     DN_HIP(hipSetDevice(d->device));
     hipStream_t s = ctx_stream(c);
-    int st = forward_f32(d, d_feat, (int)n, (int)h, (int)w, s);
-    if (st != RC_OK) return st;
-    DN_HIP(hipMemcpyAsync(d_out, d->act32 + d->f_y, (size_t)n * h * w * 4, hipMemcpyDeviceToDevice, s));
-    return RC_OK;
+    return forward_f32(d, d_feat, (int)n, (int)h, (int)w, d_out, s);
 }
 
 int rc_denoiser_train_step(rc_ctx* c, rc_denoiser* d, const uint16_t* d_feat, const float* d_target,

@@ -24,12 +24,11 @@ struct ConvArgs {
 };
 
 struct ConvArgsF32 {
-    const void* in;         // NHWC float (bf16 when in_bf16), Cin channels; with in2: N x H/2 x W/2 x Ca float
-    int in_bf16;
+    const void* in;         // NHWC float (bf16 for the 8-channel first layer), Cin channels; with in2: N x H/2 x W/2 x Ca
     const float* in2;       // optional skip tensor N x H x W x (Cin - Ca) (concatenated after upsampled `in`)
     int Ca;
     int N, H, W, Cin;
-    const float* wt;        // [9][Cin][Cout] float
+    const float* wt;        // in unet_weights_f32's order
     const float* bias;      // Cout floats
     float* out;             // NHWC float, Cout channels (ReLU applied)
     int Cout;
@@ -79,4 +78,14 @@ void unet_fill_f32(float* p, float v, size_t n, hipStream_t st);
 void unet_conv3x3_f32(const ConvArgsF32& a, hipStream_t st);
 void unet_pool2_f32(const float* in, int N, int H, int W, int C, float* out, hipStream_t st);
 void unet_head_f32(const float* d1, const float* wh, const float* bh, int P, float* y, hipStream_t st);
-void unet_weights_f32t(const float* w, int Cout, int Cin, float* wt, hipStream_t st);
+// the FP32 master weights of all layers in the order that unet_conv3x3_f32 reads
+struct UnetF32Weights {
+    struct Layer {
+        int cin, cout;
+        size_t in, out;     // offsets in w and out
+    } layer[10];
+    int n_layers;
+    const float* w;
+    float* out;
+};
+void unet_weights_f32(const UnetF32Weights& u, hipStream_t st);
