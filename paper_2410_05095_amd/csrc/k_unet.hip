@@ -776,172 +776,151 @@ __global__ __launch_bounds__(256) void k_weights_f32(UnetF32Weights u)
 }
 
 // ---------------------------------------------------------------- weight gradient
-// One wave per (pixel chunk, tap, 16-channel output tile, 16-channel input tile).
-__global__ __launch_bounds__(64) void k_wgrad(WgradArgs a)
+// dW[co][tap][ci] = sum_p g[p][co] x[p + off(tap)][ci] and db[co] = sum_p g[p][co] as MFMA GEMMs with K = pixels.
+// Both operands need 8 consecutive pixels of one channel per lane, while memory holds the channels of a pixel together;
+// ds_read_b64_tr_b16 transposes on the way out of LDS (of each 16 lanes, lane 4 q + c reads 4 channels of pixel q and
+// lane i receives channel i of the 4 pixels), so tiles are staged as they lie in memory.
+// Workgroup of 3 waves; wave w owns the taps of kernel row dy = w.  A pixel tile is 2 rows x 64 columns: its gradient (16
+// CO_T channels) and its input halo (4 rows x 66 columns, 16 CI_T channels, zero outside the image); the next tile's
+// groups are loaded into registers under this tile's instructions.  With a second source (the decoder's inputs)
+// channels below Ca come from the 2x nearest-upsampled tensor, so the concatenation is never stored.  A workgroup
+// accumulates a chunk of consecutive tiles for one group of output and one of input channels; chunks are then added
+// in order, so the result is deterministic.  The bias gradient is one more product, with ones, in wave 0.
+// Bound by memory for 32 channels (32 -> 32 at 8x512^2: 268 MB in 78 us, 3.4 TB/s) and by the matrix cores and the LDS
+// reads that feed them beyond.  With tiles transposed in registers and stored to LDS in three shifted copies, all
+// layers of the 8x512^2 step took 1.78 ms here, besides 0.21 ms of bias sums and 0.17 ms to store the
+// concatenations; 0.97 ms now.  OCC, waves per SIMD: without the bound the compiler keeps copies of the sums in a
+// second register class and one wave fits (96 -> 32 channels 334 us, 212 at 2 waves); 32 -> 32 at 2 instead of 3: 92 us.
+constexpr int WG_TW = 64, WG_R = 2, WG_THREADS = 192;
+template <int CO_T, int CI_T, bool SMALL>
+struct Wgrad {
+    static constexpr int HW = WG_TW + 2, HR = WG_R + 2;
+    static constexpr int XC8 = SMALL ? 1 : 2 * CI_T, GC8 = 2 * CO_T;          // 16-byte groups per pixel
+    static constexpr int X_ITEMS = HR * HW * XC8, G_ITEMS = WG_R * WG_TW * GC8;
+    static constexpr int XPT = (X_ITEMS + WG_THREADS - 1) / WG_THREADS, GPT = (G_ITEMS + WG_THREADS - 1) / WG_THREADS;
+    static constexpr int G_OFF = X_ITEMS + (SMALL ? 1 : 0);   // in groups; a read of 16 channels of the last 8-channel pixel
+    static constexpr int GROUPS = G_OFF + G_ITEMS;
+};
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4;
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+// 8 K values (pixels) of one channel per lane: two transposed reads, `half` bytes apart
+__device__ inline bf16x8 tr_frag(const char* p, int half)
 {
-    const int lane = threadIdx.x, r = lane & 15, g = lane >> 4;
-    const int P = a.N * a.H * a.W;
-    const int chunk = blockIdx.x, tap = blockIdx.y;
-    const int ci_tiles = (a.Cin + 15) / 16;
-    const int co_t = blockIdx.z / ci_tiles, ci_t = blockIdx.z % ci_tiles;
-    const int co = co_t * 16 + r, ci = ci_t * 16 + r;
-    const int dy = tap / 3 - 1, dx = tap % 3 - 1;
-    const int pb0 = chunk * a.chunk, pe = min(P, pb0 + a.chunk);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int pb = pb0; pb < pe; pb += 32) {
-        uint16_t av[8], bv[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            int p = pb + 8 * g + e;
-            av[e] = 0;
-            bv[e] = 0;
-            if (p < pe) {
-                av[e] = a.g[(size_t)p * a.Cout + co];
-                int x = p % a.W, t = p / a.W, y = t % a.H, n = t / a.H;
-                int ys = y + dy, xs = x + dx;
-                if (ci < a.Cin && ys >= 0 && ys < a.H && xs >= 0 && xs < a.W)
-                    bv[e] = a.x[((size_t)(n * a.H + ys) * a.W + xs) * a.Cin + ci];
-            }
-        }
-        uint4 ua, ub;
-        ua.x = av[0] | ((uint32_t)av[1] << 16); ua.y = av[2] | ((uint32_t)av[3] << 16);
-        ua.z = av[4] | ((uint32_t)av[5] << 16); ua.w = av[6] | ((uint32_t)av[7] << 16);
-        ub.x = bv[0] | ((uint32_t)bv[1] << 16); ub.y = bv[2] | ((uint32_t)bv[3] << 16);
-        ub.z = bv[4] | ((uint32_t)bv[5] << 16); ub.w = bv[6] | ((uint32_t)bv[7] << 16);
-        bf16x8 A = __builtin_bit_cast(bf16x8, ua);
-        bf16x8 B = __builtin_bit_cast(bf16x8, ub);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B, acc, 0, 0, 0);
-    }
-    // D[i = output channel][j = input channel]: lane holds j = lane & 15, rows 4 (lane >> 4) + i
-    int cio = ci_t * 16 + r;
-    if (cio >= a.Cin) return;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int coo = co_t * 16 + 4 * g + i;
-        a.partial[(((size_t)chunk * a.Cout + coo) * 9 + tap) * a.Cin + cio] = acc[i];
-    }
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + half));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// ---------------------------------------------------------------- weight gradient, LDS-tiled
-// dW[co][tap][ci] = sum_p g[p][co] x[p + off(tap)][ci] as MFMA GEMMs with K = pixels.  Workgroup of 3
-// waves; wave w owns the taps of kernel row dy = w.  Pixel tiles are 2 rows x 64 columns; for each tile
-// the gradient (all Cout channels) is staged in LDS transposed to [channel][pixel], and the input halo
-// (4 rows x 66 columns, 16 CI_T channels) in three copies shifted by dx = 0, 1, 2, also [channel][pixel],
-// so that every MFMA operand (8 consecutive pixels of one channel) is one aligned 16-byte LDS read.  A
-// workgroup accumulates a chunk of consecutive tiles for one group of input channels and writes its
-// partial sums; the chunks are then added in chunk order, so the result is deterministic.
-constexpr int WG_TW = 64, WG_R = 2;
-template <int CO_T, int CI_T>
-__global__ __launch_bounds__(192) void k_wgrad_lds(WgradArgs a, int tiles_per_chunk)
+// v or zeros, by component (a conditional between two structs selects their addresses and keeps both in scratch memory)
+__device__ inline uint4 keep_if(const uint4& v, uint32_t keep)
 {
-    extern __shared__ uint4 wg_lds[];
-    constexpr int TW = WG_TW, R = WG_R, HRW = R + 2, HC = TW + 2;
-    constexpr int CIN_T = 16 * CI_T, COUT = 16 * CO_T;
-    constexpr int GS_CO = R * TW + 8;      // bf16 elements per gradient channel row (padded)
-    constexpr int XS_CI = HRW * TW + 8;    // bf16 elements per input channel (4 halo rows, padded)
-    constexpr int XS_DX = CIN_T * XS_CI;
-    uint16_t* gs = reinterpret_cast<uint16_t*>(wg_lds);
-    uint16_t* xs = gs + COUT * GS_CO;
+    return make_uint4(keep ? v.x : 0u, keep ? v.y : 0u, keep ? v.z : 0u, keep ? v.w : 0u);
+}
+
+// slot of channel group c8 in a staged gradient pixel px: with 64 channels, pixels lie 32 banks apart, so the 32-byte
+// units of 4 neighbouring pixels are rotated against each other
+template <int GC8>
+__device__ inline int g_slot(int c8, int px) { return GC8 >= 8 ? c8 ^ ((px & 3) << 1) : c8; }
+
+template <int CO_T, int CI_T, bool SMALL, bool CAT, int OCC>
+__global__ __launch_bounds__(WG_THREADS) __attribute__((amdgpu_waves_per_eu(OCC))) void k_wgrad(WgradArgs a, int tiles_per_chunk, int ci_groups)
+{
+    using L = Wgrad<CO_T, CI_T, SMALL>;
+    __shared__ uint4 lds[L::GROUPS];
+    constexpr int XPB = L::XC8 * 16, GPB = L::GC8 * 16;   // bytes per staged pixel
+    const char* xs = reinterpret_cast<const char*>(lds);
+    const char* gs = reinterpret_cast<const char*>(lds + L::G_OFF);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, g = lane >> 4;
-    const int ci0 = blockIdx.y * CIN_T;
-    const int tiles_x = (a.W + TW - 1) / TW, tiles_y = (a.H + R - 1) / R;
+    const int cig = blockIdx.y % ci_groups, cog = blockIdx.y / ci_groups;
+    const int ci0 = cig * 16 * CI_T, co0 = cog * 16 * CO_T;
+    const int tiles_x = (a.W + WG_TW - 1) / WG_TW, tiles_y = (a.H + WG_R - 1) / WG_R;
     const int n_tiles = a.N * tiles_x * tiles_y;
     const int t_begin = blockIdx.x * tiles_per_chunk, t_end = min(n_tiles, t_begin + tiles_per_chunk);
-    const int c8_out = a.Cout / 8;
-    f32x4 acc[3][CO_T][CI_T];
+    f32x4 acc[3][CO_T][CI_T], accb[CO_T];
 #pragma unroll
-    for (int dx = 0; dx < 3; ++dx)
+    for (int i = 0; i < CO_T; ++i) {
+        accb[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < CO_T; ++i)
+        for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
             for (int j = 0; j < CI_T; ++j) acc[dx][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int t = t_begin; t < t_end; ++t) {
+    }
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
+    const bool bias = wave == 0 && cig == 0;
+    // a tile's groups in registers, from clamped addresses so that all loads are in flight together; bit k of x_in / g_in
+    // tells whether item k lies in the image (zeros are stored otherwise).  Item i of the halo is group i % XC8 of pixel
+    // i / XC8, of the gradient the group that slot i % GC8 of pixel i / GC8 holds.
+    uint4 xv[L::XPT], gv[L::GPT];
+    uint32_t x_in = 0, g_in = 0;
+    auto fetch = [&](int t) __attribute__((always_inline)) {
         const int tx = t % tiles_x, rest = t / tiles_x, ty = rest % tiles_y, n = rest / tiles_y;
-        const int x0 = tx * TW, y0 = ty * R;
-        // Staging, transposed to [channel][pixel] in registers: a thread holds the 8-channel groups of 8 (10)
-        // consecutive pixels and writes, for each of the 8 channels, the 8 pixels as one 16-byte LDS store
-        // (two pixels per 32-bit word); the input's dx-shifted copies come from the same 10 registers.  All
-        // loads of an item are in flight together (clamped addresses, zeros substituted afterwards).
-        constexpr int X_ITEMS = HRW * (TW / 8) * (CIN_T / 8), G_ITEMS = R * (TW / 8) * (COUT / 8);
-        static_assert(X_ITEMS <= 192, "one input item per thread");
-        auto pack_ch = [](const uint4& lo, const uint4& hi, int e) -> uint32_t {
-            const uint32_t wl = e < 2 ? lo.x : e < 4 ? lo.y : e < 6 ? lo.z : lo.w;
-            const uint32_t wh = e < 2 ? hi.x : e < 4 ? hi.y : e < 6 ? hi.z : hi.w;
-            return (e & 1) ? ((wl >> 16) | (wh & 0xFFFF0000u)) : ((wl & 0xFFFFu) | (wh << 16));
-        };
-        uint4 xv[10];
-        int x_c8 = 0, x_q = 0, x_row = 0;
-        const bool x_item = (int)threadIdx.x < X_ITEMS;
-        // consecutive threads take consecutive 8-pixel groups q, so that the 16-byte stores of 8 neighbouring
-        // lanes (one channel row, q = 0..7) cover all LDS banks
-        if (x_item) {
-            x_q = threadIdx.x % (TW / 8);
-            const int rest = threadIdx.x / (TW / 8);
-            x_c8 = rest % (CIN_T / 8);
-            x_row = rest / (CIN_T / 8);
-            const int y = y0 - 1 + x_row, ci = ci0 + 8 * x_c8;
-            const bool rowok = y >= 0 && y < a.H && ci < a.Cin;
-            const int yc = min(max(y, 0), a.H - 1), cic = ci < a.Cin ? ci : 0;
+        const int x0 = tx * WG_TW, y0 = ty * WG_R;
+        x_in = g_in = 0;
 #pragma unroll
-            for (int k = 0; k < 10; ++k) {
-                const int x = x0 - 1 + 8 * x_q + k;
-                const int xc = min(max(x, 0), a.W - 1);
-                const uint4 v = *reinterpret_cast<const uint4*>(a.x + ((size_t)(n * a.H + yc) * a.W + xc) * a.Cin + cic);
-                xv[k] = (rowok && x >= 0 && x < a.W) ? v : make_uint4(0u, 0u, 0u, 0u);
+        for (int k = 0; k < L::XPT; ++k) {
+            const int i = min((int)threadIdx.x + WG_THREADS * k, L::X_ITEMS - 1);
+            const int pix = i / L::XC8, ci = ci0 + 8 * (i - pix * L::XC8);
+            const int row = pix / L::HW, y = y0 - 1 + row, x = x0 - 1 + pix - row * L::HW;
+            const int yc = min(max(y, 0), a.H - 1), xc = min(max(x, 0), a.W - 1);
+            const uint16_t* src;
+            if constexpr (CAT) {
+                const bool up = ci < a.Ca;
+                const size_t ou = ((size_t)(n * (a.H >> 1) + (yc >> 1)) * (a.W >> 1) + (xc >> 1)) * a.Ca + ci;
+                const size_t os = ((size_t)(n * a.H + yc) * a.W + xc) * (a.Cin - a.Ca) + (ci - a.Ca);
+                src = (up ? a.x : a.x2) + (up ? ou : os);
+            } else {
+                src = a.x + ((size_t)(n * a.H + yc) * a.W + xc) * a.Cin + ci;
             }
+            xv[k] = *reinterpret_cast<const uint4*>(src);
+            x_in |= x == xc && y == yc ? 1u << k : 0u;
         }
-        auto g_load = [&](int it, uint4* gv) {
-            const int q = it % (TW / 8), rest = it / (TW / 8), c8 = rest % c8_out, row = rest / c8_out;
-            const int y = y0 + row, yc = min(y, a.H - 1);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int x = x0 + 8 * q + k, xc = min(x, a.W - 1);
-                const uint4 v = *reinterpret_cast<const uint4*>(a.g + ((size_t)(n * a.H + yc) * a.W + xc) * a.Cout + 8 * c8);
-                gv[k] = (y < a.H && x < a.W) ? v : make_uint4(0u, 0u, 0u, 0u);
-            }
-        };
-        auto g_store = [&](int it, const uint4* gv) {
-            const int q = it % (TW / 8), rest = it / (TW / 8), c8 = rest % c8_out, row = rest / c8_out;
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                *reinterpret_cast<uint4*>(gs + (8 * c8 + e) * GS_CO + row * TW + 8 * q) =
-                    make_uint4(pack_ch(gv[0], gv[1], e), pack_ch(gv[2], gv[3], e), pack_ch(gv[4], gv[5], e),
-                               pack_ch(gv[6], gv[7], e));
-        };
-        uint4 gv[8];
-        const bool g_first = (int)threadIdx.x < G_ITEMS;
-        if (g_first) g_load(threadIdx.x, gv);
-        __syncthreads();   // every wave is done with the previous tile's operands
-        if (x_item) {
-#pragma unroll
-            for (int dx = 0; dx < 3; ++dx)
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    *reinterpret_cast<uint4*>(xs + dx * XS_DX + (8 * x_c8 + e) * XS_CI + x_row * TW + 8 * x_q) =
-                        make_uint4(pack_ch(xv[dx], xv[dx + 1], e), pack_ch(xv[dx + 2], xv[dx + 3], e),
-                                   pack_ch(xv[dx + 4], xv[dx + 5], e), pack_ch(xv[dx + 6], xv[dx + 7], e));
+        for (int k = 0; k < L::GPT; ++k) {
+            const int i = min((int)threadIdx.x + WG_THREADS * k, L::G_ITEMS - 1);
+            const int pix = i / L::GC8, slot = i - pix * L::GC8;
+            const int row = pix / WG_TW, px = pix - row * WG_TW, y = y0 + row, x = x0 + px;
+            const int co = co0 + 8 * g_slot<L::GC8>(slot, px);   // the rotation is its own inverse
+            const int yc = min(y, a.H - 1), xc = min(x, a.W - 1);
+            gv[k] = *reinterpret_cast<const uint4*>(a.g + ((size_t)(n * a.H + yc) * a.W + xc) * a.Cout + co);
+            g_in |= x == xc && y == yc ? 1u << k : 0u;
         }
-        if (g_first) g_store(threadIdx.x, gv);
-        for (int it = threadIdx.x + 192; it < G_ITEMS; it += 192) {
-            g_load(it, gv);
-            g_store(it, gv);
+    };
+    // this lane's pixel (of a group of 4) and 4 channels in a transposed read
+    const int q = 4 * g + (r >> 2), c = r & 3;
+    if (SMALL && threadIdx.x == 0) lds[L::X_ITEMS] = make_uint4(0u, 0u, 0u, 0u);
+    if (t_begin < t_end) fetch(t_begin);
+    for (int t = t_begin; t < t_end; ++t) {
+        __syncthreads();   // every wave is done with the previous tile
+#pragma unroll
+        for (int k = 0; k < L::XPT; ++k) {
+            const int i = (int)threadIdx.x + WG_THREADS * k;
+            if (L::X_ITEMS % WG_THREADS == 0 || i < L::X_ITEMS) lds[i] = keep_if(xv[k], (x_in >> k) & 1u);
+        }
+#pragma unroll
+        for (int k = 0; k < L::GPT; ++k) {
+            const int i = (int)threadIdx.x + WG_THREADS * k;
+            if (L::G_ITEMS % WG_THREADS == 0 || i < L::G_ITEMS) lds[L::G_OFF + i] = keep_if(gv[k], (g_in >> k) & 1u);
         }
         __syncthreads();
+        if (t + 1 < t_end) fetch(t + 1);   // under this tile's instructions
 #pragma unroll
-        for (int s = 0; s < R * TW / 32; ++s) {
-            const int row = s / (TW / 32), c0 = 32 * (s % (TW / 32));
+        for (int s = 0; s < WG_R * WG_TW / 32; ++s) {
+            const int row = s / (WG_TW / 32), c0 = 32 * (s % (WG_TW / 32));
             bf16x8 A[CO_T], B[3][CI_T];
 #pragma unroll
             for (int i = 0; i < CO_T; ++i)
-                A[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(
-                                                       gs + (16 * i + r) * GS_CO + row * TW + c0 + 8 * g));
+                A[i] = tr_frag(gs + (row * WG_TW + c0 + q) * GPB + 16 * g_slot<L::GC8>(2 * i + (c >> 1), q) + 8 * (c & 1), 16 * GPB);
 #pragma unroll
             for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
                 for (int j = 0; j < CI_T; ++j)
-                    B[dx][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(
-                                   xs + dx * XS_DX + (16 * j + r) * XS_CI + (row + wave) * TW + c0 + 8 * g));
+                    B[dx][j] = tr_frag(xs + ((row + wave) * L::HW + c0 + dx + q) * XPB + 32 * j + 8 * c, 16 * XPB);
+            if (bias) {
+#pragma unroll
+                for (int i = 0; i < CO_T; ++i) accb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i], ones, accb[i], 0, 0, 0);
+            }
 #pragma unroll
             for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
@@ -952,6 +931,7 @@ __global__ __launch_bounds__(192) void k_wgrad_lds(WgradArgs a, int tiles_per_ch
         }
     }
     // D[i = output channel][j = input channel]: lane holds j = lane & 15, rows 4 (lane >> 4) + e
+    float* out = a.partial + (size_t)blockIdx.x * ((size_t)a.Cout * 9 * a.Cin + a.Cout);
 #pragma unroll
     for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
@@ -960,70 +940,37 @@ __global__ __launch_bounds__(192) void k_wgrad_lds(WgradArgs a, int tiles_per_ch
             for (int j = 0; j < CI_T; ++j) {
                 const int ci = ci0 + 16 * j + r;
                 if (ci >= a.Cin) continue;
-                const int tap = 3 * wave + dx;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int co = 16 * i + 4 * g + e;
-                    a.partial[(((size_t)blockIdx.x * a.Cout + co) * 9 + tap) * a.Cin + ci] = acc[dx][i][j][e];
-                }
+                for (int e = 0; e < 4; ++e)
+                    out[((size_t)(co0 + 16 * i + 4 * g + e) * 9 + 3 * wave + dx) * a.Cin + ci] = acc[dx][i][j][e];
             }
+    if (bias && r == 0) {
+#pragma unroll
+        for (int i = 0; i < CO_T; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) out[(size_t)a.Cout * 9 * a.Cin + co0 + 16 * i + 4 * g + e] = accb[i][e];
+    }
 }
 
-// out[i] (+)= sum over chunks c of partial[c][i]: 16 outputs per workgroup, 16 lanes per output summing
-// chunks q, q + 16, q + 32, ... in order, then a fixed-order tree over the 16 lanes
-__global__ __launch_bounds__(256) void k_reduce_chunks(const float* partial, int n_chunks, int n, float* out, int add)
+// out[i] = sum over chunks c of partial[c][i]: 64 outputs per workgroup (256-byte rows), 16 lanes per output summing
+// chunks q, q + 16, q + 32, ... in order, then a fixed-order tree over the 16
+__global__ __launch_bounds__(1024) void k_reduce_chunks(const float* partial, int n_chunks, int n, float* out)
 {
-    __shared__ float sm[16][17];
-    const int o = threadIdx.x & 15, q = threadIdx.x >> 4;
-    const int i = blockIdx.x * 16 + o;
+    __shared__ float sm[16][64];
+    const int o = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + o;
     float s = 0.0f;
-    if (i < n)
+    if (i < n) {
+#pragma unroll 8
         for (int c = q; c < n_chunks; c += 16) s += partial[(size_t)c * n + i];
+    }
     sm[q][o] = s;
     __syncthreads();
     for (int h = 8; h > 0; h >>= 1) {
         if (q < h) sm[q][o] += sm[q + h][o];
         __syncthreads();
     }
-    if (q == 0 && i < n) out[i] = add ? out[i] + sm[0][o] : sm[0][o];
-}
-
-// Column sums of a bf16 [P][C] tensor (C a multiple of 8, at most 256), per block of COLSUM_ROWS pixels:
-// a thread sums 8 channels over every G-th pixel of the block (G = 2048 / C pixel groups), then the
-// groups are added in a fixed tree order, so the result does not depend on scheduling.
-constexpr int COLSUM_ROWS = 1024;
-__global__ __launch_bounds__(256) void k_colsum(const uint16_t* g, int P, int C, float* partial)
-{
-    __shared__ float sm[8][256];
-    const int cg_n = C / 8, G = 256 / cg_n;
-    const int t = threadIdx.x, cg = t % cg_n, grp = t / cg_n;
-    const int p0 = blockIdx.x * COLSUM_ROWS, pe = min(P, p0 + COLSUM_ROWS);
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (grp < G) {
-        for (int p = p0 + grp; p < pe; p += G) {
-            uint4 v = *reinterpret_cast<const uint4*>(g + (size_t)p * C + 8 * cg);
-            uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                acc[2 * e] += __uint_as_float(w[e] << 16);
-                acc[2 * e + 1] += __uint_as_float(w[e] & 0xFFFF0000u);
-            }
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) sm[e][t] = acc[e];
-    __syncthreads();
-    for (int h = G / 2; h > 0; h >>= 1) {
-        if (grp < h) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) sm[e][t] += sm[e][t + h * cg_n];
-        }
-        __syncthreads();
-    }
-    if (grp == 0) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) partial[(size_t)blockIdx.x * C + 8 * cg + e] = sm[e][t];
-    }
+    if (q == 0 && i < n) out[i] = sm[0][o];
 }
 
 // out[o] (+)= sum over blocks b of partial[b][o], o < n: one workgroup per output, fixed-order tree
@@ -1058,22 +1005,6 @@ __global__ __launch_bounds__(256) void k_pool2(const uint16_t* in, int N, int H,
     int x = (int)(q % w), t = (int)(q / w), y = t % h, n = t / h;
     const uint16_t* b = in + (((size_t)n * H + 2 * y) * W + 2 * x) * C + c;
     st8(out + q * C + c, pool4(ld8(b), ld8(b + C), ld8(b + (size_t)W * C), ld8(b + (size_t)W * C + C)));
-}
-
-// out[N,2h,2w,Ca+Cs] = [nearest-upsampled a (Ca channels), skip (Cs channels)]
-__global__ __launch_bounds__(256) void k_up2_concat(const uint16_t* a, const uint16_t* skip, int N, int H, int W,
-                                                    int Ca, int Cs, uint16_t* out)
-{
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int C = Ca + Cs, C8 = C / 8;
-    size_t total = (size_t)N * H * W * C8;
-    if (i >= total) return;
-    int c = (int)(i % C8) * 8;
-    size_t q = i / C8;
-    int x = (int)(q % W), t = (int)(q / W), y = t % H, n = t / H;
-    uint4 v = c < Ca ? ld8(a + (((size_t)n * (H / 2) + y / 2) * (W / 2) + x / 2) * Ca + c)
-                     : ld8(skip + q * Cs + (c - Ca));
-    st8(out + q * C + c, v);
 }
 
 // gradient of the upsampled part of a concat: out[n,y,x,c] = mask * sum_{2x2} g[n,2y+a,2x+b, c0 + c]
@@ -1322,60 +1253,54 @@ void unet_conv3x3_direct(const ConvArgs& a, hipStream_t st)
     }
 }
 
-int unet_wgrad_chunks(size_t P, int chunk) { return (int)((P + chunk - 1) / chunk); }
-
-void unet_wgrad(const WgradArgs& a, hipStream_t st)
-{
-    size_t P = (size_t)a.N * a.H * a.W;
-    int chunks = unet_wgrad_chunks(P, a.chunk);
-    dim3 grid(chunks, 9, (a.Cout / 16) * ((a.Cin + 15) / 16));
-    hipLaunchKernelGGL(k_wgrad, grid, dim3(64), 0, st, a);
-}
-
 namespace {
+// channels per workgroup: 32 x 32 (32 x 48 of the 96-channel input), 64 x 32 beyond; chunks so that the workgroups of
+// all channel groups fill the 256 CUs once at the 3 (32 output channels) or 2 that LDS admits on each
 struct WgradShape {
-    int co_t, ci_t, ci_groups, tiles_per_chunk, chunks;
+    int co_t, ci_t, groups, ci_groups, tiles_per_chunk, chunks;
 };
 WgradShape wgrad_shape(const WgradArgs& a)
 {
     WgradShape w;
-    w.co_t = a.Cout / 16;
-    w.ci_t = w.co_t >= 8 ? 1 : (a.Cin <= 16 ? 1 : 2);
+    w.co_t = a.Cout >= 64 ? 4 : 2;
+    w.ci_t = a.Cin <= 16 ? 1 : (w.co_t == 2 && a.Cin % 48 == 0 ? 3 : 2);
     w.ci_groups = (a.Cin + 16 * w.ci_t - 1) / (16 * w.ci_t);
+    w.groups = w.ci_groups * (a.Cout / (16 * w.co_t));
     const int tiles = a.N * ((a.H + WG_R - 1) / WG_R) * ((a.W + WG_TW - 1) / WG_TW);
-    const int target = std::max(1, 1024 / w.ci_groups);
+    const int target = std::max(1, (w.co_t == 2 && w.ci_t < 3 ? 768 : 512) / w.groups);
     w.tiles_per_chunk = std::max(1, (tiles + target - 1) / target);
     w.chunks = (tiles + w.tiles_per_chunk - 1) / w.tiles_per_chunk;
     return w;
 }
+template <int CO_T, int CI_T, bool SMALL, bool CAT, int OCC>
+void launch_wgrad(const WgradArgs& a, const WgradShape& w, hipStream_t st)
+{
+    hipLaunchKernelGGL((k_wgrad<CO_T, CI_T, SMALL, CAT, OCC>), dim3(w.chunks, w.groups), dim3(WG_THREADS), 0, st, a,
+                       w.tiles_per_chunk, w.ci_groups);
+}
 }  // namespace
 
-int unet_wgrad_lds_chunks(const WgradArgs& a) { return wgrad_shape(a).chunks; }
+int unet_wgrad_chunks(const WgradArgs& a) { return wgrad_shape(a).chunks; }
 
-bool unet_wgrad_lds(const WgradArgs& a, hipStream_t st)
+void unet_wgrad(const WgradArgs& a, hipStream_t st)
 {
     const WgradShape w = wgrad_shape(a);
-    const size_t lds = ((size_t)16 * w.co_t * (WG_R * WG_TW + 8) + (size_t)3 * 16 * w.ci_t * ((WG_R + 2) * WG_TW + 8)) * 2;
-    const dim3 grid(w.chunks, w.ci_groups);
+    const bool cat = a.x2 != nullptr;
     switch (w.co_t * 10 + w.ci_t) {
-    case 21: hipLaunchKernelGGL((k_wgrad_lds<2, 1>), grid, dim3(192), lds, st, a, w.tiles_per_chunk); return true;
-    case 22: hipLaunchKernelGGL((k_wgrad_lds<2, 2>), grid, dim3(192), lds, st, a, w.tiles_per_chunk); return true;
-    case 42: hipLaunchKernelGGL((k_wgrad_lds<4, 2>), grid, dim3(192), lds, st, a, w.tiles_per_chunk); return true;
-    case 81: hipLaunchKernelGGL((k_wgrad_lds<8, 1>), grid, dim3(192), lds, st, a, w.tiles_per_chunk); return true;
-    default: return false;
+    case 21: launch_wgrad<2, 1, true, false, 4>(a, w, st); break;     // the 8-channel first layer
+    case 22: launch_wgrad<2, 2, false, false, 3>(a, w, st); break;
+    case 23: launch_wgrad<2, 3, false, true, 2>(a, w, st); break;      // the 96-channel concatenation
+    case 42:
+        if (cat) launch_wgrad<4, 2, false, true, 2>(a, w, st);
+        else launch_wgrad<4, 2, false, false, 2>(a, w, st);
+        break;
+    default: break;   // channel counts of this network only
     }
 }
 
-void unet_reduce_chunks(const float* partial, int n_chunks, int n, float* out, int add, hipStream_t st)
+void unet_reduce_chunks(const float* partial, int n_chunks, int n, float* out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_reduce_chunks, dim3(nb(n, 16)), dim3(256), 0, st, partial, n_chunks, n, out, add);
-}
-
-int unet_colsum_blocks(int P) { return (P + COLSUM_ROWS - 1) / COLSUM_ROWS; }
-
-void unet_colsum(const uint16_t* g, int P, int C, float* partial, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_colsum, dim3(unet_colsum_blocks(P)), dim3(256), 0, st, g, P, C, partial);
+    hipLaunchKernelGGL(k_reduce_chunks, dim3(nb(n, 64)), dim3(1024), 0, st, partial, n_chunks, n, out);
 }
 
 void unet_reduce_blocks(const float* partial, int n_blocks, int n, float* out, int add, hipStream_t st)
@@ -1387,13 +1312,6 @@ void unet_pool2(const uint16_t* in, int N, int H, int W, int C, uint16_t* out, h
 {
     size_t n = (size_t)N * (H / 2) * (W / 2) * (C / 8);
     hipLaunchKernelGGL(k_pool2, dim3(nb(n, 256)), dim3(256), 0, st, in, N, H, W, C, out);
-}
-
-void unet_up2_concat(const uint16_t* a, const uint16_t* skip, int N, int H, int W, int Ca, int Cs, uint16_t* out,
-                     hipStream_t st)
-{
-    size_t n = (size_t)N * H * W * ((Ca + Cs) / 8);
-    hipLaunchKernelGGL(k_up2_concat, dim3(nb(n, 256)), dim3(256), 0, st, a, skip, N, H, W, Ca, Cs, out);
 }
 
 void unet_up_back_mask(const uint16_t* g, int N, int H2, int W2, int Ctot, int c0, int C, const uint16_t* mask,

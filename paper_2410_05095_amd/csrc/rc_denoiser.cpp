@@ -70,7 +70,7 @@ struct rc_denoiser {
     size_t partial_cap = 0;
     float* d_sums = nullptr;
     // activation offsets (elements) within act / grad
-    size_t a_e1a, a_e1b, a_p1, a_e2a, a_e2b, a_p2, a_bna, a_bnb, a_u2, a_d2a, a_d2b, a_u1, a_d1a, a_d1b, a_total;
+    size_t a_e1a, a_e1b, a_p1, a_e2a, a_e2b, a_p2, a_bna, a_bnb, a_d2a, a_d2b, a_d1a, a_d1b, a_total;
     size_t g_d1b, g_d1a, g_u1, g_d2b, g_d2a, g_u2, g_bnb, g_bna, g_p2, g_e2b, g_e2a, g_p1, g_e1b, g_e1a, g_total;
     // FP32 copy of the forward pass: transposed FP32 weights and an FP32 activation workspace
     float* d_wt32 = nullptr;
@@ -106,8 +106,8 @@ int ensure_workspace(rc_denoiser* d, int n, int h, int w)
     auto take = [&](size_t elems) { size_t r = o; o += (elems + 63) & ~size_t(63); return r; };
     d->a_e1a = take(P * 32); d->a_e1b = take(P * 32); d->a_p1 = take(P2 * 32);
     d->a_e2a = take(P2 * 64); d->a_e2b = take(P2 * 64); d->a_p2 = take(P4 * 64);
-    d->a_bna = take(P4 * 128); d->a_bnb = take(P4 * 128); d->a_u2 = take(P2 * 192);
-    d->a_d2a = take(P2 * 64); d->a_d2b = take(P2 * 64); d->a_u1 = take(P * 96);
+    d->a_bna = take(P4 * 128); d->a_bnb = take(P4 * 128);
+    d->a_d2a = take(P2 * 64); d->a_d2b = take(P2 * 64);
     d->a_d1a = take(P * 32); d->a_d1b = take(P * 32);
     d->a_total = o;
     o = 0;
@@ -202,31 +202,28 @@ void conv_back_data(rc_denoiser* d, const uint16_t* g, int n, int h, int w, int 
     unet_conv3x3(a, st);
 }
 
-// dW and db of layer l from its input x and pre-activation gradient g, written into d_g
-void conv_back_weights(rc_denoiser* d, const uint16_t* x, const uint16_t* g, int n, int h, int w, int l, hipStream_t st)
+WgradArgs wgrad_args(int n, int h, int w, int l)
 {
-    size_t P = (size_t)n * h * w;
-    int chunk = chunk_for(P);
-    int chunks = unet_wgrad_chunks(P, chunk);
-    WgradArgs a;
-    a.x = x; a.g = g; a.N = n; a.H = h; a.W = w; a.Cin = LAYERS[l].cin; a.Cout = LAYERS[l].cout;
-    a.chunk = chunk;
-    a.partial = d->d_partial;
-    if (unet_wgrad_lds(a, st)) {
-        unet_reduce_chunks(d->d_partial, unet_wgrad_lds_chunks(a), (int)layer_w(l), d->d_g + d->off_w[l], 0, st);
-    } else {
-        unet_wgrad(a, st);
-        unet_reduce_chunks(d->d_partial, chunks, (int)layer_w(l), d->d_g + d->off_w[l], 0, st);
-    }
-    unet_colsum(g, (int)P, LAYERS[l].cout, d->d_partial, st);
-    unet_reduce_blocks(d->d_partial, unet_colsum_blocks((int)P), LAYERS[l].cout, d->d_g + d->off_b[l], 0, st);
+    WgradArgs a = {};
+    a.N = n; a.H = h; a.W = w; a.Cin = LAYERS[l].cin; a.Cout = LAYERS[l].cout;
+    return a;
 }
 
-// keep_concat: also materialise the decoder's concatenated inputs (the weight gradients read them).
+// dW and db of layer l from its input x (with `skip`: [2x nearest-upsampled x (Ca channels), skip]) and
+// pre-activation gradient g, written into d_g (the bias gradients follow the weights')
+void conv_back_weights(rc_denoiser* d, const uint16_t* x, const uint16_t* g, int n, int h, int w, int l, hipStream_t st,
+                       const uint16_t* skip = nullptr, int Ca = 0)
+{
+    WgradArgs a = wgrad_args(n, h, w, l);
+    a.x = x; a.x2 = skip; a.Ca = Ca; a.g = g;
+    a.partial = d->d_partial;
+    unet_wgrad(a, st);
+    unet_reduce_chunks(d->d_partial, unet_wgrad_chunks(a), (int)layer_w(l) + LAYERS[l].cout, d->d_g + d->off_w[l], st);
+}
+
 // y_out (inference): the head is computed in the last convolution's epilogue and written there, and the
 // last layer's activations are not stored; otherwise they are, and the head writes d_y.
-int forward(rc_denoiser* d, const uint16_t* x, int n, int h, int w, hipStream_t st, bool keep_concat,
-            float* y_out = nullptr)
+int forward(rc_denoiser* d, const uint16_t* x, int n, int h, int w, hipStream_t st, float* y_out = nullptr)
 {
     int st_ = ensure_workspace(d, n, h, w);
     if (st_ != RC_OK) return st_;
@@ -238,10 +235,8 @@ int forward(rc_denoiser* d, const uint16_t* x, int n, int h, int w, hipStream_t 
     conv(d, A + d->a_e2a, n, h2, w2, E2B, A + d->a_e2b, st, nullptr, 0, A + d->a_p2);
     conv(d, A + d->a_p2, n, h4, w4, BNA, A + d->a_bna, st);
     conv(d, A + d->a_bna, n, h4, w4, BNB, A + d->a_bnb, st);
-    if (keep_concat) unet_up2_concat(A + d->a_bnb, A + d->a_e2b, n, h2, w2, 128, 64, A + d->a_u2, st);
     conv(d, A + d->a_bnb, n, h2, w2, D2A, A + d->a_d2a, st, A + d->a_e2b, 128);
     conv(d, A + d->a_d2a, n, h2, w2, D2B, A + d->a_d2b, st);
-    if (keep_concat) unet_up2_concat(A + d->a_d2b, A + d->a_e1b, n, h, w, 64, 32, A + d->a_u1, st);
     conv(d, A + d->a_d2b, n, h, w, D1A, A + d->a_d1a, st, A + d->a_e1b, 64);
     if (y_out) {
         conv(d, A + d->a_d1a, n, h, w, D1B, nullptr, st, nullptr, 0, nullptr, y_out);
@@ -304,17 +299,12 @@ int backward(rc_denoiser* d, const uint16_t* x, const float* t, const float* m, 
     size_t P = (size_t)n * h * w;
     int h2 = h / 2, w2 = w / 2, h4 = h / 4, w4 = w / 4;
     int chunk = chunk_for(P);
-    int chunks = unet_wgrad_chunks(P, chunk);
-    size_t need = 0;
+    const int chunks = (int)((P + chunk - 1) / chunk);   // of the loss
+    size_t need = (size_t)chunks * 2;
     for (int l = 0; l < N_LAYERS; ++l) {
-        need = std::max(need, (size_t)chunks * layer_w(l));
         const int s = (l == E1A || l == E1B || l == D1A || l == D1B) ? 1 : (l == BNA || l == BNB ? 4 : 2);
-        WgradArgs q = {};
-        q.N = n; q.H = h / s; q.W = w / s; q.Cin = LAYERS[l].cin; q.Cout = LAYERS[l].cout;
-        need = std::max(need, (size_t)unet_wgrad_lds_chunks(q) * layer_w(l));
+        need = std::max(need, (size_t)unet_wgrad_chunks(wgrad_args(n, h / s, w / s, l)) * (layer_w(l) + LAYERS[l].cout));
     }
-    need = std::max(need, (size_t)chunks * 64);
-    need = std::max(need, (size_t)unet_colsum_blocks((int)P) * 128);
     need = std::max(need, (size_t)unet_head_blocks((int)P) * 33);
     int st_ = ensure_partial(d, need);
     if (st_ != RC_OK) return st_;
@@ -327,13 +317,13 @@ int backward(rc_denoiser* d, const uint16_t* x, const float* t, const float* m, 
     // decoder level 1
     conv_back_weights(d, A + d->a_d1a, G + d->g_d1b, n, h, w, D1B, st);
     conv_back_data(d, G + d->g_d1b, n, h, w, D1B, A + d->a_d1a, G + d->g_d1a, st);
-    conv_back_weights(d, A + d->a_u1, G + d->g_d1a, n, h, w, D1A, st);
+    conv_back_weights(d, A + d->a_d2b, G + d->g_d1a, n, h, w, D1A, st, A + d->a_e1b, 64);
     conv_back_data(d, G + d->g_d1a, n, h, w, D1A, nullptr, G + d->g_u1, st);
     unet_up_back_mask(G + d->g_u1, n, h, w, 96, 0, 64, A + d->a_d2b, G + d->g_d2b, st);
     // decoder level 2
     conv_back_weights(d, A + d->a_d2a, G + d->g_d2b, n, h2, w2, D2B, st);
     conv_back_data(d, G + d->g_d2b, n, h2, w2, D2B, A + d->a_d2a, G + d->g_d2a, st);
-    conv_back_weights(d, A + d->a_u2, G + d->g_d2a, n, h2, w2, D2A, st);
+    conv_back_weights(d, A + d->a_bnb, G + d->g_d2a, n, h2, w2, D2A, st, A + d->a_e2b, 128);
     conv_back_data(d, G + d->g_d2a, n, h2, w2, D2A, nullptr, G + d->g_u2, st);
     unet_up_back_mask(G + d->g_u2, n, h2, w2, 192, 0, 128, A + d->a_bnb, G + d->g_bnb, st);
     // bottleneck
@@ -481,7 +471,7 @@ int rc_denoiser_infer(rc_ctx* c, rc_denoiser* d, const uint16_t* d_feat, uint32_
     DN_HIP(hipSetDevice(d->device));
     hipStream_t s = ctx_stream(c);
     if (reinterpret_cast<uintptr_t>(d_out) & 3u) return RC_ERR_INVALID_ARG;
-    return forward(d, d_feat, (int)n, (int)h, (int)w, s, false, d_out);
+    return forward(d, d_feat, (int)n, (int)h, (int)w, s, d_out);
 }
 
 int rc_denoiser_infer_fp32(rc_ctx* c, rc_denoiser* d, const uint16_t* d_feat, uint32_t n, uint32_t h, uint32_t w,
@@ -503,7 +493,7 @@ int rc_denoiser_train_step(rc_ctx* c, rc_denoiser* d, const uint16_t* d_feat, co
     if (reinterpret_cast<uintptr_t>(d_feat) & 15u) return RC_ERR_INVALID_ARG;
     DN_HIP(hipSetDevice(d->device));
     hipStream_t s = ctx_stream(c);
-    int st = forward(d, d_feat, (int)n, (int)h, (int)w, s, true);
+    int st = forward(d, d_feat, (int)n, (int)h, (int)w, s);
     if (st == RC_OK) st = backward(d, d_feat, d_target, d_mask, (int)n, (int)h, (int)w, s);
     if (st != RC_OK) return st;
     d->step++;

@@ -35,31 +35,24 @@ struct ConvArgsF32 {
 };
 
 struct WgradArgs {
-    const uint16_t* x;      // layer input NHWC [Cin]
+    const uint16_t* x;      // layer input NHWC [Cin]; with x2: N x H/2 x W/2 x Ca, its channels [0, Ca) upsampled 2x
+    const uint16_t* x2;     // optional second source N x H x W x (Cin - Ca), as ConvArgs.in2
+    int Ca;
     const uint16_t* g;      // gradient of the pre-activation NHWC [Cout]
     int N, H, W, Cin, Cout;
-    int chunk;              // pixels per split-K chunk (multiple of 32)
-    float* partial;         // [chunks][Cout][9][Cin]
+    float* partial;         // [chunks][Cout][9][Cin] weight, then [Cout] bias gradients of each chunk
 };
 
 // LDS-tiled kernel for the channel counts of this network (any in2); unet_conv3x3_direct: the direct
 // kernel without LDS staging (no second source)
 void unet_conv3x3(const ConvArgs& a, hipStream_t st);
 void unet_conv3x3_direct(const ConvArgs& a, hipStream_t st);
-int unet_wgrad_chunks(size_t P, int chunk);
-// LDS-tiled weight gradient: partial sums per chunk of pixel tiles ([chunks][Cout][9][Cin], `chunk`
-// unused); returns false for channel counts it has no instance for
-int unet_wgrad_lds_chunks(const WgradArgs& a);
-bool unet_wgrad_lds(const WgradArgs& a, hipStream_t st);
+// weight and bias gradients: partial sums per chunk of pixel tiles, then their sum in chunk order
+int unet_wgrad_chunks(const WgradArgs& a);
 void unet_wgrad(const WgradArgs& a, hipStream_t st);
-void unet_reduce_chunks(const float* partial, int n_chunks, int n, float* out, int add, hipStream_t st);
-// bias gradients: per-block column sums, then a fixed-order reduction over the blocks
-int unet_colsum_blocks(int P);
-void unet_colsum(const uint16_t* g, int P, int C, float* partial, hipStream_t st);
+void unet_reduce_chunks(const float* partial, int n_chunks, int n, float* out, hipStream_t st);
 void unet_reduce_blocks(const float* partial, int n_blocks, int n, float* out, int add, hipStream_t st);
 void unet_pool2(const uint16_t* in, int N, int H, int W, int C, uint16_t* out, hipStream_t st);
-void unet_up2_concat(const uint16_t* a, const uint16_t* skip, int N, int H, int W, int Ca, int Cs, uint16_t* out,
-                     hipStream_t st);
 void unet_up_back_mask(const uint16_t* g, int N, int H2, int W2, int Ctot, int c0, int C, const uint16_t* mask,
                        uint16_t* out, hipStream_t st);
 void unet_pool_back_add_mask(const uint16_t* gpool, const uint16_t* gcat, int N, int H, int W, int C, int Ctot, int c0,
