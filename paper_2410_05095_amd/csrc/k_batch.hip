@@ -60,11 +60,11 @@ __device__ inline bool rc_batch_pixel(const DevView& V, const BatchTune& t, uint
 }
 
 // Register budgets of the one-stage kernels (64 views, three-kernel form): the camera-ray kernel at 6 waves per
-// SIMD (80 registers) 3.74 against 4.21 ms at its natural 104; the shadow-ray kernel, whose FP64 surface
+// SIMD (80 registers) 3.74 against 4.21 ms at its natural 104 (both with 40 bytes spilled, 12 since); the shadow-ray kernel, whose FP64 surface
 // reconstruction moved to k_batch_setup, at 5 (96 registers) 4.91 ms with the setup, against 5.46 at 4 and
 // 5.47 at 6 waves.  The camera kernel at 5 waves (3.79 ms) and the shading kernel held to 5 or 6 waves (1.05,
 // 1.42 against 0.66 ms at its natural 128 registers) were slower.
-template <int PASS>
+template <int PASS, bool COUNT>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(PASS == 1 ? 6 : PASS == 2 ? 5 : 1)))
 void k_batch(BatchParams P)
 {
@@ -98,7 +98,7 @@ void k_batch(BatchParams P)
                                  uint32_t& rays_cast, int& state) __attribute__((always_inline)) {
         rc_camera_ray(cam, px, k, ray.o, ray.d);
         trav_begin(ray, ts);
-        ++rays_cast;
+        if constexpr (COUNT) ++rays_cast;
         state = 1;
     };
     auto start_sample = [&]() __attribute__((always_inline)) {
@@ -113,7 +113,7 @@ void k_batch(BatchParams P)
         while (j < n_l) {
             if (rc_shadow_ray(lights + 6 * (size_t)j, nullptr, nullptr, false, px, j, 0u, 0u, 0u, os, nf, ray)) {
                 trav_begin(ray, ts);
-                ++rays_cast;
+                if constexpr (COUNT) ++rays_cast;
                 state = 2;
                 return true;
             }
@@ -300,7 +300,7 @@ void k_batch(BatchParams P)
             // rays alone: 8 and 2 (5.34 against 5.47 ms for 3 and 1, 16 and 4 in between)
             constexpr int NODE_STEPS = PASS == 0 ? 16 : PASS == 1 ? 3 : 8;
             constexpr int LEAF_STEPS = PASS == 0 ? 4 : PASS == 1 ? 1 : 2;
-            trav_advance<false, false, NODE_STEPS, LEAF_STEPS>(sc, ray, ts, st, state != 0, state == 2, occluded,
+            trav_advance<false, false, NODE_STEPS, LEAF_STEPS, COUNT, true>(sc, ray, ts, st, state != 0, state == 2, occluded,
                                                                node_visits, tri_tests);
             if (state != 0 && ts.cur == RC_STACK_EMPTY) end_ray(occluded != 0u);
             uint32_t n_act = (uint32_t)__popcll(__ballot(state != 0));
@@ -309,7 +309,7 @@ void k_batch(BatchParams P)
         }
     }
 
-    if (P.w.ray_count) {
+    if constexpr (COUNT) {
         unsigned long long cnt[3] = {rays_cast, node_visits, tri_tests};
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
@@ -436,11 +436,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
 static const void* batch_kernel(int pass)
 {
     switch (pass) {
-    case 1: return reinterpret_cast<const void*>(&k_batch<1>);
-    case 2: return reinterpret_cast<const void*>(&k_batch<2>);
-    case 3: return reinterpret_cast<const void*>(&k_batch<3>);
+    case 1: return reinterpret_cast<const void*>(&k_batch<1, false>);
+    case 2: return reinterpret_cast<const void*>(&k_batch<2, false>);
+    case 3: return reinterpret_cast<const void*>(&k_batch<3, false>);
     case 4: return reinterpret_cast<const void*>(&k_batch_wave<true, false>);
-    default: return reinterpret_cast<const void*>(&k_batch<0>);
+    default: return reinterpret_cast<const void*>(&k_batch<0, false>);
     }
 }
 
@@ -458,17 +458,23 @@ void rc_launch_batch(const BatchParams& P, int pass, int grid, hipStream_t st)
 {
     const size_t lds = pass == 3 ? 0 : TravStack<SL, BLOCK, true>::lds_bytes();
     if (grid < (int)RC_XCDS) grid = RC_XCDS;   // every XCD share of the queue needs workgroups
+#define RC_BATCH(PASS_)                                                                                          \
+    do {                                                                                                         \
+        if (P.w.ray_count) hipLaunchKernelGGL((k_batch<PASS_, true>), dim3(grid), dim3(BLOCK), lds, st, P);      \
+        else hipLaunchKernelGGL((k_batch<PASS_, false>), dim3(grid), dim3(BLOCK), lds, st, P);                   \
+    } while (0)
     switch (pass) {
-    case 1: hipLaunchKernelGGL(k_batch<1>, dim3(grid), dim3(BLOCK), lds, st, P); break;
+    case 1: RC_BATCH(1); break;
     case 2:
         hipLaunchKernelGGL(k_batch_setup, dim3((P.n_items + 255) / 256), dim3(256), 0, st, P);
-        if (P.wave == 0) hipLaunchKernelGGL(k_batch<2>, dim3(grid), dim3(BLOCK), lds, st, P);
+        if (P.wave == 0) RC_BATCH(2);
         else if (P.wave == 1 && !P.w.ray_count) hipLaunchKernelGGL((k_batch_wave<false, false>), dim3(grid), dim3(BLOCK), 0, st, P);
         else if (P.wave == 1) hipLaunchKernelGGL((k_batch_wave<false, true>), dim3(grid), dim3(BLOCK), 0, st, P);
         else if (!P.w.ray_count) hipLaunchKernelGGL((k_batch_wave<true, false>), dim3(grid), dim3(BLOCK), 0, st, P);
         else hipLaunchKernelGGL((k_batch_wave<true, true>), dim3(grid), dim3(BLOCK), 0, st, P);
         break;
-    case 3: hipLaunchKernelGGL(k_batch<3>, dim3(grid), dim3(BLOCK), lds, st, P); break;
-    default: hipLaunchKernelGGL(k_batch<0>, dim3(grid), dim3(BLOCK), lds, st, P); break;
+    case 3: RC_BATCH(3); break;
+    default: RC_BATCH(0); break;
     }
+#undef RC_BATCH
 }

@@ -53,7 +53,7 @@ inline uint32_t claim_size(uint64_t n_work, int grid, uint32_t per_wave, uint32_
 
 // The flat-tree camera-ray instance is compiled for 6 waves per SIMD (at most 80 registers; 5 waves otherwise),
 // which measured 3% faster (0.701 vs 0.724 ms for 1080p camera rays on 7.3M triangles).
-template <int MODE, bool TWO, bool WT>
+template <int MODE, bool TWO, bool WT, bool COUNT>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE == MODE_PRIMARY && !TWO && !WT ? 6 : 1))) void k_trace(KParams P)
 {
     constexpr bool ANY = MODE != MODE_PRIMARY;
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE == M
             if (rc_shadow_ray(P.L.point[j], P.L.rect, P.nL, false, px, j, P.L.area_stream, P.cam.seed, P.cam.frame, os, nf,
                               ray)) {
                 trav_begin(ray, ts, root, twp);
-                ++rays_cast;
+                if constexpr (COUNT) ++rays_cast;
                 return true;
             }
             j += groups;
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE == M
         if (MODE == MODE_PRIMARY) {
             rc_camera_ray(P.cam, px, pk, ray.o, ray.d);
             trav_begin(ray, ts, root, twp);
-            ++rays_cast;
+            if constexpr (COUNT) ++rays_cast;
             return true;
         } else {
             // origin and normal from the setup pass (the FP64 reconstruction stays out of this kernel)
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE == M
         // ---- traversal: node phase then leaf phase for all busy lanes, until enough lanes are idle
         for (;;) {
             uint32_t occluded = 0u;
-            trav_advance<TWO, WT, 3, 1>(sc, ray, ts, st, state == 1, ANY, occluded, node_visits, tri_tests, twp);
+            trav_advance<TWO, WT, 3, 1, COUNT>(sc, ray, ts, st, state == 1, ANY, occluded, node_visits, tri_tests, twp);
             if (state == 1 && ts.cur == RC_STACK_EMPTY) {
                 if (!end_ray(occluded != 0u)) state = 0;
             }
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE == M
         }
     }
 
-    if (P.w.ray_count) {
+    if constexpr (COUNT) {
         unsigned long long cnt[3] = {rays_cast, node_visits, tri_tests};
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE == M
 // together: its lanes start from the same point towards nearby targets and mostly fetch the same
 // nodes.  A wave claims 64 ray slots at a time, advances them to completion, and adds the visible
 // count of each pixel segment (ballot + popcount) to a per-pixel counter.
-template <bool TWO, bool WT>
+template <bool TWO, bool WT, bool COUNT>
 __global__ __launch_bounds__(BLOCK) void k_rect_packets(KParams P, uint32_t* counts)
 {
     const int tid = threadIdx.x;
@@ -246,13 +246,13 @@ __global__ __launch_bounds__(BLOCK) void k_rect_packets(KParams P, uint32_t* cou
                                      P.cam.frame, os, nf, ray);
                 if (busy) {
                     trav_begin(ray, ts, TWO ? sc.tlas_root : 0u, twp);
-                    ++rays_cast;
+                    if constexpr (COUNT) ++rays_cast;
                 }
             }
         }
         uint32_t occluded = 0u;
         while (__ballot(busy && ts.cur != RC_STACK_EMPTY) != 0)
-            trav_advance<TWO, WT, 3, 1>(sc, ray, ts, st, busy, true, occluded, node_visits, tri_tests, twp);
+            trav_advance<TWO, WT, 3, 1, COUNT>(sc, ray, ts, st, busy, true, occluded, node_visits, tri_tests, twp);
         const uint64_t vis = __ballot(busy && occluded == 0u);
         if (in_image && (lane == 0 || k == 0)) {
             uint32_t end = (uint32_t)min<uint64_t>(64, lane + (N - k));
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(BLOCK) void k_rect_packets(KParams P, uint32_t* cou
             if (c) atomicAdd(counts + px, c);
         }
     }
-    if (P.w.ray_count) {
+    if constexpr (COUNT) {
         unsigned long long cnt[3] = {rays_cast, node_visits, tri_tests};
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
@@ -503,7 +503,7 @@ __global__ __launch_bounds__(BLOCK) void k_primary_wave(KParams P)
                     float ny = ray.inv[1] >= 0.0f ? ly[c] : hy[c], fy = ray.inv[1] >= 0.0f ? hy[c] : ly[c];
                     float nz = ray.inv[2] >= 0.0f ? lz[c] : hz[c], fz = ray.inv[2] >= 0.0f ? hz[c] : lz[c];
                     float t0;
-                    const bool hit = rc_slab(ray, nx, ny, nz, fx, fy, fz, best_t, t0);
+                    const bool hit = rc_slab(ray, ray.invf, nx, ny, nz, fx, fy, fz, best_t, t0);
                     uint64_t m = __ballot(hit);
                     uint32_t k = KEY_MISS;
                     if (m != 0) {
@@ -633,9 +633,9 @@ int blocks_per_cu(const void* kernel, size_t lds)
 int rc_trace_grid(int device)
 {
     const int blocks[] = {
-        blocks_per_cu(reinterpret_cast<const void*>(&k_trace<MODE_PRIMARY, false, false>), lds_bytes<MODE_PRIMARY>()),
-        blocks_per_cu(reinterpret_cast<const void*>(&k_trace<MODE_POINT, false, false>), lds_bytes<MODE_POINT>()),
-        blocks_per_cu(reinterpret_cast<const void*>(&k_rect_packets<false, false>), TravStack<SL, BLOCK, false>::lds_bytes()),
+        blocks_per_cu(reinterpret_cast<const void*>(&k_trace<MODE_PRIMARY, false, false, false>), lds_bytes<MODE_PRIMARY>()),
+        blocks_per_cu(reinterpret_cast<const void*>(&k_trace<MODE_POINT, false, false, false>), lds_bytes<MODE_POINT>()),
+        blocks_per_cu(reinterpret_cast<const void*>(&k_rect_packets<false, false, false>), TravStack<SL, BLOCK, false>::lds_bytes()),
         blocks_per_cu(reinterpret_cast<const void*>(&k_rect_wave<false, false, false, false>), 0),
         blocks_per_cu(reinterpret_cast<const void*>(&k_primary_wave<false>), 0),
         blocks_per_cu(reinterpret_cast<const void*>(&k_point_wave<false, false, false, false>), 0)};
@@ -666,7 +666,10 @@ void rc_launch_primary(const DevScene& sc, const DevCamera& cam, uint4* gbuf, co
             hipLaunchKernelGGL(k_primary_wave<false>, dim3(grid), dim3(BLOCK), 0, st, P);
     } else {
         P.claim = claim_size(P.n_items, grid, 16, 32, 128);
-        RC_LAUNCH_TW((k_trace<MODE_PRIMARY, RC_TWO, RC_WT>), dim3(grid), dim3(BLOCK), lds_bytes<MODE_PRIMARY>(), st, P);
+        if (w.ray_count)
+            RC_LAUNCH_TW((k_trace<MODE_PRIMARY, RC_TWO, RC_WT, true>), dim3(grid), dim3(BLOCK), lds_bytes<MODE_PRIMARY>(), st, P);
+        else
+            RC_LAUNCH_TW((k_trace<MODE_PRIMARY, RC_TWO, RC_WT, false>), dim3(grid), dim3(BLOCK), lds_bytes<MODE_PRIMARY>(), st, P);
     }
 }
 
@@ -684,7 +687,7 @@ void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights&
     P.w = w;
     P.n_items = rc_n_items(cam.width, cam.height, cam.ssaa);
     const bool two = sc.inst != nullptr, wt = sc.watertight != 0u;
-    const bool count = w.ray_count != nullptr;   // the wave kernels count visits only when asked
+    const bool count = w.ray_count != nullptr;   // visits are counted only when asked
     // the wave-uniform kernels address nodes and triangles by 32-bit byte offsets and hold at most 128 stack
     // entries; they read each sample's shadow-ray origin and normal from `setup`
     const bool wave_ok = kernels != RC_KERNELS_LANE && rc_wave_ok(sc);
@@ -736,7 +739,10 @@ void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights&
             }
         } else {
             P.claim = claim_size((uint64_t)P.n_items * P.light_groups, grid, 16, 32, 128);
-            RC_LAUNCH_TW((k_trace<MODE_POINT, RC_TWO, RC_WT>), dim3(grid), dim3(BLOCK), lds_bytes<MODE_POINT>(), st, P);
+            if (count)
+                RC_LAUNCH_TW((k_trace<MODE_POINT, RC_TWO, RC_WT, true>), dim3(grid), dim3(BLOCK), lds_bytes<MODE_POINT>(), st, P);
+            else
+                RC_LAUNCH_TW((k_trace<MODE_POINT, RC_TWO, RC_WT, false>), dim3(grid), dim3(BLOCK), lds_bytes<MODE_POINT>(), st, P);
         }
     }
     if (L.has_rect) {
@@ -770,7 +776,10 @@ void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights&
             }
         } else {
             const size_t lds = TravStack<SL, BLOCK, false>::lds_bytes();
-            RC_LAUNCH_TW((k_rect_packets<RC_TWO, RC_WT>), dim3(grid), dim3(BLOCK), lds, st, P, counts);
+            if (count)
+                RC_LAUNCH_TW((k_rect_packets<RC_TWO, RC_WT, true>), dim3(grid), dim3(BLOCK), lds, st, P, counts);
+            else
+                RC_LAUNCH_TW((k_rect_packets<RC_TWO, RC_WT, false>), dim3(grid), dim3(BLOCK), lds, st, P, counts);
         }
         hipLaunchKernelGGL(k_rect_finish, dim3((n_pix + 255) / 256), dim3(256), 0, st, counts, n_pix,
                            (uint32_t)L.area_samples, visibility);

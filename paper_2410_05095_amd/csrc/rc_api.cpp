@@ -112,6 +112,7 @@ DevScene dev_scene(const rc_scene* s)
     d.n_tris = s->nt;
     // allocated node count (a two-level scene's array has room for its largest top level)
     d.n_nodes = s->two_level ? s->blas_nodes + s->tlas.cap : s->hb.n_nodes;
+    d.wide = d.n_nodes >= (1u << 25) ? 1u : 0u;   // 128-byte nodes
     d.max_stack = s->hb.max_stack;
     d.scale = s->scale;
     d.inst = s->two_level ? s->d_inst : nullptr;

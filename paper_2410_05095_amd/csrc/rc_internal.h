@@ -54,6 +54,7 @@ struct DevScene {
     uint32_t tlas_root;       // two-level structures: root node of the top level
     uint32_t watertight;      // triangles packed as (v0, v1, v2) and tested watertight (else (v0, e1, e2), MT)
     const float* nrm;         // n_vertices x 3 vertex normals (current pose), or NULL
+    uint32_t wide;            // the node array takes 4 GiB or more: per-lane walks address it with 64-bit offsets
 };
 
 // whether the wave-uniform shadow kernels can walk the scene's tree: 32-bit byte offsets of nodes and triangles, at

@@ -90,13 +90,13 @@ __device__ inline void rc_ray_inv(TravRay& r)
 
 // Slab test of one box, its near (nx, ny, nz) and far (fx, fy, fz) plane coordinates picked by the signs
 // of the ray's direction: whether the segment [0, bound] enters the box, and the entry distance t0 >= 0.
-__device__ inline bool rc_slab(const TravRay& r, float nx, float ny, float nz, float fx, float fy, float fz,
-                               float bound, float& t0)
+__device__ inline bool rc_slab(const TravRay& r, const float invf[3], float nx, float ny, float nz, float fx, float fy,
+                               float fz, float bound, float& t0)
 {
     t0 = fmaxf(fmaxf(fmaf(nx, r.inv[0], r.cn[0]), fmaf(ny, r.inv[1], r.cn[1])),
                fmaxf(fmaf(nz, r.inv[2], r.cn[2]), 0.0f));
-    const float t1 = fminf(fminf(fmaf(fx, r.invf[0], r.cf[0]), fmaf(fy, r.invf[1], r.cf[1])),
-                           fminf(fmaf(fz, r.invf[2], r.cf[2]), bound));
+    const float t1 = fminf(fminf(fmaf(fx, invf[0], r.cf[0]), fmaf(fy, invf[1], r.cf[1])),
+                           fminf(fmaf(fz, invf[2], r.cf[2]), bound));
     return t0 <= t1;
 }
 
@@ -174,6 +174,16 @@ struct TravStack {
         ++sp;
     }
 
+    // room in LDS for the three entries that one node can push
+    __device__ inline bool room3(int sp) const { return sp <= SL - 3; }
+
+    // write entry sp of the LDS part (room3), pushed or not: the caller moves sp on when it is
+    __device__ inline void put(int sp, uint32_t w, float tn)
+    {
+        rc_lds[sp * BLOCK + tid] = w;
+        if (HAS_T) rc_lds[(SL + sp) * BLOCK + tid] = __float_as_uint(tn);
+    }
+
     // pop the next entry; closest-hit rays skip entries that start beyond the current hit
     __device__ inline uint32_t pop(int& sp, bool cull, float best_t)
     {
@@ -229,26 +239,76 @@ __device__ inline uint32_t trav_pop(TravRay& r, TravState& s, Stack& st, bool an
 // Visit the internal node s.cur: test the four child boxes, continue with the nearest hit child and
 // push the others (farthest first), or pop.  `any`: any-hit ray on the segment 0 < t < 1, otherwise
 // closest hit (boxes beyond the current hit are culled).
-template <bool TWO = false, class Stack>
+// Bound by the seven 16-byte loads per lane (the texture units take 16 cycles for each, most lanes standing at nodes of
+// their own: at 1080p a wave's lanes share the node in a tenth of the camera rays' visits) and their latency, then
+// by vector issue.  So the near and far plane blocks are loaded from addresses picked by the direction's signs, not
+// selected afterwards (24 selects); the entries are pushed without branches where the LDS part has room for three; and
+// signs and far reciprocals (inv * RC_FAR_GROW, as rc_ray_inv) are worked out on each visit, since held in
+// registers they cost occupancy or spills (volatile: not moved out of the loop).  Camera / shadow rays one per lane
+// with 24 selects, three branches and counting in every launch, against now: 128x128 on 1.1M triangles 0.111 / 0.193
+// and 0.106 / 0.178 ms (4 lights); 64 batched views, camera rays 4.55 and 4.29 ms; far reciprocals and signs kept in
+// registers 5.2 (spills); 7 waves per SIMD with 10 LDS entries instead of 6 with 12: 3 to 5% slower on single views.
+// LANE_BASE: the lanes of a wave may walk node arrays of different scenes.  Otherwise a scalar base and 32-bit offsets
+// serve arrays below 4 GiB, and sc.wide (uniform) takes 64-bit addresses with selects, which need no more registers.
+template <bool TWO, bool LANE_BASE, class Stack>
 __device__ inline void trav_visit_node(const DevScene& sc, TravRay& r, TravState& s, Stack& st, bool any,
                                        TravWorld* w = nullptr)
 {
-    const float4* np = reinterpret_cast<const float4*>(sc.nodes + s.cur);
-    float4 lx = np[0], hx = np[1], ly = np[2], hy = np[3], lz = np[4], hz = np[5];
-    uint4 ch = reinterpret_cast<const uint4*>(np)[6];
+    // The near and far plane blocks come from addresses picked by the direction's signs, instead of 24 selects.  The
+    // signs and the far reciprocals (inv * RC_FAR_GROW, as rc_ray_inv) are worked out here on each visit: kept in
+    // registers they cost occupancy or spills (volatile, so that the compiler does not move them out of the loop).
+    float4 nr[3], fr[3];
+    float invf[3];
+    uint32_t up[3];
+    uint4 ch;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        static_assert(__builtin_bit_cast(uint32_t, RC_FAR_GROW) == 0x3f800008u, "far reciprocal");
+        asm volatile("v_mul_f32 %0, 0x3f800008, %1" : "=v"(invf[a]) : "v"(r.inv[a]));
+        asm volatile("v_lshrrev_b32 %0, 31, %1" : "=v"(up[a]) : "v"(r.inv[a]));
+    }
+    if constexpr (LANE_BASE) {
+        // node arrays of several scenes in one wave
+        const uint64_t np = reinterpret_cast<uint64_t>(sc.nodes) + ((uint64_t)s.cur << 7);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const uint64_t o = np | (up[a] << 4);
+            nr[a] = *reinterpret_cast<const float4*>(o + 32 * a);
+            fr[a] = *reinterpret_cast<const float4*>((o ^ 16u) + 32 * a);
+        }
+        ch = *reinterpret_cast<const uint4*>(np + 96);
+    } else if (sc.wide != 0u) {
+        const float4* np = reinterpret_cast<const float4*>(sc.nodes + s.cur);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float4 lo = np[2 * a], hi = np[2 * a + 1];
+            const bool pos = up[a] == 0u;
+            nr[a] = make_float4(pos ? lo.x : hi.x, pos ? lo.y : hi.y, pos ? lo.z : hi.z, pos ? lo.w : hi.w);
+            fr[a] = make_float4(pos ? hi.x : lo.x, pos ? hi.y : lo.y, pos ? hi.z : lo.z, pos ? hi.w : lo.w);
+        }
+        ch = reinterpret_cast<const uint4*>(np)[6];
+    } else {
+        // scalar base, 32-bit offsets
+        const char* nb = reinterpret_cast<const char*>(sc.nodes);
+        const uint32_t np = s.cur << 7;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const uint32_t o = np | (up[a] << 4);
+            nr[a] = *reinterpret_cast<const float4*>(nb + o + 32 * a);
+            fr[a] = *reinterpret_cast<const float4*>(nb + (o ^ 16u) + 32 * a);
+        }
+        ch = *reinterpret_cast<const uint4*>(nb + np + 96);
+    }
     const float bound = any ? 1.0f : s.best_t;
-    float lxs[4] = {lx.x, lx.y, lx.z, lx.w}, hxs[4] = {hx.x, hx.y, hx.z, hx.w};
-    float lys[4] = {ly.x, ly.y, ly.z, ly.w}, hys[4] = {hy.x, hy.y, hy.z, hy.w};
-    float lzs[4] = {lz.x, lz.y, lz.z, lz.w}, hzs[4] = {hz.x, hz.y, hz.z, hz.w};
+    const float nxs[4] = {nr[0].x, nr[0].y, nr[0].z, nr[0].w}, fxs[4] = {fr[0].x, fr[0].y, fr[0].z, fr[0].w};
+    const float nys[4] = {nr[1].x, nr[1].y, nr[1].z, nr[1].w}, fys[4] = {fr[1].x, fr[1].y, fr[1].z, fr[1].w};
+    const float nzs[4] = {nr[2].x, nr[2].y, nr[2].z, nr[2].w}, fzs[4] = {fr[2].x, fr[2].y, fr[2].z, fr[2].w};
     uint32_t cw[4] = {ch.x, ch.y, ch.z, ch.w};
     float tn[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        float nx = r.inv[0] >= 0.0f ? lxs[c] : hxs[c], fx = r.inv[0] >= 0.0f ? hxs[c] : lxs[c];
-        float ny = r.inv[1] >= 0.0f ? lys[c] : hys[c], fy = r.inv[1] >= 0.0f ? hys[c] : lys[c];
-        float nz = r.inv[2] >= 0.0f ? lzs[c] : hzs[c], fz = r.inv[2] >= 0.0f ? hzs[c] : lzs[c];
         float t0;
-        const bool hit = rc_slab(r, nx, ny, nz, fx, fy, fz, bound, t0);
+        const bool hit = rc_slab(r, invf, nxs[c], nys[c], nzs[c], fxs[c], fys[c], fzs[c], bound, t0);
         tn[c] = hit ? t0 : INFINITY;
     }
     // sort (distance, child) ascending with five comparators: misses (inf) sink to the end
@@ -261,9 +321,17 @@ __device__ inline void trav_visit_node(const DevScene& sc, TravRay& r, TravState
     }
     RC_CS(0, 1) RC_CS(2, 3) RC_CS(0, 2) RC_CS(1, 3) RC_CS(1, 2)
 #undef RC_CS
-    if (tn[3] < INFINITY) st.push(s.sp, cw[3], tn[3]);
-    if (tn[2] < INFINITY) st.push(s.sp, cw[2], tn[2]);
-    if (tn[1] < INFINITY) st.push(s.sp, cw[1], tn[1]);
+    if (st.room3(s.sp)) {
+#pragma unroll
+        for (int c = 3; c >= 1; --c) {
+            st.put(s.sp, cw[c], tn[c]);
+            s.sp += tn[c] < INFINITY ? 1 : 0;
+        }
+    } else {
+#pragma unroll
+        for (int c = 3; c >= 1; --c)
+            if (tn[c] < INFINITY) st.push(s.sp, cw[c], tn[c]);
+    }
     s.cur = tn[0] < INFINITY ? cw[0] : trav_pop<TWO>(r, s, st, any, w);
 }
 
@@ -436,7 +504,7 @@ __device__ inline bool rc_tri(const TravRay& r, const float4& A, const float4& B
 
 // Test the triangles of the leaf s.cur (FP32, the scene's triangle test), then pop; an any-hit ray ends at its
 // first hit (occluded = true, s.cur = RC_STACK_EMPTY).
-template <bool TWO = false, bool WT = false, class Stack>
+template <bool TWO, bool WT, bool COUNT, class Stack>
 __device__ inline void trav_test_leaf(const DevScene& sc, TravRay& r, TravState& s, Stack& st, bool any,
                                       uint32_t& occluded, uint32_t& tri_tests, TravWorld* w = nullptr)
 {
@@ -451,7 +519,7 @@ __device__ inline void trav_test_leaf(const DevScene& sc, TravRay& r, TravState&
     }
     uint32_t first = rc_leaf_first(s.cur), cnt = rc_leaf_count(s.cur);
     for (uint32_t i = 0; i < cnt; ++i) {
-        ++tri_tests;
+        if constexpr (COUNT) ++tri_tests;
         const float4* tp = sc.tris + 3 * (size_t)(first + i);
         float4 A = tp[0], B = tp[1], C = tp[2];
         float t, u, v;
@@ -476,23 +544,23 @@ __device__ inline void trav_test_leaf(const DevScene& sc, TravRay& r, TravState&
 // 3 node rounds and 1 leaf round per call took 1080p camera rays on 7.3M triangles from 0.70 to 0.57 ms.  A
 // lane's own sequence of visits is the same whatever the other lanes do; only the grouping of the work into
 // SIMD steps changes.
-template <bool TWO = false, bool WT = false, int NODE_STEPS = 0, int LEAF_STEPS = 0, class Stack>
+template <bool TWO = false, bool WT = false, int NODE_STEPS = 0, int LEAF_STEPS = 0, bool COUNT = false, bool LANE_BASE = false, class Stack>
 __device__ inline void trav_advance(const DevScene& sc, TravRay& r, TravState& s, Stack& st, bool busy,
                                     bool any, uint32_t& occluded, uint32_t& node_visits, uint32_t& tri_tests,
                                     TravWorld* w = nullptr)
 {
     for (int it = 0;; ++it) {
         bool inner = busy && !rc_is_leaf(s.cur);
-        if (__ballot(inner) == 0 || (NODE_STEPS > 0 && it >= NODE_STEPS)) break;
+        if (__builtin_amdgcn_ballot_w64(inner) == 0 || (NODE_STEPS > 0 && it >= NODE_STEPS)) break;
         if (inner) {
-            ++node_visits;
-            trav_visit_node<TWO>(sc, r, s, st, any, w);
+            if constexpr (COUNT) ++node_visits;
+            trav_visit_node<TWO, LANE_BASE>(sc, r, s, st, any, w);
         }
     }
     for (int it = 0;; ++it) {
         bool leaf = busy && s.cur != RC_STACK_EMPTY && rc_is_leaf(s.cur);
-        if (__ballot(leaf) == 0 || (LEAF_STEPS > 0 && it >= LEAF_STEPS)) break;
-        if (leaf) trav_test_leaf<TWO, WT>(sc, r, s, st, any, occluded, tri_tests, w);
+        if (__builtin_amdgcn_ballot_w64(leaf) == 0 || (LEAF_STEPS > 0 && it >= LEAF_STEPS)) break;
+        if (leaf) trav_test_leaf<TWO, WT, COUNT>(sc, r, s, st, any, occluded, tri_tests, w);
     }
 }
 

@@ -82,7 +82,7 @@ __device__ inline void wave_keys_uniform(const rc_v4f& nx, const rc_v4f& fx, con
     for (int c = 0; c < 4; ++c) {
         float t0;
         const bool hit = CLAMP ? rc_slab_seg(ray, nx[c], ny[c], nz[c], fx[c], fy[c], fz[c], t0)
-                                 : rc_slab(ray, nx[c], ny[c], nz[c], fx[c], fy[c], fz[c], bound, t0);
+                                 : rc_slab(ray, ray.invf, nx[c], ny[c], nz[c], fx[c], fy[c], fz[c], bound, t0);
         key[c] = wave_key(hit, t0, (uint32_t)c);
     }
 }
@@ -102,7 +102,7 @@ __device__ inline void wave_keys_uniform_skip(const rc_v4f& nx, const rc_v4f& fx
         }
         float t0;
         const bool hit = CLAMP ? rc_slab_seg(ray, nx[c], ny[c], nz[c], fx[c], fy[c], fz[c], t0)
-                                 : rc_slab(ray, nx[c], ny[c], nz[c], fx[c], fy[c], fz[c], bound, t0);
+                                 : rc_slab(ray, ray.invf, nx[c], ny[c], nz[c], fx[c], fy[c], fz[c], bound, t0);
         key[c] = wave_key(hit, t0, (uint32_t)c);
     }
 }
@@ -118,7 +118,7 @@ __device__ inline void wave_keys_mixed(const rc_v4f& lx, const rc_v4f& hx, const
         const float ny = ray.inv[1] >= 0.0f ? ly[c] : hy[c], fy = ray.inv[1] >= 0.0f ? hy[c] : ly[c];
         const float nz = ray.inv[2] >= 0.0f ? lz[c] : hz[c], fz = ray.inv[2] >= 0.0f ? hz[c] : lz[c];
         float t0;
-        const bool hit = CLAMP ? rc_slab_seg(ray, nx, ny, nz, fx, fy, fz, t0) : rc_slab(ray, nx, ny, nz, fx, fy, fz, bound, t0);
+        const bool hit = CLAMP ? rc_slab_seg(ray, nx, ny, nz, fx, fy, fz, t0) : rc_slab(ray, ray.invf, nx, ny, nz, fx, fy, fz, bound, t0);
         key[c] = wave_key(hit, t0, (uint32_t)c);
     }
 }
