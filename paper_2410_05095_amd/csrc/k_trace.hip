@@ -23,7 +23,7 @@ constexpr int REFILL_AT = 40;    // refill once a wave has at most this many bus
 constexpr uint32_t ITEM_CHUNK = 256;
 constexpr uint32_t RECT_CHUNK = 64;   // packets per chunk dealt to one XCD
 
-enum { MODE_PRIMARY = 0, MODE_POINT = 1 };
+enum { MODE_PRIMARY = 0, MODE_POINT = 1, MODE_RECT = 2 };
 
 struct KParams {
     DevScene sc;
@@ -585,6 +585,159 @@ __global__ __launch_bounds__(BLOCK) void k_primary_wave(KParams P)
     }
 }
 
+// value of the quad's lane (own lane ^ X)
+template <int X>
+__device__ inline uint32_t quad_xor(uint32_t v)
+{
+    constexpr int ctrl = (0 ^ X) | (1 ^ X) << 2 | (2 ^ X) << 4 | (3 ^ X) << 6;   // quad_perm
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, ctrl, 0xF, 0xF, true);
+}
+
+// Camera and shadow rays of small passes: four lanes to a ray, which test the four children of a node and up to four
+// triangles of a leaf at once.  A pass that leaves the chip idle lasts as long as its longest wave, a serial chain
+// of node visits whose time is half latency, half the wave's own instructions (four cycles each); here a visit
+// takes about 45 of them instead of 90, a leaf one round of loads instead of one per triangle, and a wave waits for
+// 16 rays instead of 64.  No queue and no refill: one wave per 16 rays, the workgroups of an XCD on neighbouring
+// tiles.  The tests are those of the per-lane walk (rc_slab, rc_tri), hits are kept per lane and reduced by (t, id).
+// 128x128 on 1.1M triangles: camera rays 0.093 to 0.051 ms, one point light 0.113 to 0.056; figures by size at quad_ok.
+template <int MODE, bool WT>
+__global__ __launch_bounds__(64) void k_quad(KParams P, uint32_t* counts)
+{
+    constexpr bool ANY = MODE != MODE_PRIMARY;
+    const uint32_t lane = threadIdx.x, q = lane >> 2, c = lane & 3u;
+    const DevScene& sc = P.sc;
+    // block b of XCD b % 8 takes the b / 8-th block of that XCD's contiguous share
+    const uint32_t share = (gridDim.x + RC_XCDS - 1) / RC_XCDS;
+    const uint32_t blk = (blockIdx.x % RC_XCDS) * share + blockIdx.x / RC_XCDS;
+    uint32_t px = 0, k = 0, light = 0;
+    bool on;
+    if (MODE == MODE_RECT) {
+        const uint64_t r = (uint64_t)blk * 16u + q;
+        const uint32_t N = (uint32_t)P.L.area_samples;
+        uint32_t none = 0;
+        on = r < (uint64_t)P.n_items * N && rc_item_to_sample(P.cam, (uint32_t)r / N, px, none);
+        k = (uint32_t)r % N;
+    } else {
+        const uint32_t groups = ANY ? (uint32_t)P.L.n_point : 1u;
+        const uint32_t part = blk / groups;
+        light = blk - part * groups;
+        const uint32_t item = part * 16u + q;
+        on = item < P.n_items && rc_item_to_sample(P.cam, item, px, k);
+    }
+    TravRay ray;
+    TravState ts;
+    const size_t smp = MODE == MODE_RECT ? (size_t)px : (size_t)px * (P.cam.ssaa * P.cam.ssaa) + k;
+    if (on) {
+        if constexpr (MODE == MODE_PRIMARY) {
+            rc_camera_ray(P.cam, px, k, ray.o, ray.d);
+        } else {
+            const float4 a = P.setup[2 * smp], b = P.setup[2 * smp + 1];
+            const float os[3] = {a.x, a.y, a.z}, nf[3] = {b.x, b.y, b.z};
+            on = a.w != 0.0f && rc_shadow_ray(P.L.point[light], P.L.rect, P.nL, MODE == MODE_RECT, px, k, P.L.area_stream,
+                                              P.cam.seed, P.cam.frame, os, nf, ray);
+        }
+    }
+    const bool cast = on;
+    uint32_t occluded = 0u;
+    if (on) {
+        trav_begin(ray, ts);
+        const char* nb = reinterpret_cast<const char*>(sc.nodes);
+        uint32_t ofs[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) ofs[a] = 32u * a + 4u * c + ((__float_as_uint(ray.inv[a]) >> 31) << 4);
+        uint2* stk = reinterpret_cast<uint2*>(rc_lds) + q;   // entry e of the quad's ray: stk[16 e]
+        float bound = ANY ? 1.0f : INFINITY;                 // closest hit of the quad so far
+        while (ts.cur != RC_STACK_EMPTY) {
+            if (!rc_is_leaf(ts.cur)) {
+                const uint32_t np = ts.cur << 7;
+                float n[3], f[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    n[a] = *reinterpret_cast<const float*>(nb + (np | ofs[a]));
+                    f[a] = *reinterpret_cast<const float*>(nb + ((np | ofs[a]) ^ 16u));
+                }
+                const uint32_t ch = *reinterpret_cast<const uint32_t*>(nb + (np | (4u * c)) + 96);
+                float t0;
+                const bool hit = rc_slab(ray, ray.invf, n[0], n[1], n[2], f[0], f[1], f[2], bound, t0);
+                asm volatile("" : : "v"(ch));   // loaded with the planes, not after the test
+                const uint32_t key = hit ? __float_as_uint(fabsf(t0)) : 0xFFFFFFF0u;
+                // this child's place among the four: by entry distance, then by slot
+                const uint32_t rank = (quad_xor<1>(key) < key + (c & 1u) ? 1u : 0u) +
+                                      (quad_xor<2>(key) < key + (c >> 1) ? 1u : 0u) +
+                                      (quad_xor<3>(key) < key + (c >> 1) ? 1u : 0u);
+                uint32_t hits = hit ? 1u : 0u;
+                hits += quad_xor<1>(hits);
+                hits += quad_xor<2>(hits);
+                if (hits != 0u) {
+                    // read by the quad's other lanes: the compiler may not move the stack's accesses past this
+                    if (hit && rank != 0u) stk[16 * (ts.sp + (int)(hits - 1u - rank))] = make_uint2(ch, key);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    ts.sp += (int)hits - 1;
+                    uint32_t first = rank == 0u ? ch : 0u;
+                    first |= quad_xor<1>(first);
+                    ts.cur = first | quad_xor<2>(first);
+                    continue;
+                }
+            } else {
+                const uint32_t first = rc_leaf_first(ts.cur), cnt = rc_leaf_count(ts.cur);
+                for (uint32_t i = c; i < cnt; i += 4u) {
+                    const float4* tp = sc.tris + 3 * (size_t)(first + i);
+                    const float4 A = tp[0], B = tp[1], C = tp[2];
+                    float t, u, v;
+                    const bool hit = rc_tri<WT>(ray, A, B, C, t, u, v);
+                    if (ANY) {
+                        if (hit && t < 1.0f) occluded = 1u;
+                    } else {
+                        const uint32_t id = __float_as_uint(A.w);
+                        if (hit && (t < ts.best_t || (t == ts.best_t && id < ts.best_id))) {
+                            ts.best_t = t; ts.best_u = u; ts.best_v = v; ts.best_id = id;
+                        }
+                    }
+                }
+                if (ANY) {
+                    occluded |= quad_xor<1>(occluded);
+                    occluded |= quad_xor<2>(occluded);
+                    if (occluded != 0u) break;
+                } else {
+                    bound = fminf(bound, ts.best_t);
+                    bound = fminf(bound, __uint_as_float(quad_xor<1>(__float_as_uint(bound))));
+                    bound = fminf(bound, __uint_as_float(quad_xor<2>(__float_as_uint(bound))));
+                }
+            }
+            // next entry; closest-hit rays skip those that start beyond the current hit
+            ts.cur = RC_STACK_EMPTY;
+            while (ts.sp > 0) {
+                --ts.sp;
+                const uint2 e = stk[16 * ts.sp];
+                if (ANY || __uint_as_float(e.y) <= bound) {
+                    ts.cur = e.x;
+                    break;
+                }
+            }
+        }
+        if constexpr (!ANY) {
+            auto take = [&](uint32_t id, float t, float u, float v) {
+                if (t < ts.best_t || (t == ts.best_t && id < ts.best_id)) {
+                    ts.best_t = t; ts.best_u = u; ts.best_v = v; ts.best_id = id;
+                }
+            };
+#define RC_TAKE(X)                                                                                              \
+    take(quad_xor<X>(ts.best_id), __uint_as_float(quad_xor<X>(__float_as_uint(ts.best_t))),                     \
+         __uint_as_float(quad_xor<X>(__float_as_uint(ts.best_u))), __uint_as_float(quad_xor<X>(__float_as_uint(ts.best_v))))
+            RC_TAKE(1);
+            RC_TAKE(2);
+#undef RC_TAKE
+        }
+    }
+    if (c != 0u || !cast) return;
+    if (MODE == MODE_PRIMARY)
+        P.gbuf_out[smp] = make_uint4(ts.best_id, __float_as_uint(ts.best_t), __float_as_uint(ts.best_u), __float_as_uint(ts.best_v));
+    else if (occluded == 0u) {
+        if (MODE == MODE_RECT) atomicAdd(counts + px, 1u);
+        else atomicOr(P.mask + smp, 1u << light);   // cleared by the setup pass
+    }
+}
+
 __global__ void k_rect_finish(const uint32_t* counts, uint32_t n_pix, uint32_t N, float* vis)
 {
     uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -593,6 +746,29 @@ __global__ void k_rect_finish(const uint32_t* counts, uint32_t n_pix, uint32_t N
 
 template <int MODE>
 constexpr size_t lds_bytes() { return TravStack<SL, BLOCK, MODE == MODE_PRIMARY>::lds_bytes(); }
+
+// Small passes go four lanes to a ray (k_quad): flat trees with stacks up to 64 entries (8 KiB of LDS per wave), nodes at
+// 32-bit offsets, nothing counted.  The limits lie where the chip is full and the quad's extra instructions per ray
+// begin to cost.  Four lanes / one lane per ray (ms), on 1.1M triangles (7.3M in brackets):
+//   camera rays         16K 0.051 / 0.093 (0.086 / 0.154), 230K 0.089 / 0.148 (0.130 / 0.206), 0.52M 0.133 / 0.155
+//                       (0.201 / 0.233), 0.92M 0.184 / 0.195 (0.291 / 0.262), 2.07M 0.341 / 0.254 (0.515 / 0.382)
+//   point lights        16K 0.056 / 0.113 (0.088 / 0.182), 0.46M 0.160 / 0.259 (0.248 / 0.278), 0.72M 0.221 / 0.273
+//                       (0.352 / 0.315), 0.92M 0.302 / 0.291 (0.428 / 0.343)
+//   rect light          16K 0.074 / 0.174 (0.122 / 0.251), 0.72M 0.201 / 0.225 (0.285 / 0.330), 0.92M 0.203 / 0.226
+//                       (0.296 / 0.322), 1.23M 0.285 / 0.240 (0.353 / 0.410)
+constexpr uint64_t PRIMARY_WAVE = 5000000;   // 2x2 samples: camera rays wave-uniform above (rc_launch_primary)
+constexpr uint64_t QUAD_CAMERA = 600000, QUAD_POINT = 600000, QUAD_RECT = 950000;
+bool quad_ok(const DevScene& sc, const TraceWork& w, uint64_t rays, uint64_t limit)
+{
+    return rays <= limit && !sc.inst && !w.ray_count && sc.max_stack <= 64 && sc.n_nodes < (1u << 25);
+}
+size_t quad_lds(const DevScene& sc) { return (size_t)sc.max_stack * 16 * sizeof(uint2); }
+// waves of 16 rays for `rays` rays in each of `groups`, a whole share for every XCD
+uint32_t quad_grid(uint64_t rays, uint32_t groups)
+{
+    const uint64_t waves = (rays + 15) / 16 * groups;
+    return (uint32_t)((waves + RC_XCDS - 1) / RC_XCDS * RC_XCDS);
+}
 
 // compute units of the device and resident blocks of a kernel per compute unit (1 if a query fails)
 int cu_count(int device)
@@ -654,11 +830,17 @@ void rc_launch_primary(const DevScene& sc, const DevCamera& cam, uint4* gbuf, co
     P.w = w;
     P.n_items = rc_n_items(cam.width, cam.height, cam.ssaa);
     P.slot = 0;
-    // the wave-uniform traversal pays off with 2x2 supersampling (a wave holds 4 samples of each of 16
-    // neighbouring pixels); with one sample per pixel, 8x8-pixel tiles diverge more and per-lane is faster
-    // (two-level structures always use the per-lane kernel for camera rays)
+    // with one sample per pixel, a wave's 8x8-pixel tile diverges too much for the wave-uniform traversal; with 2x2 (4
+    // samples of each of 16 neighbouring pixels) it pays off where there are enough waves to hide the longest walks.
+    // Wave / per lane (ms), 1.1M triangles (7.3M): 2.07M samples 0.37 / 0.26 (0.51 / 0.38), 3.7M 0.45 / 0.36 (0.63 /
+    // 0.52), 8.3M 0.68 / 0.68 (0.93 / 0.96), 33M 1.65 / 2.02 (2.26 / 2.95).  Counted frames keep the wave kernel at
+    // any size, two-level structures the per-lane one.
     const bool two = sc.inst != nullptr, wt = sc.watertight != 0u;
-    if (sc.max_stack <= 128 && !per_lane && cam.ssaa > 1 && !two) {
+    if (!per_lane && quad_ok(sc, w, P.n_items, QUAD_CAMERA)) {
+        const dim3 g(quad_grid(P.n_items, 1));
+        if (wt) hipLaunchKernelGGL((k_quad<MODE_PRIMARY, true>), g, dim3(64), quad_lds(sc), st, P, (uint32_t*)nullptr);
+        else hipLaunchKernelGGL((k_quad<MODE_PRIMARY, false>), g, dim3(64), quad_lds(sc), st, P, (uint32_t*)nullptr);
+    } else if (sc.max_stack <= 128 && !per_lane && cam.ssaa > 1 && !two && (P.n_items > PRIMARY_WAVE || w.ray_count)) {
         P.claim = claim_size((P.n_items + 63) / 64, grid, 64, 1, 4);
         if (wt)
             hipLaunchKernelGGL(k_primary_wave<true>, dim3(grid), dim3(BLOCK), 0, st, P);
@@ -710,17 +892,24 @@ void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights&
     // one unit of work per sample and light in the per-lane kernel too, where the unit count fits 32 bits
     const bool split = L.n_point > 1 && (uint64_t)P.n_items * (uint64_t)L.n_point < (1ull << 31);
     P.light_groups = split ? (uint32_t)L.n_point : 1u;
+    const bool quad_point = kernels == RC_KERNELS_AUTO && quad_ok(sc, w, (uint64_t)P.n_items * (uint64_t)L.n_point, QUAD_POINT);
+    const bool quad_rect = kernels == RC_KERNELS_AUTO && L.has_rect &&
+                           quad_ok(sc, w, (uint64_t)P.n_items * (uint64_t)L.area_samples, QUAD_RECT);
     P.setup = setup;
     if (L.n_point > 0 || L.has_rect) {
         // one setup entry per sample of the image (the item count is padded to whole tiles); every shadow kernel
         // reads its rays' origins and normals from there
         const uint32_t n_samples = (uint32_t)(cam.width * cam.height * cam.ssaa * cam.ssaa);
         hipLaunchKernelGGL(k_shadow_setup, dim3((n_samples + 255) / 256), dim3(256), 0, st, sc, cam, gbuf, n_samples,
-                           setup, L.n_point > 0 && (wave_point || split) ? mask : nullptr);
+                           setup, L.n_point > 0 && (wave_point || quad_point || split) ? mask : nullptr);
     }
     if (L.n_point > 0) {
         P.slot = 1;
-        if (wave_point) {
+        if (quad_point) {
+            const dim3 g(quad_grid(P.n_items, (uint32_t)L.n_point));
+            if (wt) hipLaunchKernelGGL((k_quad<MODE_POINT, true>), g, dim3(64), quad_lds(sc), st, P, (uint32_t*)nullptr);
+            else hipLaunchKernelGGL((k_quad<MODE_POINT, false>), g, dim3(64), quad_lds(sc), st, P, (uint32_t*)nullptr);
+        } else if (wave_point) {
             P.claim = claim_size((uint64_t)((P.n_items + 63) / 64) * (uint64_t)L.n_point, grid, 64, 1, 4);
             if (sc.max_stack <= 64) {
                 if (count)
@@ -758,7 +947,11 @@ void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights&
         rc_launch_fill_u32(counts, 0u, n_pix, st);
         // the wave-uniform traversal: a wave holds the samples of one pixel, or of 64 / N neighbouring
         // pixels, whose rays start close together
-        if (wave_rect) {
+        if (quad_rect) {
+            const dim3 g(quad_grid((uint64_t)P.n_items * (uint64_t)L.area_samples, 1));
+            if (wt) hipLaunchKernelGGL((k_quad<MODE_RECT, true>), g, dim3(64), quad_lds(sc), st, P, counts);
+            else hipLaunchKernelGGL((k_quad<MODE_RECT, false>), g, dim3(64), quad_lds(sc), st, P, counts);
+        } else if (wave_rect) {
             if (sc.max_stack <= 64) {
                 if (count)
                     RC_LAUNCH_TW((k_rect_wave<RC_TWO, RC_WT, false, true>), dim3(grid), dim3(BLOCK), 0, st, P, counts,
