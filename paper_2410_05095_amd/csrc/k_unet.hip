@@ -539,7 +539,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void
     __syncthreads();
     const int c8n = a.Cout / 8;
     if (a.head_out) {
-        // the network's head on each pixel of the tile, from the BF16 values the layer would have stored
+        // the network's head on each pixel of the tile, from the layer's BF16 values, stored (training) or not
         for (int px = lane; px < R * 16; px += 64) {
             const int o = px / 16, x = x0 + 16 * wave + (px % 16), y = y0 + o;
             if (x >= a.W || y >= a.H) continue;
@@ -548,7 +548,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void
             for (int q = 0; q < 4; ++q) unpack8(*reinterpret_cast<const uint4*>(tile + px * TS + 8 * q), f + 8 * q);
             a.head_out[(size_t)(n * a.H + y) * a.W + x] = head_value(f, a.head_w, a.head_b);
         }
-    } else {
+    }
+    if (a.out) {
         for (int q = lane; q < R * 16 * c8n; q += 64) {
             const int px = q / c8n, c8 = q - px * c8n;
             const int o = px / 16, x = x0 + 16 * wave + (px % 16), y = y0 + o;
@@ -1056,112 +1057,117 @@ __global__ __launch_bounds__(256) void k_pool_back_add_mask(const uint16_t* gpoo
     st8(out + q * C + c, pack8(r));
 }
 
-// ---------------------------------------------------------------- head, loss
-// y = sigmoid(sum_c d1[p][c] wh[c] + bh), wh rounded to BF16 like every weight, bh in FP32 like every bias
-__global__ __launch_bounds__(256) void k_head(const uint16_t* d1, const float* wh, const float* bh, int P, float* y)
+// ---------------------------------------------------------------- loss, head gradients
+// per-chunk sums of mask and mask * (y - t)^2, chunks of LOSS_CHUNK pixels (8x512^2: 512 workgroups; with 64 of
+// 32768 pixels the sums took 59 us, 14 now)
+constexpr int LOSS_CHUNK = 4096;
+__device__ inline void block_sum2(float& a, float& b, float* sm)   // of 256 threads, in thread 0
 {
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
-    const uint16_t* row = d1 + (size_t)p * 32;
-    float f[32];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) unpack8(ld8(row + 8 * q), f + 8 * q);
-    y[p] = head_value(f, wh, bh);
+    for (int h = 32; h > 0; h >>= 1) {
+        a += __shfl_xor(a, h);
+        b += __shfl_xor(b, h);
+    }
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) { sm[2 * wave] = a; sm[2 * wave + 1] = b; }
+    __syncthreads();
+    a = (sm[0] + sm[2]) + (sm[4] + sm[6]);
+    b = (sm[1] + sm[3]) + (sm[5] + sm[7]);
 }
 
-// per-chunk sums of mask and mask * (y - t)^2
-__global__ __launch_bounds__(256) void k_loss_partials(const float* y, const float* t, const float* m, int P, int chunk,
+__global__ __launch_bounds__(256) void k_loss_partials(const float* y, const float* t, const float* m, int P,
                                                        float* partial)
 {
-    __shared__ float sm[256], sl[256];
-    int p0 = blockIdx.x * chunk, pe = min(P, p0 + chunk);
+    __shared__ float sm[8];
+    const int p0 = blockIdx.x * LOSS_CHUNK;
     float a = 0.0f, b = 0.0f;
-    for (int p = p0 + threadIdx.x; p < pe; p += blockDim.x) {
-        float d = y[p] - t[p];
-        a += m[p];
-        b += m[p] * d * d;
+#pragma unroll 4
+    for (int k = 0; k < LOSS_CHUNK / 256; ++k) {
+        const int p = p0 + 256 * k + (int)threadIdx.x;
+        if (p >= P) break;
+        const float d = y[p] - t[p], w = m[p];
+        a += w;
+        b += w * d * d;
     }
-    sm[threadIdx.x] = a;
-    sl[threadIdx.x] = b;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) { sm[threadIdx.x] += sm[threadIdx.x + s]; sl[threadIdx.x] += sl[threadIdx.x + s]; }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) { partial[2 * blockIdx.x] = sm[0]; partial[2 * blockIdx.x + 1] = sl[0]; }
+    block_sum2(a, b, sm);
+    if (threadIdx.x == 0) { partial[2 * blockIdx.x] = a; partial[2 * blockIdx.x + 1] = b; }
 }
 
 // sums[0] = sum mask, sums[1] = loss = sum m (y-t)^2 / max(sum m, 1)
-__global__ void k_loss_final(const float* partial, int n, float* sums)
+__global__ __launch_bounds__(256) void k_loss_final(const float* partial, int n, float* sums)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    __shared__ float sm[8];
     float a = 0.0f, b = 0.0f;
-    for (int i = 0; i < n; ++i) { a += partial[2 * i]; b += partial[2 * i + 1]; }
-    sums[0] = a;
-    sums[1] = b / fmaxf(a, 1.0f);
+    for (int i = threadIdx.x; i < n; i += 256) { a += partial[2 * i]; b += partial[2 * i + 1]; }
+    block_sum2(a, b, sm);
+    if (threadIdx.x == 0) {
+        sums[0] = a;
+        sums[1] = b / fmaxf(a, 1.0f);
+    }
 }
 
-// dlogit = 2 m (y - t) / max(sum m, 1) * y (1 - y); gpre_d1 = mask(d1 > 0) * dlogit * wh; one pixel per
-// thread, and per block of 256 pixels the partial head gradients (32 weights, then the bias) summed in a
-// fixed tree order
+// dlogit = 2 m (y - t) / max(sum m, 1) * y (1 - y); gpre_d1 = mask(d1 > 0) * dlogit * wh, and per block of HEAD_PX
+// pixels the partial head gradients (32 weights, then the bias).  Memory-bound: 32 BF16 channels in, 32 out.  Four
+// lanes to a pixel, 8 channels each, so that a wave's loads and stores are contiguous, the sums of 8 pixels in
+// registers, then across the lanes in a fixed order.  8x512^2: 129 us with one pixel per thread, its 64 bytes apart
+// from its neighbour's, and 33 sums per 256 pixels through LDS; 49 us now (294 MB, part of it from the last-level cache).
+constexpr int HEAD_PX = 512;
 __global__ __launch_bounds__(256) void k_head_back(const uint16_t* d1, const float* y, const float* t, const float* m,
                                                    const float* sums, const float* wh, int P, uint16_t* gpre,
                                                    float* partial)
 {
-    __shared__ float sm[33][256];
-    const int tid = threadIdx.x;
-    const int p = blockIdx.x * 256 + tid;
-    float v[33];
+    __shared__ float sm[4][36];
+    const int tid = threadIdx.x, c4 = tid & 3;
+    const float inv = 2.0f / fmaxf(sums[0], 1.0f);
+    float wq[8], v[9];
 #pragma unroll
-    for (int c = 0; c < 33; ++c) v[c] = 0.0f;
-    if (p < P) {
-        const float inv = 2.0f / fmaxf(sums[0], 1.0f);
+    for (int e = 0; e < 8; ++e) {
+        wq[e] = bf2f(f2bf(wh[8 * c4 + e]));
+        v[e] = 0.0f;
+    }
+    v[8] = 0.0f;
+#pragma unroll 2
+    for (int k = 0; k < HEAD_PX / 64; ++k) {
+        const int p = blockIdx.x * HEAD_PX + 64 * k + (tid >> 2);
+        if (p >= P) break;
         const float yy = y[p];
         const float dl = m[p] * (yy - t[p]) * inv * yy * (1.0f - yy);
-        const uint4* row = reinterpret_cast<const uint4*>(d1 + (size_t)p * 32);
-        uint4* out = reinterpret_cast<uint4*>(gpre + (size_t)p * 32);
+        const size_t o = (size_t)p * 32 + 8 * c4;
+        float f[8], gr[8];
+        unpack8(*reinterpret_cast<const uint4*>(d1 + o), f);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            uint4 r = row[q];
-            uint32_t w[4] = {r.x, r.y, r.z, r.w}, o[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float a0 = __uint_as_float(w[e] << 16), a1 = __uint_as_float(w[e] & 0xFFFF0000u);
-                int c = 8 * q + 2 * e;
-                v[c] = dl * a0;
-                v[c + 1] = dl * a1;
-                uint32_t g0 = a0 > 0.0f ? f2bf(dl * bf2f(f2bf(wh[c]))) : 0u;
-                uint32_t g1 = a1 > 0.0f ? f2bf(dl * bf2f(f2bf(wh[c + 1]))) : 0u;
-                o[e] = g0 | (g1 << 16);
-            }
-            out[q] = make_uint4(o[0], o[1], o[2], o[3]);
+        for (int e = 0; e < 8; ++e) {
+            v[e] += dl * f[e];
+            gr[e] = f[e] > 0.0f ? dl * wq[e] : 0.0f;
         }
-        v[32] = dl;
+        v[8] += dl;
+        *reinterpret_cast<uint4*>(gpre + o) = pack8(gr);
     }
 #pragma unroll
-    for (int c = 0; c < 33; ++c) sm[c][tid] = v[c];
+    for (int e = 0; e < 9; ++e)
+        for (int h = 4; h < 64; h <<= 1) v[e] += __shfl_xor(v[e], h);
+    if ((tid & 63) < 4) {
+#pragma unroll
+        for (int e = 0; e < 9; ++e) sm[tid >> 6][9 * c4 + e] = v[e];
+    }
     __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if (tid < h) {
-#pragma unroll
-            for (int c = 0; c < 33; ++c) sm[c][tid] += sm[c][tid + h];
-        }
-        __syncthreads();
+    if (tid < 33) {
+        const int i = tid < 32 ? 9 * (tid >> 3) + (tid & 7) : 8;
+        partial[(size_t)blockIdx.x * 33 + tid] = (sm[0][i] + sm[1][i]) + (sm[2][i] + sm[3][i]);
     }
-    if (tid < 33) partial[(size_t)blockIdx.x * 33 + tid] = sm[tid][0];
 }
 
 // ---------------------------------------------------------------- weights, Adam, features
-// FP32 master [Cout][9][Cin] -> BF16 copies: forward layout and flipped/transposed Wf[ci][8 - tap][co]
-__global__ __launch_bounds__(256) void k_weights_bf16(const float* w, int Cout, int Cin, uint16_t* wf, uint16_t* wb)
+// FP32 master [Cout][9][Cin] of every layer -> BF16 copies: forward layout and flipped/transposed Wf[ci][8 - tap][co].
+// One launch for all layers (one each took 54 us of a step; 9 now).
+__global__ __launch_bounds__(256) void k_weights_bf16(UnetBf16Weights u)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int n = Cout * 9 * Cin;
-    if (i >= n) return;
-    int ci = i % Cin, tap = (i / Cin) % 9, co = i / (9 * Cin);
-    uint16_t v = f2bf(w[i]);
-    wf[i] = v;
-    if (wb) wb[((size_t)ci * 9 + (8 - tap)) * Cout + co] = v;
+    const UnetBf16Weights::Layer l = u.layer[blockIdx.y];
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < l.cout * 9 * l.cin; i += gridDim.x * 256) {
+        const int ci = i % l.cin, tap = (i / l.cin) % 9, co = i / (9 * l.cin);
+        const uint16_t v = f2bf(u.w[l.in + i]);
+        u.wf[l.out + i] = v;
+        u.wb[l.out + ((size_t)ci * 9 + (8 - tap)) * l.cout + co] = v;
+    }
 }
 
 __global__ __launch_bounds__(256) void k_adam(float* w, const float* g, float* m, float* v, int n, float lr, float b1,
@@ -1329,20 +1335,16 @@ void unet_pool_back_add_mask(const uint16_t* gpool, const uint16_t* gcat, int N,
                        mask, out);
 }
 
-void unet_head(const uint16_t* d1, const float* wh, const float* bh, int P, float* y, hipStream_t st)
+int unet_loss_chunks(int P) { return (P + LOSS_CHUNK - 1) / LOSS_CHUNK; }
+
+void unet_loss(const float* y, const float* t, const float* m, int P, float* partial, float* sums, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_head, dim3(nb(P, 256)), dim3(256), 0, st, d1, wh, bh, P, y);
+    const int chunks = unet_loss_chunks(P);
+    hipLaunchKernelGGL(k_loss_partials, dim3(chunks), dim3(256), 0, st, y, t, m, P, partial);
+    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(256), 0, st, partial, chunks, sums);
 }
 
-void unet_loss(const float* y, const float* t, const float* m, int P, int chunk, float* partial, float* sums,
-               hipStream_t st)
-{
-    int chunks = (P + chunk - 1) / chunk;
-    hipLaunchKernelGGL(k_loss_partials, dim3(chunks), dim3(256), 0, st, y, t, m, P, chunk, partial);
-    hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(64), 0, st, partial, chunks, sums);
-}
-
-int unet_head_blocks(int P) { return (P + 255) / 256; }
+int unet_head_blocks(int P) { return (P + HEAD_PX - 1) / HEAD_PX; }
 
 void unet_head_back(const uint16_t* d1, const float* y, const float* t, const float* m, const float* sums,
                     const float* wh, int P, uint16_t* gpre, float* partial, hipStream_t st)
@@ -1351,10 +1353,9 @@ void unet_head_back(const uint16_t* d1, const float* y, const float* t, const fl
                        partial);
 }
 
-void unet_weights_bf16(const float* w, int Cout, int Cin, uint16_t* wf, uint16_t* wb, hipStream_t st)
+void unet_weights_bf16(const UnetBf16Weights& u, hipStream_t st)
 {
-    int n = Cout * 9 * Cin;
-    hipLaunchKernelGGL(k_weights_bf16, dim3(nb(n, 256)), dim3(256), 0, st, w, Cout, Cin, wf, wb);
+    hipLaunchKernelGGL(k_weights_bf16, dim3(64, u.n_layers), dim3(256), 0, st, u);
 }
 
 void unet_adam(float* w, const float* g, float* m, float* v, int n, float lr, float b1, float b2, float eps, float c1,

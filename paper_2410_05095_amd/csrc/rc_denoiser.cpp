@@ -86,9 +86,13 @@ int ctx_device(rc_ctx* c) { return c->device; }
 
 int refresh_bf16(rc_denoiser* d, hipStream_t st)
 {
-    for (int l = 0; l < N_LAYERS; ++l)
-        unet_weights_bf16(d->d_w + d->off_w[l], LAYERS[l].cout, LAYERS[l].cin, d->d_wbf + d->off_bf[l],
-                          d->d_wfl + d->off_bf[l], st);
+    UnetBf16Weights u = {};
+    u.n_layers = N_LAYERS;
+    u.w = d->d_w;
+    u.wf = d->d_wbf;
+    u.wb = d->d_wfl;
+    for (int l = 0; l < N_LAYERS; ++l) u.layer[l] = {LAYERS[l].cin, LAYERS[l].cout, d->off_w[l], d->off_bf[l]};
+    unet_weights_bf16(u, st);
     DN_HIP(hipGetLastError());
     return RC_OK;
 }
@@ -155,16 +159,9 @@ int ensure_partial(rc_denoiser* d, size_t floats)
     return RC_OK;
 }
 
-int chunk_for(size_t P)
-{
-    size_t c = (P + 63) / 64;             // at most 64 split-K chunks
-    c = std::max<size_t>(c, 1024);
-    return (int)((c + 31) & ~size_t(31));
-}
-
 // layer l; with `skip`, the input is [2x nearest-upsampled `in` (Ca channels), skip] read directly
-// pool_out: also write the 2x2 average pool of the output; head_out: write the network's head of the output
-// (layer D1B) instead of the output
+// pool_out: also write the 2x2 average pool of the output; head_out: also write the network's head of the output
+// (layer D1B); the output itself is then optional
 void conv(rc_denoiser* d, const uint16_t* in, int n, int h, int w, int l, uint16_t* out, hipStream_t st,
           const uint16_t* skip = nullptr, int Ca = 0, uint16_t* pool_out = nullptr, float* head_out = nullptr)
 {
@@ -182,7 +179,6 @@ void conv(rc_denoiser* d, const uint16_t* in, int n, int h, int w, int l, uint16
         a.head_w = d->d_w + d->off_w[N_LAYERS];
         a.head_b = d->d_w + d->off_b[N_LAYERS];
         a.head_out = head_out;
-        a.out = nullptr;
     }
     unet_conv3x3(a, st);
 }
@@ -221,8 +217,8 @@ void conv_back_weights(rc_denoiser* d, const uint16_t* x, const uint16_t* g, int
     unet_reduce_chunks(d->d_partial, unet_wgrad_chunks(a), (int)layer_w(l) + LAYERS[l].cout, d->d_g + d->off_w[l], st);
 }
 
-// y_out (inference): the head is computed in the last convolution's epilogue and written there, and the
-// last layer's activations are not stored; otherwise they are, and the head writes d_y.
+// The head is computed in the last convolution's epilogue.  Inference: written to y_out, and the last layer's activations
+// are not stored; otherwise they are, and the head goes to d_y.
 int forward(rc_denoiser* d, const uint16_t* x, int n, int h, int w, hipStream_t st, float* y_out = nullptr)
 {
     int st_ = ensure_workspace(d, n, h, w);
@@ -238,12 +234,7 @@ int forward(rc_denoiser* d, const uint16_t* x, int n, int h, int w, hipStream_t 
     conv(d, A + d->a_bnb, n, h2, w2, D2A, A + d->a_d2a, st, A + d->a_e2b, 128);
     conv(d, A + d->a_d2a, n, h2, w2, D2B, A + d->a_d2b, st);
     conv(d, A + d->a_d2b, n, h, w, D1A, A + d->a_d1a, st, A + d->a_e1b, 64);
-    if (y_out) {
-        conv(d, A + d->a_d1a, n, h, w, D1B, nullptr, st, nullptr, 0, nullptr, y_out);
-    } else {
-        conv(d, A + d->a_d1a, n, h, w, D1B, A + d->a_d1b, st);
-        unet_head(A + d->a_d1b, d->d_w + d->off_w[N_LAYERS], d->d_w + d->off_b[N_LAYERS], n * h * w, d->d_y, st);
-    }
+    conv(d, A + d->a_d1a, n, h, w, D1B, y_out ? nullptr : A + d->a_d1b, st, nullptr, 0, nullptr, y_out ? y_out : d->d_y);
     DN_HIP(hipGetLastError());
     return RC_OK;
 }
@@ -298,9 +289,7 @@ int backward(rc_denoiser* d, const uint16_t* x, const float* t, const float* m, 
     uint16_t* G = d->grad;
     size_t P = (size_t)n * h * w;
     int h2 = h / 2, w2 = w / 2, h4 = h / 4, w4 = w / 4;
-    int chunk = chunk_for(P);
-    const int chunks = (int)((P + chunk - 1) / chunk);   // of the loss
-    size_t need = (size_t)chunks * 2;
+    size_t need = (size_t)unet_loss_chunks((int)P) * 2;
     for (int l = 0; l < N_LAYERS; ++l) {
         const int s = (l == E1A || l == E1B || l == D1A || l == D1B) ? 1 : (l == BNA || l == BNB ? 4 : 2);
         need = std::max(need, (size_t)unet_wgrad_chunks(wgrad_args(n, h / s, w / s, l)) * (layer_w(l) + LAYERS[l].cout));
@@ -310,7 +299,7 @@ int backward(rc_denoiser* d, const uint16_t* x, const float* t, const float* m, 
     if (st_ != RC_OK) return st_;
     if (!d->d_sums) DN_HIP(hipMalloc(reinterpret_cast<void**>(&d->d_sums), 64));
     // loss and head
-    unet_loss(d->d_y, t, m, (int)P, chunk, d->d_partial, d->d_sums, st);
+    unet_loss(d->d_y, t, m, (int)P, d->d_partial, d->d_sums, st);
     unet_head_back(A + d->a_d1b, d->d_y, t, m, d->d_sums, d->d_w + d->off_w[N_LAYERS], (int)P, G + d->g_d1b,
                    d->d_partial, st);
     unet_reduce_blocks(d->d_partial, unet_head_blocks((int)P), 33, d->d_g + d->off_w[N_LAYERS], 0, st);   // head.w, head.b

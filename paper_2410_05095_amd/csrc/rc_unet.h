@@ -19,8 +19,8 @@ struct ConvArgs {
     uint16_t* pool_out;     // optional: also the 2x2 average pool of the output, N x H/2 x W/2 x Cout (H, W even;
                             // the LDS-tiled kernels)
     const float* head_w;    // optional 1x1 head for Cout = 32 (the row-blocked kernel): with head_out the
-    const float* head_b;    // epilogue writes sigmoid(head_b + sum_c out[c] head_w[c]) per pixel (FP32) and
-    float* head_out;        // not `out`
+    const float* head_b;    // epilogue writes sigmoid(head_b + sum_c out[c] head_w[c]) per pixel (FP32), and
+    float* head_out;        // `out` only if it is given
 };
 
 struct ConvArgsF32 {
@@ -57,13 +57,21 @@ void unet_up_back_mask(const uint16_t* g, int N, int H2, int W2, int Ctot, int c
                        uint16_t* out, hipStream_t st);
 void unet_pool_back_add_mask(const uint16_t* gpool, const uint16_t* gcat, int N, int H, int W, int C, int Ctot, int c0,
                              const uint16_t* mask, uint16_t* out, hipStream_t st);
-void unet_head(const uint16_t* d1, const float* wh, const float* bh, int P, float* y, hipStream_t st);
-void unet_loss(const float* y, const float* t, const float* m, int P, int chunk, float* partial, float* sums,
-               hipStream_t st);
+int unet_loss_chunks(int P);
+void unet_loss(const float* y, const float* t, const float* m, int P, float* partial, float* sums, hipStream_t st);
 int unet_head_blocks(int P);
 void unet_head_back(const uint16_t* d1, const float* y, const float* t, const float* m, const float* sums,
                     const float* wh, int P, uint16_t* gpre, float* partial, hipStream_t st);
-void unet_weights_bf16(const float* w, int Cout, int Cin, uint16_t* wf, uint16_t* wb, hipStream_t st);
+struct UnetBf16Weights {
+    struct Layer {
+        int cin, cout;
+        size_t in, out;     // offsets in w and in wf, wb
+    } layer[10];
+    int n_layers;
+    const float* w;
+    uint16_t *wf, *wb;
+};
+void unet_weights_bf16(const UnetBf16Weights& u, hipStream_t st);
 void unet_adam(float* w, const float* g, float* m, float* v, int n, float lr, float b1, float b2, float eps, float c1,
                float c2, hipStream_t st);
 void unet_fill_f32(float* p, float v, size_t n, hipStream_t st);
