@@ -203,6 +203,9 @@ __device__ __align__(16) const uint4 g_zero_group = {0u, 0u, 0u, 0u};
 // through L1 one K-step ahead.  With a second source the halo loader reads channels [0, Ca) from the 2x
 // nearest-upsampled low-resolution tensor and the rest from the skip tensor, so the decoder's upsample +
 // concat is never materialised.
+// SMALL (images that leave CUs idle): the workgroup takes the 16 NT output channels from 16 NT blockIdx.y on, and the
+// next chunk's loads are in flight under this chunk's instructions (on large images the registers that they hold cost
+// occupancy: 1080x1920 inference 714 against 743 us).
 template <int MT, int NT, int CC, bool SW>
 struct ConvLds {
     static constexpr int TW = 16 * MT, HW = TW + 2, HR = 6;
@@ -217,7 +220,7 @@ struct ConvLds {
     }
 };
 
-template <int MT, int NT, int CC, bool SW, int OCC>
+template <int MT, int NT, int CC, bool SW, int OCC, bool SMALL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void k_conv_lds(ConvArgs a)
 {
     extern __shared__ uint4 conv_lds[];
@@ -234,6 +237,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void
     const int x0 = tx * TW, y0 = ty * 4;
     const int r = lane & 15, g = lane >> 4;
     const int K = 9 * a.Cin;
+    const int co0 = SMALL ? 16 * NT * (int)blockIdx.y : 0;   // output channels [co0, co0 + cn)
+    const int cn = SMALL ? min(a.Cout - co0, 16 * NT) : a.Cout;
     f32x4 acc[MT][NT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
@@ -255,7 +260,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void
     };
     auto w_item = [&](int c0, int f) -> uint4 {
         const int l = f & 63, q = f >> 6, nt = q % NT, ks = q / NT;
-        const int co = 16 * nt + (l & 15), kk = 32 * ks + 8 * (l >> 4);
+        const int co = co0 + 16 * nt + (l & 15), kk = 32 * ks + 8 * (l >> 4);
         uint4 v = make_uint4(0u, 0u, 0u, 0u);
         if (kk < 9 * CC && co < a.Cout) {
             const int tap = kk / CC, cl = kk - tap * CC;
@@ -277,8 +282,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void
             wpf[k] = (L::W_U4 % 256 == 0 || f < L::W_U4) ? w_item(c0, f) : make_uint4(0u, 0u, 0u, 0u);
         }
     };
+    if constexpr (SMALL) fetch(0);
     for (int c0 = 0; c0 < a.Cin; c0 += CC) {
-        fetch(c0);
+        if constexpr (!SMALL) fetch(c0);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < PF; ++k) {
@@ -292,6 +298,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void
             if (L::W_U4 % 256 == 0 || f < L::W_U4) wfrag[f] = wpf[k];
         }
         __syncthreads();
+        if (SMALL && c0 + CC < a.Cin) fetch(c0 + CC);   // in flight under this chunk's instructions
         // streamed weights: fragments of K-step ks loaded while the MFMAs of the step before run
         auto load_b = [&](int ks, bf16x8* Bd) {
             const int kk = 32 * ks + 8 * g;
@@ -300,7 +307,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void
             const int cl = kk - tap * CC;
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                const int co = 16 * nt + r;
+                const int co = co0 + 16 * nt + r;
                 Bd[nt] = (kv && co < a.Cout) ? load8(a.wt + (size_t)co * K + tap * a.Cin + c0 + cl) : zero;
             }
         };
@@ -346,7 +353,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         const int co = 16 * nt + r;
-        const float b = (a.bias && co < a.Cout) ? a.bias[co] : 0.0f;
+        const float b = (a.bias && co < cn) ? a.bias[co0 + co] : 0.0f;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -359,7 +366,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void
     __syncthreads();
     if (a.pool_out) {
         // 2x2 average pool of the tile (rows 0-1 and 2-3 of the 4 waves; tile origin and H, W even)
-        const int Hp = a.H / 2, Wp = a.W / 2, c8p = a.Cout / 8;
+        const int Hp = a.H / 2, Wp = a.W / 2, c8p = cn / 8;
         for (int q = threadIdx.x; q < 2 * (TPX / 2) * c8p; q += 256) {
             const int pp = q / c8p, c8 = q - pp * c8p;
             const int po = pp / (TPX / 2), px2 = pp % (TPX / 2);
@@ -369,18 +376,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void
             const uint4 v = pool4(*reinterpret_cast<const uint4*>(t0), *reinterpret_cast<const uint4*>(t0 + TS),
                                   *reinterpret_cast<const uint4*>(t0 + TPX * TS),
                                   *reinterpret_cast<const uint4*>(t0 + TPX * TS + TS));
-            *reinterpret_cast<uint4*>(a.pool_out + ((size_t)(n * Hp + y / 2) * Wp + x / 2) * a.Cout + 8 * c8) = v;
+            *reinterpret_cast<uint4*>(a.pool_out + ((size_t)(n * Hp + y / 2) * Wp + x / 2) * a.Cout + co0 + 8 * c8) = v;
         }
     }
     const int y = y0 + wave;
     if (y >= a.H) return;
-    const int c8n = a.Cout / 8;
+    const int c8n = cn / 8;
     for (int q = lane; q < TPX * c8n; q += 64) {
         const int px = q / c8n, c8 = q - px * c8n;
         const int x = x0 + px;
         if (x >= a.W) continue;
         uint4 v = *reinterpret_cast<const uint4*>(tile + px * TS + 8 * c8);
-        const size_t o = ((size_t)(n * a.H + y) * a.W + x) * a.Cout + 8 * c8;
+        const size_t o = ((size_t)(n * a.H + y) * a.W + x) * a.Cout + co0 + 8 * c8;
         if (a.mask) {
             float f[8], mk[8];
             unpack8(v, f);
@@ -1194,21 +1201,25 @@ inline unsigned nb(size_t n, unsigned b) { return (unsigned)((n + b - 1) / b); }
 
 }  // namespace
 
-template <int MT, int NT, int CC, bool SW, int OCC>
+size_t conv_tiles(const ConvArgs& a, int rows, int cols)
+{
+    return (size_t)a.N * ((a.H + rows - 1) / rows) * ((a.W + cols - 1) / cols);
+}
+
+template <int MT, int NT, int CC, bool SW, int OCC, bool SMALL = false>
 void launch_conv_lds(const ConvArgs& a, hipStream_t st)
 {
-    constexpr int TW = 16 * MT;
-    const size_t tiles = (size_t)a.N * ((a.H + 3) / 4) * ((a.W + TW - 1) / TW);
     const size_t lds = ConvLds<MT, NT, CC, SW>::bytes();
-    hipLaunchKernelGGL((k_conv_lds<MT, NT, CC, SW, OCC>), dim3((unsigned)tiles), dim3(256), lds, st, a);
+    hipLaunchKernelGGL((k_conv_lds<MT, NT, CC, SW, OCC, SMALL>),
+                       dim3((unsigned)conv_tiles(a, 4, 16 * MT), SMALL ? (a.Cout + 16 * NT - 1) / (16 * NT) : 1), dim3(256),
+                       lds, st, a);
 }
 
 template <int R, int NT, int OCC>
 void launch_conv_rows(const ConvArgs& a, hipStream_t st)
 {
-    const size_t tiles = (size_t)a.N * ((a.H + R - 1) / R) * ((a.W + 63) / 64);
     const size_t lds = ConvRows<R, NT>::bytes();
-    hipLaunchKernelGGL((k_conv_rows<R, NT, OCC>), dim3((unsigned)tiles), dim3(256), lds, st, a);
+    hipLaunchKernelGGL((k_conv_rows<R, NT, OCC>), dim3((unsigned)conv_tiles(a, R, 64)), dim3(256), lds, st, a);
 }
 
 void unet_conv3x3(const ConvArgs& a, hipStream_t st)
@@ -1227,6 +1238,30 @@ void unet_conv3x3(const ConvArgs& a, hipStream_t st)
                       ConvLds<2, 6, 16, true>::bytes() <= 65536 && ConvLds<2, 8, 16, true>::bytes() <= 65536 &&
                       ConvLds<2, 12, 8, true>::bytes() <= 65536,
                   "convolution LDS beyond 64 KB");
+    // Small images leave CUs idle, and a layer lasts as long as one workgroup's chain of chunks (load, stage, multiply):
+    // smaller tiles, the output channels split over workgroups, and the next chunk loaded under this one's instructions
+    // (k_conv_lds SMALL; rows of 2 instead of 8).  Same sums in the same order.  Inference, these kernels / the others
+    // (us): 64^2 66 / 132, 256^2 74 / 142; 360x640 16- and 8-channel-chunk layers 90 / 119, row-blocked 51 / 44, first
+    // layer 12 / 9; 540x960 171 / 171, 98 / 81, 22 / 15.  In workgroups of the smaller tiles (row-blocked: of the larger
+    // ones) the layers cross over between 1100 and 2000, 128 and 450, and at about 1000.
+    const size_t small_blocks = conv_tiles(a, 4, 32) * (size_t)((nt + 1) / 2);
+    const bool small = nt <= 2 ? (cfg == 208 ? conv_tiles(a, 4, 16) <= 1024 : conv_tiles(a, RC_CONV_ROWS, 64) <= 256)
+                               : small_blocks <= 1200;
+    if (small) {
+        switch (cfg) {
+        case 208: launch_conv_lds<1, 2, 8, false, 4, true>(a, st); return;
+        case 232:
+        case 264:
+            if (nt == 1) launch_conv_rows<2, 1, 4>(a, st);
+            else launch_conv_rows<2, 2, 3>(a, st);
+            return;
+        case 416:
+        case 616:
+        case 816: launch_conv_lds<2, 2, 16, true, 3, true>(a, st); return;
+        case 1208: launch_conv_lds<2, 2, 8, true, 3, true>(a, st); return;
+        default: break;
+        }
+    }
     switch (cfg) {
     case 208: launch_conv_lds<4, 2, 8, false, RC_OCC_E1A>(a, st); return;
     case 232:
