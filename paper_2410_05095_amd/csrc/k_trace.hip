@@ -600,7 +600,7 @@ __device__ inline uint32_t quad_xor(uint32_t v)
 // 16 rays instead of 64.  No queue and no refill: one wave per 16 rays, the workgroups of an XCD on neighbouring
 // tiles.  The tests are those of the per-lane walk (rc_slab, rc_tri), hits are kept per lane and reduced by (t, id).
 // 128x128 on 1.1M triangles: camera rays 0.093 to 0.051 ms, one point light 0.113 to 0.056; figures by size at quad_ok.
-template <int MODE, bool WT>
+template <int MODE, bool TWO, bool WT>
 __global__ __launch_bounds__(64) void k_quad(KParams P, uint32_t* counts)
 {
     constexpr bool ANY = MODE != MODE_PRIMARY;
@@ -626,6 +626,7 @@ __global__ __launch_bounds__(64) void k_quad(KParams P, uint32_t* counts)
     }
     TravRay ray;
     TravState ts;
+    TravWorld tw;
     const size_t smp = MODE == MODE_RECT ? (size_t)px : (size_t)px * (P.cam.ssaa * P.cam.ssaa) + k;
     if (on) {
         if constexpr (MODE == MODE_PRIMARY) {
@@ -640,11 +641,14 @@ __global__ __launch_bounds__(64) void k_quad(KParams P, uint32_t* counts)
     const bool cast = on;
     uint32_t occluded = 0u;
     if (on) {
-        trav_begin(ray, ts);
+        trav_begin(ray, ts, TWO ? sc.tlas_root : 0u, TWO ? &tw : nullptr);
         const char* nb = reinterpret_cast<const char*>(sc.nodes);
-        uint32_t ofs[3];
+        uint32_t ofs[3];   // this child's near planes within a node
+        auto set_ofs = [&]() {
 #pragma unroll
-        for (int a = 0; a < 3; ++a) ofs[a] = 32u * a + 4u * c + ((__float_as_uint(ray.inv[a]) >> 31) << 4);
+            for (int a = 0; a < 3; ++a) ofs[a] = 32u * a + 4u * c + ((__float_as_uint(ray.inv[a]) >> 31) << 4);
+        };
+        set_ofs();
         uint2* stk = reinterpret_cast<uint2*>(rc_lds) + q;   // entry e of the quad's ray: stk[16 e]
         float bound = ANY ? 1.0f : INFINITY;                 // closest hit of the quad so far
         while (ts.cur != RC_STACK_EMPTY) {
@@ -678,6 +682,17 @@ __global__ __launch_bounds__(64) void k_quad(KParams P, uint32_t* counts)
                     ts.cur = first | quad_xor<2>(first);
                     continue;
                 }
+            } else if (TWO && tw.in_blas == 0u) {
+                // top-level leaf: enter the instance, its return point on the stack
+                const DevInst& I = sc.inst[rc_leaf_first(ts.cur)];
+                rc_map_ray(I.w2o, tw.o, tw.d, ray);
+                set_ofs();
+                if (c == 0u) stk[16 * ts.sp] = make_uint2(RC_INST_RETURN, 0u);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                ++ts.sp;
+                tw.in_blas = 1u;
+                ts.cur = I.root;
+                continue;
             } else {
                 const uint32_t first = rc_leaf_first(ts.cur), cnt = rc_leaf_count(ts.cur);
                 for (uint32_t i = c; i < cnt; i += 4u) {
@@ -709,6 +724,14 @@ __global__ __launch_bounds__(64) void k_quad(KParams P, uint32_t* counts)
             while (ts.sp > 0) {
                 --ts.sp;
                 const uint2 e = stk[16 * ts.sp];
+                if (TWO && e.x == RC_INST_RETURN) {   // back in world space
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) { ray.o[a] = tw.o[a]; ray.d[a] = tw.d[a]; }
+                    rc_ray_inv(ray);
+                    set_ofs();
+                    tw.in_blas = 0u;
+                    continue;
+                }
                 if (ANY || __uint_as_float(e.y) <= bound) {
                     ts.cur = e.x;
                     break;
@@ -747,8 +770,8 @@ __global__ void k_rect_finish(const uint32_t* counts, uint32_t n_pix, uint32_t N
 template <int MODE>
 constexpr size_t lds_bytes() { return TravStack<SL, BLOCK, MODE == MODE_PRIMARY>::lds_bytes(); }
 
-// Small passes go four lanes to a ray (k_quad): flat trees with stacks up to 64 entries (8 KiB of LDS per wave), nodes at
-// 32-bit offsets, nothing counted.  The limits lie where the chip is full and the quad's extra instructions per ray
+// Small passes go four lanes to a ray (k_quad): stacks up to 128 entries in LDS, nodes at 32-bit offsets, nothing
+// counted.  The limits lie where the chip is full and the quad's extra instructions per ray
 // begin to cost.  Four lanes / one lane per ray (ms), on 1.1M triangles (7.3M in brackets):
 //   camera rays         16K 0.051 / 0.093 (0.086 / 0.154), 230K 0.089 / 0.148 (0.130 / 0.206), 0.52M 0.133 / 0.155
 //                       (0.201 / 0.233), 0.92M 0.184 / 0.195 (0.291 / 0.262), 2.07M 0.341 / 0.254 (0.515 / 0.382)
@@ -756,13 +779,19 @@ constexpr size_t lds_bytes() { return TravStack<SL, BLOCK, MODE == MODE_PRIMARY>
 //                       (0.352 / 0.315), 0.92M 0.302 / 0.291 (0.428 / 0.343)
 //   rect light          16K 0.074 / 0.174 (0.122 / 0.251), 0.72M 0.201 / 0.225 (0.285 / 0.330), 0.92M 0.203 / 0.226
 //                       (0.296 / 0.322), 1.23M 0.285 / 0.240 (0.353 / 0.410)
-constexpr uint64_t PRIMARY_WAVE = 5000000;   // 2x2 samples: camera rays wave-uniform above (rc_launch_primary)
+// with trees of SAH or LBVH builds, whose stacks let 20 waves or more on a CU.  With deeper stacks, as of two-level
+// structures, in proportion to the waves that fit; there, 1.1M triangles: camera rays 16K 0.102 / 0.145, 230K 0.193 /
+// 0.202; one point light 16K 0.084 / 0.168, 230K 0.212 / 0.234; rect light 130K 0.141 / 0.253, 230K 0.203 / 0.241, 0.52M
+// 0.350 / 0.268.
 constexpr uint64_t QUAD_CAMERA = 600000, QUAD_POINT = 600000, QUAD_RECT = 950000;
+constexpr uint64_t PRIMARY_WAVE = 5000000;   // 2x2 samples: camera rays wave-uniform above (rc_launch_primary)
+size_t quad_lds(const DevScene& sc) { return (size_t)sc.max_stack * 16 * sizeof(uint2); }
 bool quad_ok(const DevScene& sc, const TraceWork& w, uint64_t rays, uint64_t limit)
 {
-    return rays <= limit && !sc.inst && !w.ray_count && sc.max_stack <= 64 && sc.n_nodes < (1u << 25);
+    if (w.ray_count || sc.max_stack > 128 || sc.n_nodes >= (1u << 25)) return false;
+    const uint64_t waves = 163840 / quad_lds(sc);
+    return waves >= 20 ? rays <= limit : rays * 20 <= QUAD_CAMERA * waves;
 }
-size_t quad_lds(const DevScene& sc) { return (size_t)sc.max_stack * 16 * sizeof(uint2); }
 // waves of 16 rays for `rays` rays in each of `groups`, a whole share for every XCD
 uint32_t quad_grid(uint64_t rays, uint32_t groups)
 {
@@ -838,8 +867,7 @@ void rc_launch_primary(const DevScene& sc, const DevCamera& cam, uint4* gbuf, co
     const bool two = sc.inst != nullptr, wt = sc.watertight != 0u;
     if (!per_lane && quad_ok(sc, w, P.n_items, QUAD_CAMERA)) {
         const dim3 g(quad_grid(P.n_items, 1));
-        if (wt) hipLaunchKernelGGL((k_quad<MODE_PRIMARY, true>), g, dim3(64), quad_lds(sc), st, P, (uint32_t*)nullptr);
-        else hipLaunchKernelGGL((k_quad<MODE_PRIMARY, false>), g, dim3(64), quad_lds(sc), st, P, (uint32_t*)nullptr);
+        RC_LAUNCH_TW((k_quad<MODE_PRIMARY, RC_TWO, RC_WT>), g, dim3(64), quad_lds(sc), st, P, (uint32_t*)nullptr);
     } else if (sc.max_stack <= 128 && !per_lane && cam.ssaa > 1 && !two && (P.n_items > PRIMARY_WAVE || w.ray_count)) {
         P.claim = claim_size((P.n_items + 63) / 64, grid, 64, 1, 4);
         if (wt)
@@ -907,8 +935,7 @@ void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights&
         P.slot = 1;
         if (quad_point) {
             const dim3 g(quad_grid(P.n_items, (uint32_t)L.n_point));
-            if (wt) hipLaunchKernelGGL((k_quad<MODE_POINT, true>), g, dim3(64), quad_lds(sc), st, P, (uint32_t*)nullptr);
-            else hipLaunchKernelGGL((k_quad<MODE_POINT, false>), g, dim3(64), quad_lds(sc), st, P, (uint32_t*)nullptr);
+            RC_LAUNCH_TW((k_quad<MODE_POINT, RC_TWO, RC_WT>), g, dim3(64), quad_lds(sc), st, P, (uint32_t*)nullptr);
         } else if (wave_point) {
             P.claim = claim_size((uint64_t)((P.n_items + 63) / 64) * (uint64_t)L.n_point, grid, 64, 1, 4);
             if (sc.max_stack <= 64) {
@@ -949,8 +976,7 @@ void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights&
         // pixels, whose rays start close together
         if (quad_rect) {
             const dim3 g(quad_grid((uint64_t)P.n_items * (uint64_t)L.area_samples, 1));
-            if (wt) hipLaunchKernelGGL((k_quad<MODE_RECT, true>), g, dim3(64), quad_lds(sc), st, P, counts);
-            else hipLaunchKernelGGL((k_quad<MODE_RECT, false>), g, dim3(64), quad_lds(sc), st, P, counts);
+            RC_LAUNCH_TW((k_quad<MODE_RECT, RC_TWO, RC_WT>), g, dim3(64), quad_lds(sc), st, P, counts);
         } else if (wave_rect) {
             if (sc.max_stack <= 64) {
                 if (count)

@@ -17,14 +17,15 @@ def scenes():
 
 
 @pytest.mark.parametrize("watertight", [False, True])
-def test_equals_the_per_lane_kernels(watertight):
+@pytest.mark.parametrize("two_level", [False, True])
+def test_equals_the_per_lane_kernels(watertight, two_level):
     import torch
     from paper_2410_05095_amd import _native as N
     ctx = N.Context(0)
     rng = np.random.default_rng(4)
     for scene in scenes():
-        gs = ctx.scene_from(scene).build(watertight=watertight)
-        assert 3 * gs.stats()["depth"] + 1 <= 64
+        gs = ctx.scene_from(scene).build(watertight=watertight, two_level=two_level)
+        assert gs.stats()["max_stack"] <= 128
         lights = np.concatenate([rng.uniform((-3, 1, -3), (3, 9, 3), (5, 3)), np.ones((5, 3))], 1).astype(np.float32)
         for (w, h, ssaa) in ((1, 1, 1), (8, 8, 1), (17, 9, 1), (33, 70, 1), (3, 5, 2), (20, 11, 2)):
             cam = dataclasses.replace(scene.cameras[0], width=w, height=h, ssaa=ssaa)
