@@ -71,6 +71,14 @@ __global__ void k_fill_u32(uint32_t* p, uint32_t value, uint32_t n)
     if (i < n) p[i] = value;
 }
 
+// the counters of a frame (words 0 to 7 and the queues; not the sticky error flags between them): one launch, of the
+// 53 us that a 128x128 frame takes each costs 2 to 3
+__global__ void k_clear_counters(uint32_t* p)
+{
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < 8u || (i >= RC_QUEUE_BASE && i < RC_COUNTER_WORDS)) p[i] = 0u;
+}
+
 // x' = ((R00 x + R01 y) + R02 z) + t0 per row, from the rest positions of body body_ids[blockIdx.y]
 // vertex normals (when present) are rotated the same way, without the translation
 __global__ __launch_bounds__(256) void k_transform(const float* rest, float* pos, const float* nrm_rest, float* nrm,
@@ -337,6 +345,11 @@ void rc_launch_fill_u32(uint32_t* p, uint32_t value, uint32_t n, hipStream_t st)
 {
     if (n == 0) return;
     hipLaunchKernelGGL(k_fill_u32, dim3(blocks(n, 256)), dim3(256), 0, st, p, value, n);
+}
+
+void rc_launch_clear_counters(uint32_t* counters, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_clear_counters, dim3(blocks(RC_COUNTER_WORDS, 256)), dim3(256), 0, st, counters);
 }
 
 void rc_launch_transform(const float* rest, float* pos, const float* nrm_rest, float* nrm,

@@ -769,8 +769,7 @@ int rc_render(rc_ctx* c, rc_scene* s, const rc_camera* cam, const rc_point_light
     w.overflow = c->d_overflow;
 
     hipStream_t q = c->stream;
-    rc_launch_fill_u32(c->d_counters, 0u, 8, q);
-    rc_launch_fill_u32(c->d_counters + RC_QUEUE_BASE, 0u, RC_COUNTER_WORDS - RC_QUEUE_BASE, q);
+    rc_launch_clear_counters(c->d_counters, q);
     // ray, node and triangle counts are gathered on request only (RC_FLAG_COUNT: the wave kernels are compiled
     // without their counters otherwise)
     const bool counting = opts && (opts->flags & RC_FLAG_COUNT);
@@ -1158,8 +1157,7 @@ int batch_launch(rc_ctx* c, rc_scene* const* scenes, uint32_t n_scenes, const rc
             if (c->graph) { hipGraphDestroy(c->graph); c->graph = nullptr; }
             if (!c->capture_stream) RC_HIP(hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking));
             RC_HIP(hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeRelaxed));
-            rc_launch_fill_u32(c->d_counters, 0u, 8, c->capture_stream);   // not word 8: the sticky error flag
-            rc_launch_fill_u32(c->d_counters + RC_QUEUE_BASE, 0u, RC_COUNTER_WORDS - RC_QUEUE_BASE, c->capture_stream);
+            rc_launch_clear_counters(c->d_counters, c->capture_stream);
             rc_launch_fill_u32(reinterpret_cast<uint32_t*>(c->d_rays), 0u, 16, c->capture_stream);
             for (int p = 0; p < 4; ++p)
                 if (grids[p]) rc_launch_batch(P, p, grids[p], c->capture_stream);
@@ -1170,8 +1168,7 @@ int batch_launch(rc_ctx* c, rc_scene* const* scenes, uint32_t n_scenes, const rc
         }
         RC_HIP(hipGraphLaunch(c->graph_exec, c->stream));
     } else {
-        rc_launch_fill_u32(c->d_counters, 0u, 8, c->stream);   // not word 8: the sticky error flag
-        rc_launch_fill_u32(c->d_counters + RC_QUEUE_BASE, 0u, RC_COUNTER_WORDS - RC_QUEUE_BASE, c->stream);
+        rc_launch_clear_counters(c->d_counters, c->stream);
         rc_launch_fill_u32(reinterpret_cast<uint32_t*>(c->d_rays), 0u, 16, c->stream);
         if (t.passes == 1) {
             rc_launch_batch(P, 0, grids[0], c->stream);

@@ -229,6 +229,7 @@ void rc_launch_pack_features(const DevScene& sc, const DevCamera& cam, const uin
                              float inv_log_norm, uint16_t* feat, uint32_t* bad_value, hipStream_t st);
 void rc_launch_pack(const float* pos, const uint32_t* idx, const uint32_t* order, uint32_t n_tris,
                     float4* tris, bool raw, hipStream_t st);
+void rc_launch_clear_counters(uint32_t* counters, hipStream_t st);
 void rc_launch_fill_u32(uint32_t* p, uint32_t value, uint32_t n, hipStream_t st);
 void rc_launch_record_o2w(const float* xf, const uint32_t* body_ids, uint32_t n, uint32_t scene_bodies, float* o2w,
                           hipStream_t st);
