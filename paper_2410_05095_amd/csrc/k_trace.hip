@@ -51,10 +51,11 @@ inline uint32_t claim_size(uint64_t n_work, int grid, uint32_t per_wave, uint32_
     return (uint32_t)std::min<uint64_t>(hi, std::max<uint64_t>(lo, c));
 }
 
-// The flat-tree camera-ray instance is compiled for 6 waves per SIMD (at most 80 registers; 5 waves otherwise),
-// which measured 3% faster (0.701 vs 0.724 ms for 1080p camera rays on 7.3M triangles).
+// Waves per SIMD: 6 for flat-tree camera rays (80 registers; 3% faster than 5), 5 for two-level structures (96; their
+// camera rays at 720p 0.265 ms against 0.283 at the natural 4 and 0.293 at 6, on 1.1M triangles), the compiler's choice
+// elsewhere (flat shadow rays at 6: 2 to 5% slower).
 template <int MODE, bool TWO, bool WT, bool COUNT>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(MODE == MODE_PRIMARY && !TWO && !WT ? 6 : 1))) void k_trace(KParams P)
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WT ? 1 : TWO ? 5 : MODE == MODE_PRIMARY ? 6 : 1))) void k_trace(KParams P)
 {
     constexpr bool ANY = MODE != MODE_PRIMARY;
 
