@@ -159,16 +159,13 @@ __global__ __launch_bounds__(256) void k_mark_dirty(const uint32_t* body_ids, ui
     if (n < n_nodes) dirty[n] = 1u;
 }
 
-// The marked nodes of one level (first .. first + count - 1), four threads per node: thread c recomputes child
-// slot c; thread 0 then clears the node's mark and marks its parent (read by the next launch).
-__global__ __launch_bounds__(256) void k_refit_level_dirty(Node4* nodes, const float* pos, const uint32_t* idx,
-                                                           const uint32_t* order, float4* tris, uint32_t raw,
-                                                           uint32_t* dirty, uint32_t first, uint32_t count,
-                                                           uint32_t n_nodes)
+// Thread c of marked node n's four recomputes child slot c; thread 0 then clears the node's mark and marks its parent
+// (read by the level above).
+__device__ __attribute__((always_inline)) inline void rc_refit_node(Node4* nodes, const float* pos, const uint32_t* idx,
+                                                                    const uint32_t* order, float4* tris, uint32_t raw,
+                                                                    uint32_t* dirty, uint32_t n, uint32_t c,
+                                                                    uint32_t n_nodes)
 {
-    const uint32_t q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q / 4 >= count) return;
-    const uint32_t n = first + q / 4, c = q & 3u;
     if (dirty[n] == 0u) return;
     Node4* nd = nodes + n;
     const uint32_t w = nd->child[c];
@@ -224,6 +221,38 @@ __global__ __launch_bounds__(256) void k_refit_level_dirty(Node4* nodes, const f
         dirty[n] = 0u;
         const uint32_t p = nd->parent;
         if (p < n_nodes) dirty[p] = 1u;   // the root's parent is 0xFFFFFFFF
+    }
+}
+
+// The marked nodes of one level (first .. first + count - 1), four threads per node
+__global__ __launch_bounds__(256) void k_refit_level_dirty(Node4* nodes, const float* pos, const uint32_t* idx,
+                                                           const uint32_t* order, float4* tris, uint32_t raw,
+                                                           uint32_t* dirty, uint32_t first, uint32_t count,
+                                                           uint32_t n_nodes)
+{
+    const uint32_t q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q / 4 < count) rc_refit_node(nodes, pos, idx, order, tris, raw, dirty, first + q / 4, q & 3u, n_nodes);
+}
+
+// Consecutive levels of at most REFIT_SMALL nodes each, from the deepest up, in one workgroup: a level costs its few
+// dependent loads and a barrier instead of a launch.  Frames with moving bodies: 20,000 triangles 128.8 to 123.8 us,
+// 200,000 157.5 to 151.9, 1.1M unchanged (most of its 17 levels are larger).
+constexpr uint32_t REFIT_SMALL = 256;
+constexpr int REFIT_LEVELS = 24;
+struct RefitLevels {
+    uint32_t n;
+    uint32_t first[REFIT_LEVELS], count[REFIT_LEVELS];
+};
+__global__ __launch_bounds__(4 * REFIT_SMALL) void k_refit_small_levels(Node4* nodes, const float* pos, const uint32_t* idx,
+                                                                        const uint32_t* order, float4* tris, uint32_t raw,
+                                                                        uint32_t* dirty, RefitLevels levels,
+                                                                        uint32_t n_nodes)
+{
+    const uint32_t q = threadIdx.x;
+    for (uint32_t l = 0; l < levels.n; ++l) {
+        if (q / 4 < levels.count[l])
+            rc_refit_node(nodes, pos, idx, order, tris, raw, dirty, levels.first[l] + q / 4, q & 3u, n_nodes);
+        __syncthreads();
     }
 }
 
@@ -397,11 +426,26 @@ void rc_launch_refit_dirty(Node4* nodes, const float* pos, const uint32_t* idx, 
 {
     const int depth = (int)level_start.size() - 1;
     const uint32_t n_nodes = level_start[depth];
+    RefitLevels small = {};
+    auto flush = [&]() {
+        if (small.n)
+            hipLaunchKernelGGL(k_refit_small_levels, dim3(1), dim3(4 * REFIT_SMALL), 0, st, nodes, pos, idx, order, tris,
+                               raw ? 1u : 0u, dirty, small, n_nodes);
+        small.n = 0;
+    };
     for (int lv = depth - 1; lv >= 0; --lv) {
         const uint32_t first = level_start[lv], count = level_start[lv + 1] - level_start[lv];
         if (count == 0) continue;
+        if (count <= REFIT_SMALL) {
+            small.first[small.n] = first;
+            small.count[small.n++] = count;
+            if (small.n == REFIT_LEVELS) flush();
+            continue;
+        }
+        flush();
         hipLaunchKernelGGL(k_refit_level_dirty, dim3(blocks(4 * (size_t)count, 256)), dim3(256), 0, st, nodes, pos, idx,
                            order, tris, raw ? 1u : 0u, dirty, first, count, n_nodes);
     }
+    flush();
 }
 
