@@ -250,18 +250,21 @@ enum {
                                   1) = 3.5M and rect-light shadow rays from 3M rays per frame; BVH depth <=
                                   42, under 2^25 nodes and 2^32 bytes of packed triangles) or four lanes
                                   to a ray (passes of up to 600,000 camera or point-light rays, 950,000
-                                  rect-light rays); same results outside the FP32 band, for comparison */
+                                  rect-light rays); same results outside the FP32 band, for comparison.
+                                  rc_render_batch: the three-pass form's shadow rays one ray per lane (its
+                                  results are the same either way; takes precedence over RC_FLAG_WAVE) */
     RC_FLAG_NO_SHADE = 8u,     /* rc_render: stop after the visibility stages; d_rgba and d_sample_rgba are
                                   left untouched (for a caller that shades later with rc_shade, e.g. from a
                                   denoised visibility) */
     RC_FLAG_COUNT = 16u,       /* rc_render: count rays cast, nodes visited and triangles tested
                                   (rc_get_stage_times); without it the traversal kernels run without their
                                   counters, and small passes four lanes to a ray (with it: one) */
-    RC_FLAG_WAVE = 32u         /* rc_render, rc_render_batch with three passes: shadow rays through the wave-uniform kernels (where the BVH
+    RC_FLAG_WAVE = 32u         /* rc_render: shadow rays through the wave-uniform kernels (where the BVH
                                   allows them) also for passes below the sizes above, which by default go
-                                  one ray per lane or four lanes to a ray: a small pass lasts as long as its most divergent wave's
-                                  walk.  Same results outside the FP32 band.  With RC_FLAG_PER_LANE:
-                                  RC_ERR_INVALID_ARG */
+                                  one ray per lane or four lanes to a ray: a small pass lasts as long as its
+                                  most divergent wave's walk.  Same results outside the FP32 band.  With
+                                  RC_FLAG_PER_LANE: RC_ERR_INVALID_ARG.  rc_render_batch: the same for the
+                                  three-pass form, with the same results */
 };
 
 typedef struct rc_render_opts {
@@ -397,9 +400,10 @@ enum {
 /* Render all views in persistent launches fed by device work queues (point lights and 2x2 or 1
  * sample per pixel): one launch, or one per stage (rc_tune.passes); with RC_FLAG_GRAPH one graph launch
  * either way.  Every view's outputs are bit-identical to rc_render of that view
- * alone with RC_FLAG_PER_LANE (the same triangle tests and per-lane camera rays; the three-kernel form's shadow rays
- * may take the wave-uniform walk, as rc_render's do, which returns the same masks outside the FP32 band), for any
- * tuning.  flags: RC_FLAG_TIMING (rc_get_stage_times ms[3]; with three passes and no graph also ms[0..2] per pass), RC_FLAG_COUNT (its counts: all rays in [0] for one pass, camera and shadow rays in [0] and [1] for three), RC_FLAG_GRAPH.  All
+ * alone with RC_FLAG_PER_LANE, for any tuning (three passes: the shadow rays of large batches, or with RC_FLAG_WAVE of
+ * any, are traced by wave-uniform walks that decide each ray as the per-lane walk does).  flags: RC_FLAG_TIMING
+ * (rc_get_stage_times ms[3]; with three passes and no graph also ms[0..2] per pass), RC_FLAG_COUNT (its counts: all rays
+ * in [0] for one pass, camera and shadow rays in [0] and [1] for three), RC_FLAG_GRAPH, RC_FLAG_PER_LANE, RC_FLAG_WAVE.  All
  * scenes must be built (flat BVHs: two-level structures give RC_ERR_UNSUPPORTED).  Errors:
  * RC_ERR_INVALID_ARG, RC_ERR_NOT_BUILT, RC_ERR_UNSUPPORTED, RC_ERR_HIP. */
 int rc_render_batch(rc_ctx* ctx, rc_scene* const* scenes, uint32_t n_scenes, const rc_view* views, uint32_t n_views,

@@ -1064,9 +1064,10 @@ int batch_launch(rc_ctx* c, rc_scene* const* scenes, uint32_t n_scenes, const rc
     int grids[4] = {0, 0, 0, 0};
     // The shadow pass of the three-kernel form by wave-uniform walks where a single view of as many segments would
     // take them (rc_launch_shadow; shadow pass per lane / wave-uniform: 2 views with 4.9M segments 0.53 / 0.32 ms, 12
-    // views with 17.1M 3.33 / 1.46 ms, 64 views with 97.2M 14.96 / 9.98 ms).  An untuned or largest waves_per_simd
-    // gives that kernel its own largest grid.
-    const bool wave = t.passes == 3 && bp.wave_ok && bp.n_units > 0 && bp.n_units < (1ull << 32) &&
+    // views with 17.1M 3.33 / 1.46 ms, 64 views with 97.2M 14.98 / 10.5 ms).  The masks are the same either way.  An
+    // untuned or largest waves_per_simd gives that kernel its own largest grid.
+    const bool wave = t.passes == 3 && !(flags & RC_FLAG_PER_LANE) && bp.wave_ok && bp.n_units > 0 &&
+                      bp.n_units < (1ull << 32) &&
                       (bp.wave_work >= RC_WAVE_WORK || (flags & RC_FLAG_WAVE));
     for (int p = 0; p < 4; ++p)
         if ((p == 0) == (t.passes == 1))

@@ -123,6 +123,47 @@ __device__ inline void wave_keys_mixed(const rc_v4f& lx, const rc_v4f& hx, const
     }
 }
 
+// EXACT walks return the per-lane walk's answer for every ray, not only outside the FP32 band.  The per-lane walk
+// tests exactly the triangles of the leaves whose own box rc_slab accepts: the boxes nest, an FMA with a fixed factor
+// and addend is monotone in the plane, so rc_slab accepts every box around one that it accepts.  A wave also tests
+// triangles of leaves that only other lanes enter, and an FP32 triangle test can report a hit a little outside
+// the box.  So
+//  - the walk enters every box that rc_slab accepts: wave_ray_exact doubles the margins of rc_slab_seg's constants,
+//    which lie within 14 ulp of it otherwise (its entry is then at most rc_slab's, and below it when that is
+//    above 0; its exit is above rc_slab's);
+//  - a triangle hit counts once rc_slab, with its own constants, has accepted the leaf's box (rc_enters): a few
+//    leaves per walk, found through the node that each stack entry came from.
+__device__ inline void wave_ray_exact(TravRay& r)
+{
+    rc_ray_inv<true>(r);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        r.cn[a] -= fabsf(r.cn[a]) * 0x1p-21f + 0x1p-120f;
+        r.cf[a] += fabsf(r.cf[a]) * 0x1p-21f + 0x1p-120f;
+    }
+}
+
+// Whether the per-lane walk's box test (rc_slab, segment 0 <= t <= 1) lets the ray into the child `w` of a node.
+__device__ inline bool rc_enters(const char* node, uint32_t w, const TravRay& ray)
+{
+    typedef const __attribute__((address_space(4))) float c_float;
+    const rc_v4u ch = *(rc_const_v4u*)(const void*)(node + 96);
+    const char* lo = node + (ch[0] == w ? 0u : ch[1] == w ? 4u : ch[2] == w ? 8u : 12u);
+    TravRay q;
+    float n[3], f[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) { q.o[a] = ray.o[a]; q.d[a] = ray.d[a]; }
+    rc_ray_inv(q);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float l = *(c_float*)(const void*)(lo + 32 * a), h = *(c_float*)(const void*)(lo + 32 * a + 16);
+        n[a] = q.inv[a] >= 0.0f ? l : h;
+        f[a] = q.inv[a] >= 0.0f ? h : l;
+    }
+    float t0;
+    return rc_slab(q, q.invf, n[0], n[1], n[2], f[0], f[1], f[2], 1.0f, t0);
+}
+
 // Two-level structures: at a top-level leaf every lane maps its ray into the instance (rc_map_ray), the
 // wave pushes an end marker and descends into the instance's tree; popping the marker restores the world
 // rays (and the wave's octant).
@@ -132,7 +173,7 @@ __device__ inline void wave_keys_mixed(const rc_v4f& lx, const rc_v4f& hx, const
 // plane blocks come with three 32-byte loads at constant offsets and the near/far choice is made when
 // compiling; 8: mixed octants (each lane picks its planes); -1: decided at run time, per instance for
 // two-level structures (the mapped rays' octant changes at each instance).
-template <bool WT, bool BIG, bool CLAMP, bool COUNT>
+template <bool WT, bool BIG, bool CLAMP, bool COUNT, bool EXACT = false>
 __device__ __attribute__((always_inline)) inline uint32_t wave_walk_flat(const DevScene& sc, const char* nodes_b,
                                                                        const char* tris_b, TravRay& ray, bool busy,
                                                                        uint32_t& node_visits, uint32_t& tri_tests,
@@ -142,7 +183,8 @@ __device__ __attribute__((always_inline)) inline uint32_t wave_walk_flat(const D
 // instead of 12); otherwise rc_slab with a bound per lane (two-level structures and the watertight test, whose
 // walks hold more registers and measured slower with the muting)
 // COUNT: the walk counts node visits and triangle tests of live lanes (frames timed by stage report them)
-template <bool TWO, bool WT, bool BIG, int OCT, bool CLAMP, bool COUNT>
+// EXACT: the per-lane walk's decisions (see wave_ray_exact; flat trees)
+template <bool TWO, bool WT, bool BIG, int OCT, bool CLAMP, bool COUNT, bool EXACT = false>
 __device__ __attribute__((always_inline)) inline uint32_t wave_walk(const DevScene& sc, const char* nodes_b,
                                                                   const char* tris_b, TravRay& ray, bool busy,
                                                                   uint32_t& node_visits, uint32_t& tri_tests,
@@ -178,19 +220,24 @@ __device__ __attribute__((always_inline)) inline uint32_t wave_walk(const DevSce
     uint32_t cur = busy_mask != 0 ? (TWO ? sc.tlas_root : root) : RC_STACK_EMPTY;
     int sp = 0;
     uint32_t stk0 = 0, stk1 = 0;   // entry e of the wave's stack lives in lane e % 64 of stk{e / 64}
+    uint32_t up0 = 0, up1 = 0;     // EXACT: the node that holds each entry's child word
+    uint32_t up = 0;               // EXACT: the node that holds `cur`, or ~0 if it was popped (then entry sp's)
     // next entry of the wave's stack
     auto pop_next = [&]() -> uint32_t {
         if (sp == 0) return RC_STACK_EMPTY;
         --sp;
+        if constexpr (EXACT) up = 0xFFFFFFFFu;
         return BIG ? (uint32_t)__builtin_amdgcn_readlane((int)(sp < 64 ? stk0 : stk1), sp & 63)
                    : (uint32_t)__builtin_amdgcn_readlane((int)stk0, sp);
     };
     auto push_entry = [&](uint32_t w) {
         if (sp < 64) {
             stk0 = (uint32_t)rc_writelane((int)w, sp, (int)stk0);
+            if constexpr (EXACT) up0 = (uint32_t)rc_writelane((int)cur, sp, (int)up0);
             ++sp;
         } else if (BIG && sp < 128) {
             stk1 = (uint32_t)rc_writelane((int)w, sp - 64, (int)stk1);
+            if constexpr (EXACT) up1 = (uint32_t)rc_writelane((int)cur, sp - 64, (int)up1);
             ++sp;
         } else if (lane == 0) {
             *error_flag = 1u;   // beyond the bound the host checked: entry dropped, reported
@@ -243,6 +290,7 @@ __device__ __attribute__((always_inline)) inline uint32_t wave_walk(const DevSce
                 for (int c = 3; c >= 1; --c)
                     if (key[c] < RC_KEY_MISS) {
                         stk0 = (uint32_t)rc_writelane((int)child(key[c]), sp, (int)stk0);
+                        if constexpr (EXACT) up0 = (uint32_t)rc_writelane((int)cur, sp, (int)up0);
                         ++sp;
                     }
             } else {
@@ -250,6 +298,7 @@ __device__ __attribute__((always_inline)) inline uint32_t wave_walk(const DevSce
                 for (int c = 3; c >= 1; --c)
                     if (key[c] < RC_KEY_MISS) push_entry(child(key[c]));
             }
+            if constexpr (EXACT) up = cur;
             cur = key[0] < RC_KEY_MISS ? child(key[0]) : pop_next();
         } else if (TWO) {
             // top-level leaf: every ray mapped into the instance, whose tree the flat walk takes (compiled for
@@ -284,6 +333,15 @@ __device__ __attribute__((always_inline)) inline uint32_t wave_walk(const DevSce
                                     : rc_mt_segment(ray, A.x, A.y, A.z, B.x, B.y, B.z, C.x, C.y, C.z);
                 o |= hit ? 1u : 0u;
             }
+            if constexpr (EXACT) {
+                const uint32_t fresh = o ^ occ;
+                if (__ballot(fresh != 0u) != 0) {
+                    const uint32_t e = BIG && sp >= 64 ? (uint32_t)__builtin_amdgcn_readlane((int)up1, sp - 64)
+                                                       : (uint32_t)__builtin_amdgcn_readlane((int)up0, sp & 63);
+                    const char* node = nodes_b + ((up != 0xFFFFFFFFu ? up : e) << 7);
+                    o = occ | (rc_enters(node, cur, ray) ? fresh : 0u);
+                }
+            }
             occ = o;
             live &= o ^ 1u;
             if constexpr (CLAMP) wave_mute(ray, live, true);
@@ -297,8 +355,9 @@ __device__ __attribute__((always_inline)) inline uint32_t wave_walk(const DevSce
 
 // Any-hit traversal of the segments o + t d, 0 <= t <= 1, of a wave's rays (called by all 64 lanes; busy
 // lanes hold a ray whose traversal constants rc_ray_inv set): returns 1 in the lanes whose segment is
-// occluded.  Flat trees: one walk specialised for the wave's octant, or for mixed octants.
-template <bool TWO, bool WT, bool BIG, bool COUNT>
+// occluded.  Flat trees: one walk specialised for the wave's octant, or for mixed octants.  EXACT: constants
+// set by wave_ray_exact, the per-lane walk's answers.
+template <bool TWO, bool WT, bool BIG, bool COUNT, bool EXACT = false>
 __device__ __attribute__((always_inline)) inline uint32_t wave_occluded(const DevScene& sc, const char* nodes_b,
                                                                       const char* tris_b, TravRay& ray, bool busy,
                                                                       uint32_t& node_visits, uint32_t& tri_tests,
@@ -308,21 +367,21 @@ __device__ __attribute__((always_inline)) inline uint32_t wave_occluded(const De
         return wave_walk<TWO, WT, BIG, -1, false, COUNT>(sc, nodes_b, tris_b, ray, busy, node_visits, tri_tests, error_flag,
                                                         0u);
     else
-        return wave_walk_flat<WT, BIG, !WT, COUNT>(sc, nodes_b, tris_b, ray, busy, node_visits, tri_tests, error_flag, 0u);
+        return wave_walk_flat<WT, BIG, !WT, COUNT, EXACT>(sc, nodes_b, tris_b, ray, busy, node_visits, tri_tests, error_flag, 0u);
 }
 
 // The flat walk from node `root`, compiled once per direction octant of the busy rays and once for mixed
 // octants.  For two-level structures it walks an instance's tree with a one-register stack: the host takes
 // the wave kernels only when 3 x (deepest instance tree + 24) + 2 <= 128, so an instance tree is at most 18
 // levels deep and its walk needs at most 55 stack entries.
-template <bool WT, bool BIG, bool CLAMP, bool COUNT>
+template <bool WT, bool BIG, bool CLAMP, bool COUNT, bool EXACT>
 __device__ __attribute__((always_inline)) inline uint32_t wave_walk_flat(const DevScene& sc, const char* nodes_b,
                                                                        const char* tris_b, TravRay& ray, bool busy,
                                                                        uint32_t& node_visits, uint32_t& tri_tests,
                                                                        uint32_t* error_flag, uint32_t root)
 {
 #define RC_WALK(o) \
-    wave_walk<false, WT, BIG, o, CLAMP, COUNT>(sc, nodes_b, tris_b, ray, busy, node_visits, tri_tests, error_flag, root)
+    wave_walk<false, WT, BIG, o, CLAMP, COUNT, EXACT>(sc, nodes_b, tris_b, ray, busy, node_visits, tri_tests, error_flag, root)
     const uint64_t busy_mask = __ballot(busy);
     const uint32_t my_oct = (ray.inv[0] < 0.0f ? 1u : 0u) | (ray.inv[1] < 0.0f ? 2u : 0u) |
                             (ray.inv[2] < 0.0f ? 4u : 0u);
