@@ -442,7 +442,7 @@ int rc_denoiser_infer(rc_ctx* ctx, rc_denoiser* den, const uint16_t* d_features,
                       float* d_out);
 /* The same network evaluated in FP32 from the FP32 master weights (FP32 activations and accumulation,
  * the BF16 features as input): the full-precision copy that the BF16 inference is compared against.
- * Arguments as rc_denoiser_infer. */
+ * Arguments as rc_denoiser_infer, but d_out may have any address (one that is not 4-byte aligned costs a copy). */
 int rc_denoiser_infer_fp32(rc_ctx* ctx, rc_denoiser* den, const uint16_t* d_features, uint32_t n, uint32_t h,
                            uint32_t w, float* d_out);
 /* One Adam step (beta 0.9/0.999, eps 1e-8, bias-corrected) on the loss

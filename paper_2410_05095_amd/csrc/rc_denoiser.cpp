@@ -277,9 +277,12 @@ int forward_f32(rc_denoiser* d, const uint16_t* x, int n, int h, int w, float* y
     conv_f32(d, F + d->f_d2a, n, h2, w2, D2B, F + d->f_d2b, st);
     conv_f32(d, F + d->f_d2b, n, h, w, D1A, F + d->f_d1a, st, F + d->f_e1b, 64);
     conv_f32(d, F + d->f_d1a, n, h, w, D1B, F + d->f_d1b, st);
-    unet_head_f32(F + d->f_d1b, d->d_w + d->off_w[N_LAYERS], d->d_w + d->off_b[N_LAYERS], n * h * w, y_out,
-                  st);
+    // the head stores whole floats: an address that is no multiple of 4 gets its bytes by a copy from the workspace (the
+    // first layer's output, read by no one any more)
+    float* y = (reinterpret_cast<uintptr_t>(y_out) & 3u) ? F + d->f_e1a : y_out;
+    unet_head_f32(F + d->f_d1b, d->d_w + d->off_w[N_LAYERS], d->d_w + d->off_b[N_LAYERS], n * h * w, y, st);
     DN_HIP(hipGetLastError());
+    if (y != y_out) DN_HIP(hipMemcpyAsync(y_out, y, (size_t)n * h * w * 4, hipMemcpyDeviceToDevice, st));
     return RC_OK;
 }
 
