@@ -12,6 +12,7 @@
 // descent (nearest child first) for closest hits; per-lane stack of (node, entry distance)
 // in LDS with a lane-interleaved global overflow area.  Triangles: Moller-Trumbore in FP32.
 #include <algorithm>
+#include <cmath>
 
 #include "rc_wave.h"
 
@@ -372,19 +373,20 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TWO || WT
 }
 
 // Point-light shadow rays, wave-uniform traversal.  A unit of work is 64 consecutive samples (neighbouring
-// pixels) and one light: the wave walks the tree once, each lane casting its sample's segment to the light where
-// that lies above the surface, with the same tests and results as the per-lane kernel.  Mask bit l of a sample
-// (cleared by the setup pass): the ray to light l is cast and not occluded.  The pass cannot end before its longest
-// walk, so the lights of a packet are separate units instead of walks in turn of one wave (4 lights: the 64
-// samples that diverge most take a quarter of the time; figures at rc_launch_shadow).
-template <bool TWO, bool WT, bool BIG, bool COUNT>
+// pixels) and one light, or with TURN and all lights: the wave walks the tree once per light, each lane casting its
+// sample's segment to the light where that lies above the surface, with the same tests and results as the per-lane
+// kernel.  Mask bit l of a sample (cleared by the setup pass unless TURN): the ray to light l is cast and not occluded.  The pass cannot end before its longest unit, so the lights of a packet are units
+// of their own (4 lights: the 64 samples that diverge most take a quarter of the time) unless the pass is so long that
+// the number of claims and the repeated set-up cost more (point_lights_in_turn).  An instance for each: with the loop
+// over the lights the watertight kernel takes 66 registers instead of 60, 7 waves per SIMD instead of 8 (8% slower).
+template <bool TWO, bool WT, bool BIG, bool COUNT, bool TURN>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TWO || WT ? 1 : 8))) void k_point_wave(KParams P, const float4* setup)
 {
     const uint32_t lane = __lane_id();
     const DevScene sc = P.sc;
     const uint32_t spp = (uint32_t)(P.cam.ssaa * P.cam.ssaa);
     const uint32_t n_l = (uint32_t)P.L.n_point;
-    const uint64_t n_units = (uint64_t)((P.n_items + 63u) / 64u) * n_l;
+    const uint64_t n_units = (uint64_t)((P.n_items + 63u) / 64u) * (TURN ? 1u : n_l);
     uint32_t rays_cast = 0, node_visits = 0, tri_tests = 0;
     const char* nodes_b = (const char*)(const void*)sc.nodes;
     const char* tris_b = (const char*)(const void*)sc.tris;
@@ -399,28 +401,54 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TWO || WT
         if (queue.exhausted(j)) break;
         const uint64_t unit = queue.at(j);
         if (unit >= n_units) continue;
-        const uint32_t blk = (uint32_t)unit / n_l, l = (uint32_t)unit - blk * n_l;
+        const uint32_t blk = TURN ? (uint32_t)unit : (uint32_t)unit / n_l, l0 = TURN ? 0u : (uint32_t)unit - blk * n_l;
         const uint32_t item = blk * 64u + lane;
         uint32_t px = 0, pk = 0;
         const bool in_image = item < P.n_items && rc_item_to_sample(P.cam, item, px, pk);
         const size_t smp = (size_t)px * spp + pk;
-        TravRay ray;
-        bool busy = false;
+        if constexpr (!TURN) {
+            TravRay ray;
+            bool busy = false;
+            if (in_image) {
+                const float4 a = setup[2 * smp], b = setup[2 * smp + 1];
+                if (a.w != 0.0f) {
+                    float os[3] = {a.x, a.y, a.z}, nf[3] = {b.x, b.y, b.z};
+                    busy = rc_shadow_ray(P.L.point[l0], P.L.rect, P.nL, false, px, l0, P.L.area_stream, P.cam.seed,
+                                         P.cam.frame, os, nf, ray);
+                    if (busy) {
+                        rc_ray_inv<!TWO && !WT>(ray);   // the flat Moller-Trumbore walk takes the clamped slab test
+                        ++rays_cast;
+                    }
+                }
+            }
+            const uint32_t occ = wave_occluded<TWO, WT, BIG, COUNT>(sc, nodes_b, tris_b, ray, busy, node_visits, tri_tests,
+                                                             P.w.error_flag);
+            if (busy && occ == 0u) atomicOr(P.mask + smp, 1u << l0);
+            continue;
+        }
+        float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f), b = a;
         if (in_image) {
-            const float4 a = setup[2 * smp], b = setup[2 * smp + 1];
+            a = setup[2 * smp];
+            b = setup[2 * smp + 1];
+        }
+        const float os[3] = {a.x, a.y, a.z}, nf[3] = {b.x, b.y, b.z};
+        uint32_t mask = 0;
+        for (uint32_t l = 0; l < n_l; ++l) {
+            TravRay ray;
+            bool busy = false;
             if (a.w != 0.0f) {
-                float os[3] = {a.x, a.y, a.z}, nf[3] = {b.x, b.y, b.z};
                 busy = rc_shadow_ray(P.L.point[l], P.L.rect, P.nL, false, px, l, P.L.area_stream, P.cam.seed,
                                      P.cam.frame, os, nf, ray);
                 if (busy) {
-                    rc_ray_inv<!TWO && !WT>(ray);   // the flat Moller-Trumbore walk takes the clamped slab test
+                    rc_ray_inv<!TWO && !WT>(ray);
                     ++rays_cast;
                 }
             }
+            const uint32_t occ = wave_occluded<TWO, WT, BIG, COUNT>(sc, nodes_b, tris_b, ray, busy, node_visits, tri_tests,
+                                                             P.w.error_flag);
+            if (busy && occ == 0u) mask |= 1u << l;
         }
-        const uint32_t occ = wave_occluded<TWO, WT, BIG, COUNT>(sc, nodes_b, tris_b, ray, busy, node_visits, tri_tests,
-                                                         P.w.error_flag);
-        if (busy && occ == 0u) atomicOr(P.mask + smp, 1u << l);
+        if (in_image) P.mask[smp] = mask;
     }
     if (P.w.ray_count) {
         unsigned long long cnt[3] = {rays_cast, node_visits, tri_tests};
@@ -844,7 +872,7 @@ int rc_trace_grid(int device)
         blocks_per_cu(reinterpret_cast<const void*>(&k_rect_packets<false, false, false>), TravStack<SL, BLOCK, false>::lds_bytes()),
         blocks_per_cu(reinterpret_cast<const void*>(&k_rect_wave<false, false, false, false>), 0),
         blocks_per_cu(reinterpret_cast<const void*>(&k_primary_wave<false>), 0),
-        blocks_per_cu(reinterpret_cast<const void*>(&k_point_wave<false, false, false, false>), 0)};
+        blocks_per_cu(reinterpret_cast<const void*>(&k_point_wave<false, false, false, false, false>), 0)};
     int b = 1;
     for (int x : blocks) b = std::max(b, x);
     return cu_count(device) * b;
@@ -884,6 +912,22 @@ void rc_launch_primary(const DevScene& sc, const DevCamera& cam, uint4* gbuf, co
     }
 }
 
+// Whether a packet's lights are walked in turn by one wave, one claim and one set-up for all of them, instead of as units
+// of their own.  A claim is an atomic on one of eight counters, and these pass about 0.5 claims per ns: a pass of U
+// units takes at least 2 U ns, which short walks (small trees) do not.  Against that stands the tail, a packet's
+// walks one after another.  Separate units / in turn (ms), 2, 4 and 8 lights:
+//     20K triangles  2.07M samples 0.19 / 0.21, 0.28 / 0.35, 0.51 / 0.59; 3.7M 0.27 / 0.25, 0.46 / 0.33, 0.86 / 0.53
+//    200K            2.07M 0.75, 0.66, 0.52 of in turn; 3.7M 1.05, 1.02, 0.87; 5.0M 1.11, 1.12, 1.08; 8.3M 1.22, 1.43, 1.56
+//    500K            3.7M 0.79, 0.84, 0.75; 6.5M 0.82, 1.01, 1.04; 8.3M 1.04, 1.11, 1.11; 14.7M 1.18, 1.40, 1.01
+//    1.1M            5.0M 0.87, 0.87, 0.86; 6.5M 0.95, 0.92, 0.94; 8.3M 0.82, 1.02, 1.08; 14.7M 1.08, 1.24, 1.04
+//    7.3M            8.3M 1.03, 0.94, 0.88; 14.7M 1.05, 1.08, 0.98
+// so the line lies at 2.5M samples for 20K triangles and moves out with the fourth root of their number (watertight
+// tests and two-level structures cross within a tenth of the same places).
+static bool point_lights_in_turn(const DevScene& sc, uint64_t n_samples)
+{
+    return (double)n_samples >= 2.5e6 * std::sqrt(std::sqrt((double)sc.n_tris / 20000.0));
+}
+
 void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights& L, const uint4* gbuf,
                       uint32_t* mask, float* visibility, uint32_t* counts, float4* setup, const TraceWork& w,
                       int grid, RcKernels kernels, hipStream_t st)
@@ -921,6 +965,7 @@ void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights&
     // one unit of work per sample and light in the per-lane kernel too, where the unit count fits 32 bits
     const bool split = L.n_point > 1 && (uint64_t)P.n_items * (uint64_t)L.n_point < (1ull << 31);
     P.light_groups = split ? (uint32_t)L.n_point : 1u;
+    const bool turn = L.n_point > 1 && point_lights_in_turn(sc, n_samples_img);   // wave-uniform
     const bool quad_point = kernels == RC_KERNELS_AUTO && quad_ok(sc, w, (uint64_t)P.n_items * (uint64_t)L.n_point, QUAD_POINT);
     const bool quad_rect = kernels == RC_KERNELS_AUTO && L.has_rect &&
                            quad_ok(sc, w, (uint64_t)P.n_items * (uint64_t)L.area_samples, QUAD_RECT);
@@ -930,7 +975,7 @@ void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights&
         // reads its rays' origins and normals from there
         const uint32_t n_samples = (uint32_t)(cam.width * cam.height * cam.ssaa * cam.ssaa);
         hipLaunchKernelGGL(k_shadow_setup, dim3((n_samples + 255) / 256), dim3(256), 0, st, sc, cam, gbuf, n_samples,
-                           setup, L.n_point > 0 && (wave_point || quad_point || split) ? mask : nullptr);
+                           setup, L.n_point > 0 && (quad_point || (wave_point ? !turn : split)) ? mask : nullptr);
     }
     if (L.n_point > 0) {
         P.slot = 1;
@@ -938,22 +983,24 @@ void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights&
             const dim3 g(quad_grid(P.n_items, (uint32_t)L.n_point));
             RC_LAUNCH_TW((k_quad<MODE_POINT, RC_TWO, RC_WT>), g, dim3(64), quad_lds(sc), st, P, (uint32_t*)nullptr);
         } else if (wave_point) {
-            P.claim = claim_size((uint64_t)((P.n_items + 63) / 64) * (uint64_t)L.n_point, grid, 64, 1, 4);
+            P.claim = claim_size((uint64_t)((P.n_items + 63) / 64) * (turn ? 1u : (uint64_t)L.n_point), grid, 64, 1, 4);
+#define RC_POINT_WAVE(BIG_, COUNT_)                                                                                        \
+    do {                                                                                                               \
+        if (turn)                                                                                                      \
+            RC_LAUNCH_TW((k_point_wave<RC_TWO, RC_WT, BIG_, COUNT_, true>), dim3(grid), dim3(BLOCK), 0, st, P,         \
+                         (const float4*)setup);                                                                        \
+        else                                                                                                           \
+            RC_LAUNCH_TW((k_point_wave<RC_TWO, RC_WT, BIG_, COUNT_, false>), dim3(grid), dim3(BLOCK), 0, st, P,        \
+                         (const float4*)setup);                                                                        \
+    } while (0)
             if (sc.max_stack <= 64) {
-                if (count)
-                    RC_LAUNCH_TW((k_point_wave<RC_TWO, RC_WT, false, true>), dim3(grid), dim3(BLOCK), 0, st, P,
-                                 (const float4*)setup);
-                else
-                    RC_LAUNCH_TW((k_point_wave<RC_TWO, RC_WT, false, false>), dim3(grid), dim3(BLOCK), 0, st, P,
-                                 (const float4*)setup);
+                if (count) RC_POINT_WAVE(false, true);
+                else RC_POINT_WAVE(false, false);
             } else {
-                if (count)
-                    RC_LAUNCH_TW((k_point_wave<RC_TWO, RC_WT, true, true>), dim3(grid), dim3(BLOCK), 0, st, P,
-                                 (const float4*)setup);
-                else
-                    RC_LAUNCH_TW((k_point_wave<RC_TWO, RC_WT, true, false>), dim3(grid), dim3(BLOCK), 0, st, P,
-                                 (const float4*)setup);
+                if (count) RC_POINT_WAVE(true, true);
+                else RC_POINT_WAVE(true, false);
             }
+#undef RC_POINT_WAVE
         } else {
             P.claim = claim_size((uint64_t)P.n_items * P.light_groups, grid, 16, 32, 128);
             if (count)
