@@ -800,26 +800,32 @@ template <int MODE>
 constexpr size_t lds_bytes() { return TravStack<SL, BLOCK, MODE == MODE_PRIMARY>::lds_bytes(); }
 
 // Small passes go four lanes to a ray (k_quad): stacks up to 128 entries in LDS, nodes at 32-bit offsets, nothing
-// counted.  The limits lie where the chip is full and the quad's extra instructions per ray
-// begin to cost.  Four lanes / one lane per ray (ms), on 1.1M triangles (7.3M in brackets):
-//   camera rays         16K 0.051 / 0.093 (0.086 / 0.154), 230K 0.089 / 0.148 (0.130 / 0.206), 0.52M 0.133 / 0.155
-//                       (0.201 / 0.233), 0.92M 0.184 / 0.195 (0.291 / 0.262), 2.07M 0.341 / 0.254 (0.515 / 0.382)
-//   point lights        16K 0.056 / 0.113 (0.088 / 0.182), 0.46M 0.160 / 0.259 (0.248 / 0.278), 0.72M 0.221 / 0.273
-//                       (0.352 / 0.315), 0.92M 0.302 / 0.291 (0.428 / 0.343)
-//   rect light          16K 0.074 / 0.174 (0.122 / 0.251), 0.72M 0.201 / 0.225 (0.285 / 0.330), 0.92M 0.203 / 0.226
-//                       (0.296 / 0.322), 1.23M 0.285 / 0.240 (0.353 / 0.410)
-// with trees of SAH or LBVH builds, whose stacks let 20 waves or more on a CU.  With deeper stacks, as of two-level
-// structures, in proportion to the waves that fit; there, 1.1M triangles: camera rays 16K 0.102 / 0.145, 230K 0.193 /
-// 0.202; one point light 16K 0.084 / 0.168, 230K 0.212 / 0.234; rect light 130K 0.141 / 0.253, 230K 0.203 / 0.241, 0.52M
-// 0.350 / 0.268.
-constexpr uint64_t QUAD_CAMERA = 600000, QUAD_POINT = 600000, QUAD_RECT = 950000;
+// counted.  The limits lie where the chip is full and the quad's extra instructions per ray begin to cost: later in
+// small trees, whose nodes stay in the L2, and early for camera rays of large two-level structures, whose rays go
+// through many bodies.  Time four lanes to a ray over one lane to a ray:
+//   flat, 1.1M triangles (7.3M): camera rays 0.20M 0.65 (0.62), 0.39M 0.82 (0.81), 0.58M 0.87 (0.86), 0.92M 1.00 (1.01), of an
+//       LBVH 0.58M 1.08 (0.91); point lights 0.31M 0.69 (0.76), 0.61M 0.92 (0.97), LBVH 1.04 (0.97); rect light 0.61M
+//       0.68 (0.98), 0.77M 0.71 (1.12), 0.92M 0.76 to 1.05 (1.03 to 1.22)
+//   flat, 20K triangles (200K): camera rays 0.92M 0.51 (0.63); point lights 0.58M 0.47 (0.63); rect light 0.92M 0.68 (0.70)
+//   two-level, 1.1M (7.3M): camera rays 0.12M 0.88 (1.03), 0.15M 0.99 (0.97), 0.20M 1.07 (1.08), 0.31M 1.42 (1.39); point lights
+//       0.31M 0.88 to 1.07 (0.96 to 1.02), 0.39M 1.00 (1.16); rect light 0.31M 0.74 to 0.86 (0.94 to 1.02), 0.46M 0.90 (1.07)
+//   two-level, 20K (200K): camera rays 0.31M 0.63 (0.73); point lights 0.31M 0.61 (0.83); rect light 0.31M 0.71 (0.66)
+// Stacks that leave LDS for fewer than 20 waves on a CU, as of two-level structures: in proportion to the waves that fit
+// (330K rays at 11).
+constexpr uint64_t QUAD_RAYS = 600000;
+uint64_t quad_limit(const DevScene& sc, int mode)
+{
+    if (mode == MODE_PRIMARY && sc.inst && sc.n_tris >= 600000u) return 180000;
+    if (mode == MODE_RECT) return sc.n_tris >= 3000000u ? 620000 : 950000;
+    return QUAD_RAYS;
+}
 constexpr uint64_t PRIMARY_WAVE = 5000000;   // 2x2 samples: camera rays wave-uniform above (rc_launch_primary)
 size_t quad_lds(const DevScene& sc) { return (size_t)sc.max_stack * 16 * sizeof(uint2); }
-bool quad_ok(const DevScene& sc, const TraceWork& w, uint64_t rays, uint64_t limit)
+bool quad_ok(const DevScene& sc, const TraceWork& w, uint64_t rays, int mode)
 {
     if (w.ray_count || sc.max_stack > 128 || sc.n_nodes >= (1u << 25)) return false;
-    const uint64_t waves = 163840 / quad_lds(sc);
-    return waves >= 20 ? rays <= limit : rays * 20 <= QUAD_CAMERA * waves;
+    const uint64_t waves = 163840 / quad_lds(sc), limit = quad_limit(sc, mode);
+    return rays <= (waves >= 20 ? limit : std::min(limit, QUAD_RAYS * waves / 20));
 }
 // waves of 16 rays for `rays` rays in each of `groups`, a whole share for every XCD
 uint32_t quad_grid(uint64_t rays, uint32_t groups)
@@ -894,7 +900,7 @@ void rc_launch_primary(const DevScene& sc, const DevCamera& cam, uint4* gbuf, co
     // 0.52), 8.3M 0.68 / 0.68 (0.93 / 0.96), 33M 1.65 / 2.02 (2.26 / 2.95).  Counted frames keep the wave kernel at
     // any size, two-level structures the per-lane one.
     const bool two = sc.inst != nullptr, wt = sc.watertight != 0u;
-    if (!per_lane && quad_ok(sc, w, P.n_items, QUAD_CAMERA)) {
+    if (!per_lane && quad_ok(sc, w, P.n_items, MODE_PRIMARY)) {
         const dim3 g(quad_grid(P.n_items, 1));
         RC_LAUNCH_TW((k_quad<MODE_PRIMARY, RC_TWO, RC_WT>), g, dim3(64), quad_lds(sc), st, P, (uint32_t*)nullptr);
     } else if (sc.max_stack <= 128 && !per_lane && cam.ssaa > 1 && !two && (P.n_items > PRIMARY_WAVE || w.ray_count)) {
@@ -966,9 +972,9 @@ void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights&
     const bool split = L.n_point > 1 && (uint64_t)P.n_items * (uint64_t)L.n_point < (1ull << 31);
     P.light_groups = split ? (uint32_t)L.n_point : 1u;
     const bool turn = L.n_point > 1 && point_lights_in_turn(sc, n_samples_img);   // wave-uniform
-    const bool quad_point = kernels == RC_KERNELS_AUTO && quad_ok(sc, w, (uint64_t)P.n_items * (uint64_t)L.n_point, QUAD_POINT);
+    const bool quad_point = kernels == RC_KERNELS_AUTO && quad_ok(sc, w, (uint64_t)P.n_items * (uint64_t)L.n_point, MODE_POINT);
     const bool quad_rect = kernels == RC_KERNELS_AUTO && L.has_rect &&
-                           quad_ok(sc, w, (uint64_t)P.n_items * (uint64_t)L.area_samples, QUAD_RECT);
+                           quad_ok(sc, w, (uint64_t)P.n_items * (uint64_t)L.area_samples, MODE_RECT);
     P.setup = setup;
     if (L.n_point > 0 || L.has_rect) {
         // one setup entry per sample of the image (the item count is padded to whole tiles); every shadow kernel
