@@ -47,11 +47,17 @@ __global__ __launch_bounds__(256) void k_tonemap(const float4* rgba, uint32_t n,
     out[i] = make_uchar4(q[0], q[1], q[2], (uint8_t)floor(a * 255.0 + 0.5));
 }
 
-// Workgroup tile of 64 x 16 pixels, staged in LDS with the 13 pixels around it that the edge search can reach (border
+// Workgroup tile of 64 x FX_H pixels, staged in LDS with the 13 pixels around it that the edge search can reach (border
 // clamped): the search reads one pixel after the other, up to 48 of them, each of which had waited for memory.  The tile's
 // edge pixels are gathered first and blended by full waves: nearly every row of 64 pixels holds some, and a row's wave
-// would walk the search for those alone.  1080p with 8% edge pixels: 39 us from memory, 35 from LDS, 19 gathered.
-constexpr int FX_W = 64, FX_H = 16, FX_B = SEARCH + 1, FX_P = FX_W + 2 * FX_B;
+// would walk the search for those alone.  1080p with 8% edge pixels, 16 rows: 39 us from memory, 35 from LDS, 19 gathered.
+// 16 rows stage each pixel 3.7 times (4: 10.5 times), but an image of few such tiles lasts as long as one tile's rounds of
+// edge pixels.  Whole post pass, one pixel per thread from memory / 16 rows / 4 rows: noise of 128x128 11.6 / 19.7 / 11.9 us,
+// 480x640 18.7 / 23.1 / 15.9, 540x960 26.5 / 23.5 / 19.0, 720x1280 40.2 / 30.2 / 27.7, 1080p 72 / 42 / 50; hard-edged regions 12.7
+// / 16.7 / 11.7, 21.1 / 19.0 / 14.6, 30.8 / 19.0 / 17.1, 46.8 / 24.3 / 24.4, 86 / 32 / 45.  So 4 rows up to FX_SMALL pixels (and 65535
+// rows of tiles, the most that a grid takes).
+constexpr int FX_W = 64, FX_B = SEARCH + 1, FX_P = FX_W + 2 * FX_B;
+constexpr uint32_t FX_SMALL = 700000;
 
 // 77 R + 150 G + 29 B
 __device__ inline int luma(uint32_t p) { return (int)__builtin_amdgcn_udot4(p, 77u | (150u << 8) | (29u << 16), 0u, false); }
@@ -129,6 +135,7 @@ __device__ inline uchar4 fxaa_blend(const uint32_t* tile, int at)
     return make_uchar4(r[0], r[1], r[2], p >> 24);
 }
 
+template <int FX_H>
 __global__ __launch_bounds__(256) void k_fxaa(const uint32_t* in, int W, int H, uint32_t* out)
 {
     __shared__ uint32_t tile[(FX_H + 2 * FX_B) * FX_P];
@@ -175,9 +182,13 @@ void rc_launch_postprocess(const float* rgba, uint32_t w, uint32_t h, bool fxaa,
     uchar4* tm = reinterpret_cast<uchar4*>(fxaa ? scratch : out);
     hipLaunchKernelGGL(k_tonemap, dim3((n + 255) / 256), dim3(256), 0, st, reinterpret_cast<const float4*>(rgba), n,
                        tm);
-    if (fxaa)
-        hipLaunchKernelGGL(k_fxaa, dim3((w + FX_W - 1) / FX_W, (h + FX_H - 1) / FX_H), dim3(256), 0, st,
+    if (!fxaa) return;
+    auto run = [&](auto kernel, uint32_t rows) {
+        hipLaunchKernelGGL(kernel, dim3((w + FX_W - 1) / FX_W, (h + rows - 1) / rows), dim3(256), 0, st,
                            reinterpret_cast<const uint32_t*>(tm), (int)w, (int)h, reinterpret_cast<uint32_t*>(out));
+    };
+    if (n <= FX_SMALL && h <= 4u * 65535u) run(k_fxaa<4>, 4u);
+    else run(k_fxaa<16>, 16u);
 }
 
 // Fixed scratch of rc_postprocess_noalloc: the tone-mapped 8-bit image that FXAA reads, for images of at most
