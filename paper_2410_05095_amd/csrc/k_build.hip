@@ -886,7 +886,10 @@ namespace {
 
 constexpr int SAH_NB_MAX = 64;
 constexpr uint32_t SAH_SMALL = 512;
-constexpr uint32_t SAH_CHUNK = 2048;   // 1M triangles: binning passes 1.38 ms at 8192 (122 workgroups), 0.80 at 2048, 0.72 at 1024
+// Triangles per workgroup of the level-wise passes: enough workgroups on the first levels, against their fixed costs.
+// Whole builds at 1024 / 2048 / 4096: 20K triangles 1.15 / 1.21 / 1.33 ms, 100K 1.55 / 1.69 / 1.95, 1M 4.18 / 4.24 / 4.51, 7.3M 19.3 /
+// 20.4 / 20.8; binning at 1M 1.38 ms at 8192 (122 workgroups), 0.72 at 1024.
+constexpr uint32_t SAH_CHUNK = 1024;
 constexpr int SAH_BIN_WORDS = 8;   // ordered lo[3], hi[3], count, pad
 
 __device__ inline uint32_t f2o(float f)
