@@ -968,8 +968,12 @@ void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights&
     const bool big_rect = n_samples_img * (uint64_t)(L.has_rect ? L.area_samples : 0) >= 3000000u;
     const bool wave_point = wave_ok && (kernels == RC_KERNELS_WAVE || big_point);
     const bool wave_rect = wave_ok && (kernels == RC_KERNELS_WAVE || big_rect);
-    // one unit of work per sample and light in the per-lane kernel too, where the unit count fits 32 bits
-    const bool split = L.n_point > 1 && (uint64_t)P.n_items * (uint64_t)L.n_point < (1ull << 31);
+    // one unit of work per sample and light in the per-lane kernel too, where the unit count fits 32 bits; but two lights
+    // of a small tree in turn, whose walks are too short for a second claim and set-up to pay (units / in turn, ms, 2
+    // lights: 1.3K triangles 0.3M samples 0.095 / 0.085, 1.15M 0.195 / 0.166; 20K 0.77M 0.172 / 0.151, 1.15M 0.197 / 0.164; 60K
+    // 1.15M 0.202 / 0.173; 3 lights within 4%, 200K triangles faster as units)
+    const bool split = (L.n_point > 2 || (L.n_point == 2 && sc.n_tris >= 100000u)) &&
+                       (uint64_t)P.n_items * (uint64_t)L.n_point < (1ull << 31);
     P.light_groups = split ? (uint32_t)L.n_point : 1u;
     const bool turn = L.n_point > 1 && point_lights_in_turn(sc, n_samples_img);   // wave-uniform
     const bool quad_point = kernels == RC_KERNELS_AUTO && quad_ok(sc, w, (uint64_t)P.n_items * (uint64_t)L.n_point, MODE_POINT);
