@@ -249,8 +249,9 @@ enum {
                                   ssaa = 2 from 5M samples; point-light shadow rays from samples x (lights +
                                   1) = 3.5M and rect-light shadow rays from 3M rays per frame; BVH depth <=
                                   42, under 2^25 nodes and 2^32 bytes of packed triangles) or four lanes
-                                  to a ray (passes of up to 600,000 camera or point-light rays, 950,000
-                                  rect-light rays); same results outside the FP32 band, for comparison.
+                                  to a ray (small passes: at most 600,000 camera or point-light rays, 950,000
+                                  rect-light rays, fewer in two-level structures and with many triangles);
+                                  same results outside the FP32 band, for comparison.
                                   rc_render_batch: the three-pass form's shadow rays one ray per lane (its
                                   results are the same either way; takes precedence over RC_FLAG_WAVE) */
     RC_FLAG_NO_SHADE = 8u,     /* rc_render: stop after the visibility stages; d_rgba and d_sample_rgba are

@@ -53,8 +53,10 @@ inline uint32_t claim_size(uint64_t n_work, int grid, uint32_t per_wave, uint32_
 }
 
 // Waves per SIMD: 6 for flat-tree camera rays (80 registers; 3% faster than 5), 5 for two-level structures (96; their
-// camera rays at 720p 0.265 ms against 0.283 at the natural 4 and 0.293 at 6, on 1.1M triangles), the compiler's choice
-// elsewhere (flat shadow rays at 6: 2 to 5% slower).
+// camera rays at 720p 0.265 ms against 0.283 at the natural 4 and 0.293 at 6, on 1.1M triangles; their point-light shadow
+// rays at 5 / 4 within 3% of each other from 0.5M samples on and 3 to 7% slower at 0.23M, which go four lanes to a ray
+// by default: 1.1M triangles, 4 lights, 640x360 0.39 / 0.40, 960x540 0.61 / 0.63, 1080p 1.56 / 1.58 ms; 7.3M 0.51 / 0.50, 0.70 /
+// 0.70, 1.85 / 1.88), the compiler's choice elsewhere (flat shadow rays at 6: 2 to 5% slower).
 template <int MODE, bool TWO, bool WT, bool COUNT>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WT ? 1 : TWO ? 5 : MODE == MODE_PRIMARY ? 6 : 1))) void k_trace(KParams P)
 {
@@ -963,6 +965,13 @@ void rc_launch_shadow(const DevScene& sc, const DevCamera& cam, const DevLights&
     //             a sample's by one lane: 0.52M 0.84 / 1.36 (0.61 / 1.01), 2.07M 1.54 / 1.33 (1.28 / 0.88)
     //   rect light, 1 sample per pixel at 1080p 0.56 / 0.58 (0.34 / 0.40), 2 samples 0.71 / 0.58 (0.48 / 0.45), 1
     //             sample at 2160p 1.17 / 0.88 (0.88 / 0.69)
+    // Two-level structures cross somewhat earlier; the same lines serve them (per-lane / wave on 1.1M triangles, 200K in
+    // brackets):
+    //   1 light   0.92M samples 0.35 / 0.35 (0.25 / 0.25), 2.07M 0.51 / 0.32 (0.35 / 0.29)
+    //   2 lights  0.52M 0.42 / 0.37 (0.26 / 0.31), 0.92M 0.52 / 0.44 (0.32 / 0.30), 2.07M 0.82 / 0.46 (0.50 / 0.35)
+    //   4 lights  0.23M 0.40 / 0.45 (0.23 / 0.32), 0.52M 0.60 / 0.48 (0.33 / 0.32), 0.92M 0.87 / 0.55 (0.45 / 0.34)
+    //   rect light, 1.8M rays 0.36 / 0.40 (0.21 / 0.27), 3.7M 0.57 / 0.46 (0.28 / 0.31), 8.3M 0.90 / 0.61 (0.42 / 0.40), 16.6M
+    //             1.69 / 1.13 (0.73 / 0.60), 133M 9.76 / 5.47 (3.31 / 2.24)
     const uint64_t n_samples_img = (uint64_t)cam.width * cam.height * cam.ssaa * cam.ssaa;
     const bool big_point = rc_wave_work(n_samples_img, (uint64_t)L.n_point) >= RC_WAVE_WORK;
     const bool big_rect = n_samples_img * (uint64_t)(L.has_rect ? L.area_samples : 0) >= 3000000u;

@@ -601,7 +601,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC))) void
 // 16-byte read per tile and tap feeds S instructions of each of its row or column of tiles.  The first layer reads the
 // BF16 features; the decoder's upsample + concat is fused into the halo load as in the BF16 kernel.
 // 540x960 inference: 2.43 ms when each instruction took one 4-byte LDS read and one 4-byte load from the weights in
-// memory (48 TFLOP/s), 1.30 ms now (90; 1080x1920 4.4 ms, 106 TFLOP/s).  The next chunk's halo, or halo and weights, held
+// memory (48 TFLOP/s), 1.21 ms now (97; 1080x1920 4.4 ms, 106 TFLOP/s).  The next chunk's halo, or halo and weights, held
 // in registers under this chunk's instructions measured 6% and 60% slower.
 constexpr int F32_NB = 64;   // output channels of a block: 16 NT = min(Cout, F32_NB)
 
@@ -1295,8 +1295,11 @@ void unet_conv3x3_direct(const ConvArgs& a, hipStream_t st)
 }
 
 namespace {
-// channels per workgroup: 32 x 32 (32 x 48 of the 96-channel input), 64 x 32 beyond; chunks so that the workgroups of
-// all channel groups fill the 256 CUs once at the 3 (32 output channels) or 2 that LDS admits on each
+// channels per workgroup: 32 x 32 (32 x 48 of the 96-channel input), 64 x 32 beyond; chunks so that the workgroups of all
+// channel groups fill the 256 CUs once, at three (32 output channels) or two workgroups of 3 waves to a CU.  Registers
+// hold that many at once, 12 and 8 waves (OCC 3 and 2; the 25 to 33 KB of LDS would admit 4 to 6); a second, partly
+// filled round and more partial sums to add cost more than they balance.  Whole 8x512^2 step at 768 / 512 workgroups 3.08 ms;
+// 512 / 512 3.07, 1024 / 512 3.12, 1280 / 512 3.13, 768 / 768 3.31, 768 / 384 3.28.
 struct WgradShape {
     int co_t, ci_t, groups, ci_groups, tiles_per_chunk, chunks;
 };

@@ -254,9 +254,6 @@ template <bool TWO, bool LANE_BASE, class Stack>
 __device__ inline void trav_visit_node(const DevScene& sc, TravRay& r, TravState& s, Stack& st, bool any,
                                        TravWorld* w = nullptr)
 {
-    // The near and far plane blocks come from addresses picked by the direction's signs, instead of 24 selects.  The
-    // signs and the far reciprocals (inv * RC_FAR_GROW, as rc_ray_inv) are worked out here on each visit: kept in
-    // registers they cost occupancy or spills (volatile, so that the compiler does not move them out of the loop).
     float4 nr[3], fr[3];
     float invf[3];
     uint32_t up[3];
