@@ -37,7 +37,7 @@ ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 # the copy-kernel calibration), keyed by (workload, spp, hash of the traversal kernel sources); the
 # value only applies while those sources are unchanged (summaries under profiles/).
 MEASURED_TRAFFIC = {
-    ("big_7M", 64, "05e74b2ae40401df:3be95a1ed7a0f059:a90129df91e8c72b:b795ca1ca70e7499"): 442_300_000,
+    ("big_7M", 64, "0a5ebfd83cb6dd46:3be95a1ed7a0f059:9d2bcf07dae4a482:6f05da23292e53a3"): 442_400_000,
 }
 
 

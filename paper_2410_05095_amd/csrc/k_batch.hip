@@ -358,7 +358,7 @@ __global__ __launch_bounds__(256) void k_batch_setup(BatchParams P)
 // Point-light shadow rays of the three-kernel form by wave-uniform walks (wave_occluded): a unit of work is 64
 // consecutive samples of one view (an 8x8-pixel tile, or 4x4 pixels x 4 samples, whatever the tuning's tile) and
 // one of its lights.  Node and triangle records come through the scalar cache once per wave, where the per-lane
-// kernel's divergent 16-byte loads keep the texture units 91% busy and its vector pipe 70%.  The walk takes the
+// kernel's divergent 16-byte loads keep the texture units 91% busy and its vector pipe 66%.  The walk takes the
 // per-lane pass's decisions ray by ray (wave_occluded, EXACT), so that a view's masks do not depend on the pass: 64
 // views of four scenes 14.98 ms per lane, 9.89 ms with every triangle hit counted, 10.5 ms so.
 template <bool BIG, bool COUNT>
